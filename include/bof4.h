@@ -330,24 +330,23 @@ size_t bof4_gemv_outlier_table_bytes(uint64_t rows, uint64_t cols, uint64_t n_ou
  *     y[t][r] = sum_c W^[r][c] * x[t][c],     W^ = what bof4_dequantize returns for the same quantised tensor.
  * Every product of two bfloat16 numbers is exact in binary32; the sums are binary32 (matrix cores, up to 128 tokens
  * per pass over the codes) in a fixed order: y is bit-reproducible and lies within (cols + 64) * 2^-24 * sum_c |W^ x|
- * of the exact sum (an outlier position counts with its decoded placeholder as well as with its value), and is exact
- * whenever every partial sum is a binary32 number.  The order of the additions depends on rows, cols and n_tokens
- * (how the columns are dealt out over workgroups), so the same token may differ in its last bits between calls with
- * different n_tokens; equal calls give equal bits.
+ * of the exact sum, and is exact whenever every partial sum is a binary32 number.  The order of the additions depends
+ * on rows, cols and n_tokens (how the columns are dealt out over workgroups), so the same token may differ in its last
+ * bits between calls with different n_tokens; equal calls give equal bits.
  *
  * The matrix is read from a copy in the order of the matrix cores' operands, made once per matrix by bof4_gemm_pack
  * from what bof4_quantize wrote for n = rows * cols (row-major [rows x cols], cols a multiple of block):
  * bof4_gemm_packed_bytes(rows, cols) bytes (device, 16-byte aligned) - per tile of 32 rows x 64 columns 1024 bytes of
  * codes and 64 binary16 constants, 0.5625 bytes per weight; BOF4_ERR_WORKSPACE if the buffer is smaller.
  *   packed_dev  that copy
- *   table_dev   what bof4_gemm_outlier_table made of the outlier list (from the unpacked codes and constants): layout
- *               and size of bof4_gemv's table (bof4_gemv_outlier_table_bytes), but per entry
- *               (bfloat16(value) - bfloat16(constant * level)); may be NULL when n_outliers == 0
+ *   table_dev   what bof4_gemm_outlier_table made of the outlier list for these rows, cols and n_outliers: the size of
+ *               bof4_gemv's table (bof4_gemv_outlier_table_bytes), its contents the values in bfloat16, sorted into
+ *               the products' tiles of 32 rows x 64 columns; may be NULL when n_outliers == 0
  *   x_dev       n_tokens x cols bfloat16 (device, 16-byte aligned), y_dev  n_tokens x rows binary32 (device)
  *   ws_dev      bof4_gemm_workspace_bytes(rows, cols, n_tokens) bytes (device, 256-byte aligned),
- *               BOF4_ERR_WORKSPACE if smaller: x reordered for the matrix cores and transposed for the list (4 bytes
- *               per token slot and column, token slots in 32s), and - for matrices with too few rows to fill the
- *               chip - the partial results of the workgroups that share a row
+ *               BOF4_ERR_WORKSPACE if smaller: x reordered for the matrix cores and as much again (4 bytes per token
+ *               slot and column, token slots in 32s), and - for matrices with too few rows to fill the chip - the
+ *               partial results of the workgroups that share a row
  * Limits: cols <= 32768 and a multiple of 32, n_tokens <= 65536.  The codes are read once per 128 tokens.  All three
  * calls only enqueue.
  */

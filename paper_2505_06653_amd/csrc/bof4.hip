@@ -1112,11 +1112,10 @@ size_t bof4_gemv_outlier_table_bytes(uint64_t rows, uint64_t cols, uint64_t n_ou
 }  // extern "C"
 
 namespace {
-// rounded = false: the entries of bof4_gemv (value - m * level); true: those of bof4_gemm (both terms in bfloat16).
-int outlier_table_impl(bool rounded, const uint8_t* codes_dev, const uint16_t* scales_dev, uint64_t rows,
-                       uint64_t cols, uint32_t block, const double* cb_host, const int64_t* out_idx_dev,
-                       const uint16_t* out_val_dev, uint64_t n_outliers, void* table_dev, size_t table_bytes,
-                       void* stream) {
+// The checks that the two outlier tables share; BOF4_OK or the error.
+int outlier_table_check(const uint8_t* codes_dev, const uint16_t* scales_dev, uint64_t rows, uint64_t cols,
+                        uint32_t block, const double* cb_host, const int64_t* out_idx_dev,
+                        const uint16_t* out_val_dev, uint64_t n_outliers, void* table_dev, size_t table_bytes) {
     if (!codes_dev || !scales_dev || !table_dev || (n_outliers > 0 && (!out_idx_dev || !out_val_dev)))
         return fail(BOF4_ERR_ARG, "outlier table: null pointer");
     if (!valid_block(block) || rows == 0 || cols == 0 || cols % block != 0)
@@ -1128,21 +1127,29 @@ int outlier_table_impl(bool rounded, const uint8_t* codes_dev, const uint16_t* s
         return fail(BOF4_ERR_ARG, "outlier table: codebook must be 16 finite ascending levels");
     if (!aligned(out_idx_dev, 8) || !aligned(out_val_dev, 2) || !aligned(scales_dev, 2) || !aligned(table_dev, 8))
         return fail(BOF4_ERR_ARG, "outlier table: misaligned pointer (the table needs 8 bytes)");
-    const GemvTableLayout L = gemv_table_layout(rows, strips, n_outliers);
-    if (table_bytes < L.total) return fail(BOF4_ERR_WORKSPACE, "outlier table: table buffer too small");
-    hipStream_t s = (hipStream_t)stream;
-    const CodebookArgs cb = make_codebook_args(cb_host);
-    uint32_t log2_block = 5;
-    while ((1u << log2_block) < block) ++log2_block;
-    const uint64_t count = rows * strips + 1;
-    hipLaunchKernelGGL(outlier_strip_offsets_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, s,
-                       out_idx_dev, (uint32_t)n_outliers, rows, cols, (uint32_t)strips, (uint32_t*)table_dev);
-    if (n_outliers > 0)
-        hipLaunchKernelGGL(outlier_delta_kernel, dim3((uint32_t)((n_outliers + 255) / 256)), dim3(256), 0, s,
-                           codes_dev, scales_dev, rows * cols, cols, log2_block, cb, out_idx_dev, out_val_dev,
-                           (uint32_t)n_outliers, rounded ? 1u : 0u, (uint2*)((char*)table_dev + L.entries));
-    HIP_TRY(hipGetLastError());
+    if (table_bytes < gemv_table_layout(rows, strips, n_outliers).total)
+        return fail(BOF4_ERR_WORKSPACE, "outlier table: table buffer too small");
     return BOF4_OK;
+}
+
+// The table of bof4_gemm: offsets per tile of 32 rows and group of chunks, one closing offset, then the entries (4 bytes
+// each) - inside the bytes of the gemv table for the same matrix and list: the groups are as fine as fits, one
+// chunk each wherever rows is a multiple of 32 or the list is longer than the offsets need in addition.
+struct GemmTableLayout {
+    GemmListGeometry lg;
+    uint32_t row_tiles;
+    size_t entries;
+};
+GemmTableLayout gemm_table_layout(uint64_t rows, uint64_t cols, uint64_t n_outliers) {
+    GemmTableLayout T;
+    const uint64_t total = gemv_table_layout(rows, (cols + GEMV_STRIP - 1) / GEMV_STRIP, n_outliers).total;
+    const uint64_t row_tiles = (rows + GEMM_ROWS - 1) / GEMM_ROWS, chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK;
+    T.row_tiles = (uint32_t)row_tiles;
+    for (T.lg.log2_group = 0;; ++T.lg.log2_group) {  // ends: with 2^5 chunks per group there is one group per strip
+        T.lg.n_groups = (uint32_t)((chunks + (1u << T.lg.log2_group) - 1) >> T.lg.log2_group);
+        T.entries = (row_tiles * T.lg.n_groups + 1) * 4;
+        if (T.entries + 4 * n_outliers <= total || T.lg.log2_group == 5) return T;
+    }
 }
 
 // Tiles of 32 rows per wave: with two, every word of x read serves 64 rows, at twice the accumulators.  Measured
@@ -1164,10 +1171,10 @@ uint32_t gemm_split(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     return (uint32_t)(split < 1 ? 1 : split);
 }
 
-// Workspace of bof4_gemm: x in the order of the products, x transposed (for the list), the partial results.
+// Workspace of bof4_gemm: x in the order of the products, room for a second copy of it, the partial results.
 constexpr uint32_t GEMM_MAX_TOKENS = 65536;
 struct GemmWsLayout {
-    size_t xp, xt, part, total;
+    size_t xp, part, total;
 };
 GemmWsLayout gemm_ws_layout(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     const uint64_t n_pad = (n_tokens + GEMM_TOKENS - 1) / GEMM_TOKENS * GEMM_TOKENS;
@@ -1175,8 +1182,7 @@ GemmWsLayout gemm_ws_layout(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     const uint64_t per_launch = n_pad < GEMM_TOKENS * GEMM_MAX_TILES ? n_pad : GEMM_TOKENS * GEMM_MAX_TILES;
     GemmWsLayout L;
     L.xp = 0;
-    L.xt = align_up(L.xp + n_pad * chunks * GEMM_CHUNK * 2, 256);
-    L.part = align_up(L.xt + cols * n_pad * 2, 256);
+    L.part = align_up(align_up(L.xp + n_pad * chunks * GEMM_CHUNK * 2, 256) + cols * n_pad * 2, 256);  // (as documented)
     L.total = L.part + (split > 1 ? split * per_launch * rows * 4 : 0);
     return L;
 }
@@ -1188,16 +1194,38 @@ int bof4_gemv_outlier_table(const uint8_t* codes_dev, const uint16_t* scales_dev
                             uint32_t block, const double* cb_host, const int64_t* out_idx_dev,
                             const uint16_t* out_val_dev, uint64_t n_outliers, void* table_dev, size_t table_bytes,
                             void* stream) {
-    return outlier_table_impl(false, codes_dev, scales_dev, rows, cols, block, cb_host, out_idx_dev, out_val_dev,
-                              n_outliers, table_dev, table_bytes, stream);
+    const int rc = outlier_table_check(codes_dev, scales_dev, rows, cols, block, cb_host, out_idx_dev, out_val_dev,
+                                       n_outliers, table_dev, table_bytes);
+    if (rc != BOF4_OK) return rc;
+    hipStream_t s = (hipStream_t)stream;
+    const uint64_t strips = (cols + GEMV_STRIP - 1) / GEMV_STRIP, count = rows * strips + 1;
+    const CodebookArgs cb = make_codebook_args(cb_host);
+    uint32_t log2_block = 5;
+    while ((1u << log2_block) < block) ++log2_block;
+    hipLaunchKernelGGL(outlier_strip_offsets_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, s,
+                       out_idx_dev, (uint32_t)n_outliers, rows, cols, (uint32_t)strips, (uint32_t*)table_dev);
+    if (n_outliers > 0)
+        hipLaunchKernelGGL(outlier_delta_kernel, dim3((uint32_t)((n_outliers + 255) / 256)), dim3(256), 0, s,
+                           codes_dev, scales_dev, rows * cols, cols, log2_block, cb, out_idx_dev, out_val_dev,
+                           (uint32_t)n_outliers,
+                           (uint2*)((char*)table_dev + gemv_table_layout(rows, strips, n_outliers).entries));
+    HIP_TRY(hipGetLastError());
+    return BOF4_OK;
 }
 
 int bof4_gemm_outlier_table(const uint8_t* codes_dev, const uint16_t* scales_dev, uint64_t rows, uint64_t cols,
                             uint32_t block, const double* cb_host, const int64_t* out_idx_dev,
                             const uint16_t* out_val_dev, uint64_t n_outliers, void* table_dev, size_t table_bytes,
                             void* stream) {
-    return outlier_table_impl(true, codes_dev, scales_dev, rows, cols, block, cb_host, out_idx_dev, out_val_dev,
-                              n_outliers, table_dev, table_bytes, stream);
+    const int rc = outlier_table_check(codes_dev, scales_dev, rows, cols, block, cb_host, out_idx_dev, out_val_dev,
+                                       n_outliers, table_dev, table_bytes);
+    if (rc != BOF4_OK) return rc;
+    const GemmTableLayout T = gemm_table_layout(rows, cols, n_outliers);
+    hipLaunchKernelGGL(gemm_list_kernel, dim3(T.row_tiles), dim3(256), 0, (hipStream_t)stream, out_idx_dev, out_val_dev,
+                       (uint32_t)n_outliers, rows, (uint32_t)cols, T.lg, (uint32_t*)table_dev,
+                       (uint32_t*)((char*)table_dev + T.entries));
+    HIP_TRY(hipGetLastError());
+    return BOF4_OK;
 }
 
 size_t bof4_gemm_workspace_bytes(uint64_t rows, uint64_t cols, uint32_t n_tokens) {
@@ -1248,9 +1276,9 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
         return fail(BOF4_ERR_ARG, "bof4_gemm: misaligned pointer (packed matrix and x need 16 bytes, the table 8, the workspace 256)");
     const GemmWsLayout L = gemm_ws_layout(rows, cols, n_tokens);
     if (ws_bytes < L.total) return fail(BOF4_ERR_WORKSPACE, "bof4_gemm: workspace too small");
+    const GemmTableLayout T = gemm_table_layout(rows, cols, n_outliers);
     const uint32_t* offsets_dev = (const uint32_t*)table_dev;
-    const uint2* entries_dev =
-        table_dev ? (const uint2*)((const char*)table_dev + gemv_table_layout(rows, strips, n_outliers).entries) : nullptr;
+    const uint32_t* entries_dev = table_dev ? (const uint32_t*)((const char*)table_dev + T.entries) : nullptr;
     hipStream_t s = (hipStream_t)stream;
     const CodebookArgs cb = make_codebook_args(cb_host);
     const uint32_t split = gemm_split(rows, cols, n_tokens);
@@ -1260,13 +1288,11 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
     const uint32_t row_groups = (uint32_t)(gemm_row_tiles(rows) / per_wg_tiles);
     const uint32_t n_pad = (n_tokens + GEMM_TOKENS - 1) / GEMM_TOKENS * GEMM_TOKENS, tok_tiles = n_pad / GEMM_TOKENS;
     const uint4* xp = (const uint4*)((char*)ws_dev + L.xp);
-    const uint16_t* xt = (const uint16_t*)((char*)ws_dev + L.xt);
     float* part = (float*)((char*)ws_dev + L.part);
     {
         const uint64_t total = (uint64_t)tok_tiles * chunks * 256;
         hipLaunchKernelGGL(gemm_pack_x_kernel, dim3((uint32_t)((total + 255) / 256)), dim3(256), 0, s,
-                           (const uint16_t*)x_dev, n_tokens, (uint32_t)cols, chunks, n_pad, (uint4*)xp,
-                           n_outliers > 0 ? (uint16_t*)xt : nullptr);
+                           (const uint16_t*)x_dev, n_tokens, (uint32_t)cols, chunks, n_pad, (uint4*)xp);
     }
     timing_begin(s);
     for (uint32_t tile0 = 0; tile0 < tok_tiles;) {
@@ -1278,7 +1304,7 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
 #define BOF4_LAUNCH_GEMM(R_, NT_, OUT_)                                                                           \
     hipLaunchKernelGGL((gemm_kernel<R_, NT_, OUT_>), dim3(row_groups, split), dim3(64 * waves), 0, s,             \
                        (const char*)packed_dev, (uint32_t)rows, (uint32_t)cols, cb, offsets_dev, entries_dev,     \
-                       (uint32_t)n_outliers, (uint32_t)strips, xp, xt, n_pad, tile0, nt, dst);
+                       (uint32_t)n_outliers, T.lg, T.row_tiles, xp, tile0, nt, dst);
 #define BOF4_LAUNCH_GEMM_NT(R_, OUT_)                                                                             \
     if (nt_tiles == 4) { BOF4_LAUNCH_GEMM(R_, 4, OUT_) } else if (nt_tiles == 3) { BOF4_LAUNCH_GEMM(R_, 3, OUT_) } \
     else if (nt_tiles == 2) { BOF4_LAUNCH_GEMM(R_, 2, OUT_) } else { BOF4_LAUNCH_GEMM(R_, 1, OUT_) }

@@ -155,6 +155,21 @@ def test_gemm_dense_outlier_rows_take_several_rounds_and_empty_rows_none(n_token
     assert np.max(np.abs(y_g[:, 4:12] - y_none[:, 4:12])) > 1e-3  # the list matters
 
 
+@pytest.mark.parametrize("rows,cols,k", [(1, 4160, 1), (3, 2112, 2), (17, 8192, 3), (33, 6176, 5), (33, 6176, 3000),
+                                         (64, 32768, 4), (40, 64, 2560)])
+def test_gemm_list_with_few_entries_and_with_all_positions(rows, cols, k):
+    """Row counts for which the list's offsets cover 1, 2, 4 or 32 chunks of 64 columns each (they have to fit the table's
+    size), with the matrix's first and last position always listed; the last case lists every position."""
+    block = 32
+    cb, codes, scales, _, _ = quantized(rows, cols, block, 1, 0, seed=85)
+    rng = np.random.default_rng(k)
+    oi = rng.choice(rows * cols, k, replace=False)
+    oi[: min(k, 2)] = [rows * cols - 1, 0][: min(k, 2)]
+    oi = np.unique(oi).astype(np.int64)
+    ov = (rng.standard_normal(oi.size).astype(np.float32)).astype(np.float16).view(np.uint16)
+    check(cb, codes, scales, oi, ov, rows, cols, block, rand_x(5, cols, 3))
+
+
 @pytest.mark.parametrize("opq", [0, 1])
 def test_gemm_a_token_that_is_not_finite_stays_on_its_own(opq):
     """One token carries an infinity: its own results are not finite (every row multiplies it), every other token's are
