@@ -1171,6 +1171,45 @@ uint32_t gemm_split(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     return (uint32_t)(split < 1 ? 1 : split);
 }
 
+// Where gemm_wide_kernel takes the product over from gemm_kernel.  It computes whole groups of 128 tokens and costs the
+// same for one token of a group as for 128, and it starts later; gemm_kernel takes 32 tokens at a time.  Measured with
+// a list, gemm_kernel / the wide one in us:
+//   2000 tokens: 4096 x 4096 286 / 105, 22016 x 4096 888 / 547, 57344 x 8192 3075 / 2475, 8000 x 1024 155 / 66
+//    300 tokens: 4096 x 4096 53 / 39, 12288 x 4096 84 / 90, 22016 x 4096 154 / 173, 10240 x 8192 166 / 102, 8000 x 1024 28 / 30
+//    256 tokens: 22016 x 4096 117 / 91, 4096 x 11008 69 / 49, 57344 x 8192 390 / 338, 12288 x 4096 64 / 60, 8000 x 1024 21 / 30
+//    160 tokens: 12288 x 4096 49 / 57, 57344 x 8192 296 / 335
+//    128 tokens: 10240 x 8192 65 / 49, 57344 x 8192 204 / 184, 4096 x 4096 22 / 31, 8192 x 8192 41 / 42
+bool gemm_is_wide(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
+    const uint64_t wg_tokens = GEMM_WIDE_TOK_TILES * GEMM_TOKENS, wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS;
+    const uint64_t tok_groups = (n_tokens + wg_tokens - 1) / wg_tokens;
+    if (cols < 512 || (rows + wg_rows - 1) / wg_rows * tok_groups * GEMM_WIDE_MAX_SPLIT >= (1ull << 31)) return false;
+    const bool full = tok_groups * wg_tokens * 10 <= n_tokens * 11;  // hardly a token slot of the groups is empty
+    if (n_tokens <= wg_tokens) return full && rows >= cols && rows * cols > (1ull << 26);
+    if (rows * cols >= (1ull << 27)) return full;  // here it gains least
+    return n_tokens > 320 || (n_tokens > 256 && (cols >= 6144 || rows <= 4096)) ||
+           (full && (rows >= 16384 || cols >= 6144));
+}
+// Over how many workgroups its columns are split: what the model of its time says is fastest - rounds of 256 workgroups
+// (one per compute unit: its LDS), 1.4 us per chunk and 8 us to start and end, the partial results at 4 TB/s.
+struct GemmWideSplit {
+    uint32_t split, per_split;  // workgroups along the columns, chunks each
+};
+GemmWideSplit gemm_wide_split(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
+    const uint64_t wg_tokens = GEMM_WIDE_TOK_TILES * GEMM_TOKENS, wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS;
+    const uint64_t groups = (rows + wg_rows - 1) / wg_rows * ((n_tokens + wg_tokens - 1) / wg_tokens);
+    const uint64_t chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK;
+    GemmWideSplit best = {1, (uint32_t)chunks};
+    double best_time = 0.0;
+    for (uint64_t want = 1; want <= GEMM_WIDE_MAX_SPLIT && want * 8 <= chunks; ++want) {
+        const uint64_t per = (chunks + want - 1) / want, split = (chunks + per - 1) / per;
+        const double rounds = (double)((groups * split + 255) / 256);
+        const double t = rounds * (6.0 + (double)per) * 1.4 +
+                         (split > 1 ? 4.0 + (double)(2 * split + 1) * (double)(n_tokens * rows) * 4.0 / 4e6 : 0.0);
+        if (want == 1 || t < best_time) best = {(uint32_t)split, (uint32_t)per}, best_time = t;
+    }
+    return best;
+}
+
 // Workspace of bof4_gemm: x in the order of the products, room for a second copy of it, the partial results.
 constexpr uint32_t GEMM_MAX_TOKENS = 65536;
 struct GemmWsLayout {
@@ -1183,7 +1222,9 @@ GemmWsLayout gemm_ws_layout(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     GemmWsLayout L;
     L.xp = 0;
     L.part = align_up(align_up(L.xp + n_pad * chunks * GEMM_CHUNK * 2, 256) + cols * n_pad * 2, 256);  // (as documented)
-    L.total = L.part + (split > 1 ? split * per_launch * rows * 4 : 0);
+    const uint64_t wide = gemm_is_wide(rows, cols, n_tokens) ? gemm_wide_split(rows, cols, n_tokens).split : 1;
+    const uint64_t part = split > 1 ? split * per_launch * rows : 0, wide_part = wide > 1 ? wide * n_tokens * rows : 0;
+    L.total = L.part + 4 * (part > wide_part ? part : wide_part);
     return L;
 }
 }  // namespace
@@ -1295,6 +1336,29 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
                            (const uint16_t*)x_dev, n_tokens, (uint32_t)cols, chunks, n_pad, (uint4*)xp);
     }
     timing_begin(s);
+    if (gemm_is_wide(rows, cols, n_tokens)) {
+        const GemmWideSplit W = gemm_wide_split(rows, cols, n_tokens);
+        const uint32_t tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
+        const uint32_t wide_groups = (T.row_tiles + GEMM_WIDE_WAVES - 1) / GEMM_WIDE_WAVES;
+        // the matrix cores' chain of additions is no longer than an eighth of the columns, as with eight waves to a row
+        const uint32_t eighth = (chunks + 7) / 8, flush = eighth < 8 ? 8 : eighth;
+        float* dst = W.split > 1 ? part : y_dev;
+#define BOF4_LAUNCH_WIDE(OUT_)                                                                                       \
+    hipLaunchKernelGGL((gemm_wide_kernel<OUT_>), dim3(tok_groups * wide_groups * W.split), dim3(64 * GEMM_WIDE_WAVES), \
+                       0, s, (const char*)packed_dev, (uint32_t)rows, (uint32_t)cols, cb, offsets_dev, entries_dev,  \
+                       (uint32_t)n_outliers, T.lg, T.row_tiles, (uint32_t)gemm_row_tiles(rows), xp, tok_tiles,       \
+                       tok_groups, W.per_split, flush, n_tokens, dst);
+        if (n_outliers > 0) { BOF4_LAUNCH_WIDE(true) } else { BOF4_LAUNCH_WIDE(false) }
+#undef BOF4_LAUNCH_WIDE
+        if (W.split > 1) {
+            const uint64_t count = (uint64_t)n_tokens * rows;
+            hipLaunchKernelGGL(gemm_sum_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, s, part, W.split,
+                               count, y_dev);
+        }
+        timing_end(s);
+        HIP_TRY(hipGetLastError());
+        return BOF4_OK;
+    }
     for (uint32_t tile0 = 0; tile0 < tok_tiles;) {
         const uint32_t left = tok_tiles - tile0, nt_tiles = left >= 4 ? 4 : left;
         const uint32_t t0 = tile0 * GEMM_TOKENS;

@@ -22,6 +22,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 
 #include "bof4_device.h"
@@ -353,6 +354,251 @@ __global__ __launch_bounds__(64 * GEMM_MAX_WAVES) void gemm_kernel(
                 const uint32_t i = idx >> 6, l = idx & 63;
                 const uint32_t mr = 8 * (i >> 2) + 4 * (l >> 5) + (i & 3u), n = 32 * t + (l & 31);
                 if (r0 + mr < rows && n < n_tokens) out[(uint64_t)n * rows + r0 + mr] = s;
+            }
+        }
+    }
+}
+
+// Many tokens: the same product with a tile of 256 rows x 128 tokens per workgroup of eight waves.  gemm_kernel reads
+// all of x once per 64 rows (0.8 GB per 128 tokens through a Llama-7B-shaped block, and it ran at the rate at which the
+// caches deliver that); here the decoded weights and x are shared through LDS, so x is read once per 256 rows and a
+// weight is decoded once per 128 tokens by one wave.
+//   A step is one chunk of 64 columns.  Each wave decodes its one row tile of the chunk after the next into LDS (list
+// entries are written over their placeholders there: a wave's LDS accesses are carried out in order, so nothing is
+// waited for), carries its share of that chunk's x over, and multiplies two row tiles with two token tiles of the
+// current chunk (four waves by two).  The step goes in quarters - one 16-byte word of every operand -, and the LDS
+// reads of a quarter are under way while the one before is multiplied, across the step's barrier too: that is what the
+// third buffer is for.
+//   The matrix cores' chain of additions is cut every `flush` chunks and added to a second set of accumulators: the
+// error of the sums stays that of gemm_kernel, whose waves each take an eighth of the columns.
+//   2000 tokens with a list, gemm_kernel -> this: 4096 x 4096 286 -> 105 us, 22016 x 4096 888 -> 547, 10240 x 8192
+// 973 -> 511, 57344 x 8192 3075 -> 2475 (760 TFLOP/s).  A step takes 1.3 us, 0.5 of them in the matrix cores; leaving out
+// any one of look-ups, operand reads, stores or three quarters of the products shortens it by a tenth only, so it
+// is the sum of a wave's dependent stages at two waves per SIMD that bounds it, and no single unit.
+// The weights are the second operand here: accumulator i of lane l is token 8 (i / 4) + 4 (l / 32) + i % 4 and row
+// l % 32, so that a store of a wave writes two runs of 128 bytes.
+constexpr uint32_t GEMM_WIDE_WAVES = 8, GEMM_WIDE_TOK_TILES = 4;  // a row tile per wave; token tiles per workgroup
+constexpr uint32_t GEMM_WIDE_MAX_SPLIT = 16;
+constexpr uint32_t GEMM_TILE_WORDS = 4 * 64;                      // 16-byte words of one tile's bfloat16 operand
+template <bool OUTLIERS>
+__global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_wide_kernel(
+    const char* __restrict__ packed, uint32_t rows, uint32_t cols, CodebookArgs cb, const uint32_t* __restrict__ list_ptr,
+    const uint32_t* __restrict__ entries, uint32_t n_out, GemmListGeometry lg, uint32_t row_tiles, uint32_t packed_tiles,
+    const uint4* __restrict__ xp, uint32_t tok_tiles, uint32_t tok_groups, uint32_t per_split, uint32_t flush,
+    uint32_t n_tokens, float* __restrict__ dst) {
+    struct Shared {
+        float tab[16];
+        uint16_t unused[GEMM_WIDE_WAVES][64];  // where lanes without an entry write
+        uint4 a[3][GEMM_WIDE_WAVES][GEMM_TILE_WORDS];
+        uint4 b[3][GEMM_WIDE_TOK_TILES][GEMM_TILE_WORDS];
+    };
+    __shared__ __attribute__((aligned(16))) Shared sh;
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid < 16) sh.tab[tid] = cb.lv32[tid];
+    __syncthreads();
+    const char* tab = reinterpret_cast<const char*>(sh.tab);
+    const uint32_t n_chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK;
+
+    // Workgroups go to the eight dies in turn; each die takes a contiguous run of tiles, token groups fastest, so
+    // that the workgroups on one die share rows and tokens in its cache.
+    uint32_t id = blockIdx.x;
+    {
+        const uint32_t total = gridDim.x, q = total / 8, rem = total % 8, die = id % 8;
+        id = die * q + min(die, rem) + id / 8;
+    }
+    const uint32_t tg = id % tok_groups, rg = (id / tok_groups) % ((row_tiles + 7) / 8),
+                   part = id / (tok_groups * ((row_tiles + 7) / 8));
+    const uint32_t ch0 = part * per_split, ch1 = min(n_chunks, ch0 + per_split), n_steps = ch1 - ch0;
+    const uint32_t my_rt = rg * GEMM_WIDE_WAVES + wave;
+    // a row tile or token tile past the last is read from the last one and not stored
+    const char* my_tile = packed + (uint64_t)min(my_rt, packed_tiles - 1) * n_chunks * GEMM_TILE_BYTES;
+    const uint32_t my_tt = min(tg * GEMM_WIDE_TOK_TILES + (wave >> 1), tok_tiles - 1);
+    const uint4* my_x = xp + (uint64_t)my_tt * n_chunks * GEMM_TILE_WORDS + (wave & 1) * 128 + lane;
+
+    struct Ahead {  // what a wave brings into LDS for one chunk: the codes of its row tile and its share of x
+        uint4 q, x0, x1;
+        uint16_t m;
+        uint32_t en, lo, n_en;  // this lane's list entry of the tile; where the tile's entries begin, how many
+    };
+    uint32_t e_lo = 0, e_hi = 0;  // lane i: where the entries of the i-th of 64 chunks begin and end
+    auto fetch = [&](uint32_t nth) __attribute__((always_inline)) {  // called for nth = 0, 1, 2, ...
+        Ahead o = {};
+        const uint32_t chunk = min(ch0 + nth, ch1 - 1);
+        if (OUTLIERS) {
+            if ((nth & 63u) == 0u) {
+                const uint32_t c = ch0 + nth + lane;
+                e_lo = e_hi = 0u;
+                if (my_rt < row_tiles && c < ch1) {
+                    const uint32_t* p = list_ptr + (uint64_t)my_rt * lg.n_groups + (c >> lg.log2_group);
+                    e_lo = min(p[0], n_out);
+                    e_hi = min(p[1], n_out);
+                }
+            }
+            o.lo = (uint32_t)__builtin_amdgcn_readlane((int)e_lo, (int)(nth & 63u));
+            o.n_en = (uint32_t)__builtin_amdgcn_readlane((int)e_hi, (int)(nth & 63u)) - o.lo;
+            o.en = lane < o.n_en ? entries[o.lo + lane] : 0u;
+        }
+        const char* tile = my_tile + (uint64_t)chunk * GEMM_TILE_BYTES;
+        o.q = reinterpret_cast<const uint4*>(tile)[lane];
+        o.m = reinterpret_cast<const uint16_t*>(tile + 1024)[lane];
+        const uint4* p = my_x + (uint64_t)chunk * GEMM_TILE_WORDS;
+        o.x0 = p[0];
+        o.x1 = p[64];
+        return o;
+    };
+    // Decoding in quarters (one 16-byte word of the operand each): the look-ups, then products, rounding and the store.
+    struct Levels {
+        float v[8];
+    };
+    auto look_up = [&](const uint32_t w) __attribute__((always_inline)) {
+        const uint32_t even = (w << 2) & 0x3c3c3c3cu, odd = (w >> 2) & 0x3c3c3c3cu;
+        const uint32_t oe[4] = {byte_of<0>(even), byte_of<1>(even), byte_of<2>(even), byte_of<3>(even)};
+        const uint32_t oo[4] = {byte_of<0>(odd), byte_of<1>(odd), byte_of<2>(odd), byte_of<3>(odd)};
+        Levels l;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            l.v[2 * i] = *reinterpret_cast<const float*>(tab + oe[i]);
+            l.v[2 * i + 1] = *reinterpret_cast<const float*>(tab + oo[i]);
+        }
+        return l;
+    };
+    auto store_word = [&](const Levels l, float msc, uint32_t buf, int j) __attribute__((always_inline)) {
+        uint32_t a[4];  // the decoder's product and rounding
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[i] = gemm_pack_bf16(msc * l.v[2 * i], msc * l.v[2 * i + 1]);
+        sh.a[buf][wave][64 * j + lane] = make_uint4(a[0], a[1], a[2], a[3]);
+    };
+    auto patch = [&](const Ahead o, uint32_t nth, uint32_t buf) __attribute__((always_inline)) {
+        const uint32_t my_parked = (uint32_t)offsetof(Shared, a) + (buf * GEMM_WIDE_WAVES + wave) * GEMM_TILE_WORDS * 16;
+        const uint32_t my_unused = (uint32_t)offsetof(Shared, unused) + (wave * 64 + lane) * 2;
+        const uint32_t place = min(ch0 + nth, ch1 - 1) & ((1u << lg.log2_group) - 1u);
+        wave_lds_fence();  // the entries after what they overwrite
+        const bool mine = lane < o.n_en && (o.en >> 27) == place;
+        const uint32_t at = mine ? my_parked + 2 * ((o.en >> 16) & 2047u) : my_unused;
+        *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(&sh) + at) = (uint16_t)o.en;
+        if (o.n_en > 64u) {  // a tile with more entries than lanes
+            uint16_t* parked = reinterpret_cast<uint16_t*>(sh.a[buf][wave]);
+            for (uint32_t k = 64u + lane; k < o.n_en; k += 64u) {
+                const uint32_t e = entries[o.lo + k];
+                if ((e >> 27) == place) parked[(e >> 16) & 2047u] = (uint16_t)e;
+            }
+        }
+    };
+
+    gemm_f32x16 acc[2][2], sum[2][2];  // [row tile][token tile]
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[r][t][i] = sum[r][t][i] = 0.0f;
+    const uint32_t wr = 2 * (wave & 3), wt = 2 * (wave >> 2);  // first row tile and token tile that the wave multiplies
+    struct Operands {
+        gemm_bf16x8 a[2], b[2];
+    };
+    auto read_operands = [&](uint32_t buf, int j) __attribute__((always_inline)) {
+        const gemm_bf16x8* a = reinterpret_cast<const gemm_bf16x8*>(sh.a[buf][wr]) + lane;
+        const gemm_bf16x8* b = reinterpret_cast<const gemm_bf16x8*>(sh.b[buf][wt]) + lane;
+        const Operands o = {{a[64 * j], a[GEMM_TILE_WORDS + 64 * j]}, {b[64 * j], b[GEMM_TILE_WORDS + 64 * j]}};
+        return o;
+    };
+    auto multiply = [&](const Operands o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                acc[r][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.b[t], o.a[r], acc[r][t], 0, 0, 0);
+    };
+    auto store_x = [&](const uint4 v0, const uint4 v1, uint32_t buf) __attribute__((always_inline)) {
+        uint4* p = sh.b[buf][wave >> 1] + (wave & 1) * 128 + lane;
+        p[0] = v0;
+        p[64] = v1;
+    };
+
+    uint32_t until_flush = flush;
+    // Before step s: buffer s % 3 holds chunk s and buffer (s + 1) % 3 chunk s + 1; `o` is what chunk s + 2 needs; what
+    // chunk s + 3 needs is on its way, that of chunk s + 4 is asked for during the step; `op` and `lv` are the operands
+    // and the look-ups of the step's first quarter.
+    Operands op;
+    Levels lv;
+    auto step = [&](uint32_t s, const uint32_t buf, const Ahead o, uint32_t next_word) __attribute__((always_inline)) {
+        const uint32_t buf1 = buf == 2u ? 0u : buf + 1u, buf2 = buf == 0u ? 2u : buf - 1u;
+        const Ahead asked = fetch(s + 4);
+        const float msc = f16_bits_to_f32(o.m);
+        const uint32_t w[5] = {o.q.x, o.q.y, o.q.z, o.q.w, next_word};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            // the next quarter's LDS reads are on their way while this one is multiplied and stored
+            const Operands op_next = read_operands(j < 3 ? buf : buf1, (j + 1) & 3);
+            const Levels lv_next = look_up(w[j + 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(op);
+            store_word(lv, msc, buf2, j);
+            if (j == 2) store_x(o.x0, o.x1, buf2);
+            __builtin_amdgcn_sched_barrier(0);
+            lv = lv_next;
+            op = op_next;
+        }
+        if (OUTLIERS) patch(o, s + 2, buf2);
+        if (--until_flush == 0u) {
+            until_flush = flush;
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        sum[r][t][i] += acc[r][t][i];
+                        acc[r][t][i] = 0.0f;
+                    }
+        }
+        __syncthreads();
+        return asked;
+    };
+    Ahead o2, o3;
+    {
+        const Ahead first = fetch(0), second = fetch(1);
+        o2 = fetch(2);
+        o3 = fetch(3);
+        const uint32_t w[8] = {first.q.x, first.q.y, first.q.z, first.q.w, second.q.x, second.q.y, second.q.z, second.q.w};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) store_word(look_up(w[j]), f16_bits_to_f32(j < 4 ? first.m : second.m), j >> 2, j & 3);
+        if (OUTLIERS) {
+            patch(first, 0, 0);
+            patch(second, 1, 1);
+        }
+        store_x(first.x0, first.x1, 0);
+        store_x(second.x0, second.x1, 1);
+        lv = look_up(o2.q.x);
+        __syncthreads();
+        op = read_operands(0, 0);
+    }
+    // Three steps to a round, so that neither the buffers' places nor the registers of what is on its way move: a copy
+    // of a register that is being loaded would wait for the load (each step then takes as long as memory's latency:
+    // 57344 x 8192, 128 tokens 176 us).
+    uint32_t s = 0;
+    for (uint32_t rounds = n_steps / 3; rounds > 0; --rounds, s += 3) {
+        const Ahead o4 = step(s, 0, o2, o3.q.x);
+        o2 = step(s + 1, 1, o3, o4.q.x);
+        o3 = step(s + 2, 2, o4, o2.q.x);
+    }
+    if (s < n_steps) {
+        const Ahead o4 = step(s, 0, o2, o3.q.x);
+        if (s + 1 < n_steps) step(s + 1, 1, o3, o4.q.x);
+    }
+
+    float* out = dst + (uint64_t)part * n_tokens * rows;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const uint32_t row = (rg * GEMM_WIDE_WAVES + wr + r) * GEMM_ROWS + (lane & 31);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint32_t tok0 = (tg * GEMM_WIDE_TOK_TILES + wt + t) * GEMM_TOKENS + 4 * (lane >> 5);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const uint32_t tok = tok0 + 8 * (i >> 2) + (i & 3);
+                if (row < rows && tok < n_tokens) out[(uint64_t)tok * rows + row] = sum[r][t][i] + acc[r][t][i];
             }
         }
     }

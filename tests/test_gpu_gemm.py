@@ -170,6 +170,25 @@ def test_gemm_list_with_few_entries_and_with_all_positions(rows, cols, k):
     check(cb, codes, scales, oi, ov, rows, cols, block, rand_x(5, cols, 3))
 
 
+@pytest.mark.parametrize("rows,cols,n_tokens,share", [
+    (1, 512, 257, 0.02), (255, 544, 385, 0.01), (257, 1056, 300, 0.01), (520, 512, 512, 0.0), (40, 640, 260, 1.0),
+    (33, 6176, 250, 0.004), (96, 8256, 640, 0.01), (256, 13024, 244, 0.006), (16390, 512, 255, 0.001)])
+def test_gemm_wide_tile(rows, cols, n_tokens, share):
+    """The tile of 256 rows x 128 tokens: one row more and less than a tile, row tiles and token tiles that are absent,
+    half chunks of columns, columns split over several workgroups with one to many steps each, more than 64 steps (the
+    list's offsets are read 64 at a time), sums cut into several runs; lists with no, few and (share 1) all positions,
+    and row counts whose offsets cover several chunks each.  The bound is that of every product here."""
+    block = 32
+    cb, codes, scales, _, _ = quantized(rows, cols, block, 1, 0, seed=91)
+    cb = cb + 0.004  # no zero level: every placeholder decodes to something
+    rng = np.random.default_rng(rows + cols)
+    oi = ov = None
+    if share > 0:
+        oi = np.sort(rng.choice(rows * cols, int(rows * cols * share), replace=False)).astype(np.int64)
+        ov = (rng.standard_normal(oi.size).astype(np.float32)).astype(np.float16).view(np.uint16)
+    check(cb, codes, scales, oi, ov, rows, cols, block, rand_x(n_tokens, cols, 3))
+
+
 @pytest.mark.parametrize("opq", [0, 1])
 def test_gemm_a_token_that_is_not_finite_stays_on_its_own(opq):
     """One token carries an infinity: its own results are not finite (every row multiplies it), every other token's are
