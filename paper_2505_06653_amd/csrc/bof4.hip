@@ -758,7 +758,7 @@ int bof4_quant_error(const void* w_dev, uint64_t n, uint32_t block, const double
     double* rec_dev = partials + (uint64_t)sgrid * ERR_PART;
     double* direct = (double*)device_view_of_host(out_host);
     if (direct) out_host->n = FLAG_PENDING;  // the word the final kernel writes last
-    hipLaunchKernelGGL(error_final_kernel, dim3(1), dim3(64), 0, s, partials, sgrid, n, direct ? direct : rec_dev);
+    hipLaunchKernelGGL(error_final_kernel, dim3(1), dim3(1024), 0, s, partials, sgrid, n, direct ? direct : rec_dev);
     HIP_TRY(hipGetLastError());
     if (direct) {
         HIP_TRY(wait_for_flag(s, &out_host->n));
