@@ -339,9 +339,11 @@ size_t bof4_gemv_outlier_table_bytes(uint64_t rows, uint64_t cols, uint64_t n_ou
  * bof4_gemm_packed_bytes(rows, cols) bytes (device, 16-byte aligned) - per tile of 32 rows x 64 columns 1024 bytes of
  * codes and 64 binary16 constants, 0.5625 bytes per weight; BOF4_ERR_WORKSPACE if the buffer is smaller.
  *   packed_dev  that copy
- *   table_dev   what bof4_gemm_outlier_table made of the outlier list for these rows, cols and n_outliers: the size of
- *               bof4_gemv's table (bof4_gemv_outlier_table_bytes), its contents the values in bfloat16, sorted into
- *               the products' tiles of 32 rows x 64 columns; may be NULL when n_outliers == 0
+ *   table_dev   what bof4_gemm_outlier_table made of the outlier list (n_outliers entries) for these rows and cols: the
+ *               size of bof4_gemv's table (bof4_gemv_outlier_table_bytes), its contents the values in bfloat16, sorted
+ *               into the products' tiles of 32 rows x 64 columns (not bof4_gemv's table, and no format to keep in a
+ *               file); may be NULL when n_outliers == 0.  With another n_outliers than the table was made for, nothing
+ *               is read outside the shorter of the two lists
  *   x_dev       n_tokens x cols bfloat16 (device, 16-byte aligned), y_dev  n_tokens x rows binary32 (device)
  *   ws_dev      bof4_gemm_workspace_bytes(rows, cols, n_tokens) bytes (device, 256-byte aligned),
  *               BOF4_ERR_WORKSPACE if smaller: x reordered for the matrix cores and as much again (4 bytes per token

@@ -1133,22 +1133,22 @@ int outlier_table_check(const uint8_t* codes_dev, const uint16_t* scales_dev, ui
 }
 
 // The table of bof4_gemm: offsets per tile of 32 rows and group of chunks, one closing offset, then the entries (4 bytes
-// each) - inside the bytes of the gemv table for the same matrix and list: the groups are as fine as fits, one
-// chunk each wherever rows is a multiple of 32 or the list is longer than the offsets need in addition.
+// each) - inside the bytes of the gemv table for the same matrix and list, and with the entries at the same place.  The
+// groups are as fine as fits in front of them.  Nothing here depends on the length of the list: a product that is told
+// another length than the table was made for still finds offsets and entries where they are.
 struct GemmTableLayout {
     GemmListGeometry lg;
     uint32_t row_tiles;
     size_t entries;
 };
-GemmTableLayout gemm_table_layout(uint64_t rows, uint64_t cols, uint64_t n_outliers) {
+GemmTableLayout gemm_table_layout(uint64_t rows, uint64_t cols) {
     GemmTableLayout T;
-    const uint64_t total = gemv_table_layout(rows, (cols + GEMV_STRIP - 1) / GEMV_STRIP, n_outliers).total;
+    T.entries = gemv_table_layout(rows, (cols + GEMV_STRIP - 1) / GEMV_STRIP, 0).entries;
     const uint64_t row_tiles = (rows + GEMM_ROWS - 1) / GEMM_ROWS, chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK;
     T.row_tiles = (uint32_t)row_tiles;
     for (T.lg.log2_group = 0;; ++T.lg.log2_group) {  // ends: with 2^5 chunks per group there is one group per strip
         T.lg.n_groups = (uint32_t)((chunks + (1u << T.lg.log2_group) - 1) >> T.lg.log2_group);
-        T.entries = (row_tiles * T.lg.n_groups + 1) * 4;
-        if (T.entries + 4 * n_outliers <= total || T.lg.log2_group == 5) return T;
+        if ((row_tiles * T.lg.n_groups + 1) * 4 <= T.entries || T.lg.log2_group == 5) return T;
     }
 }
 
@@ -1261,7 +1261,7 @@ int bof4_gemm_outlier_table(const uint8_t* codes_dev, const uint16_t* scales_dev
     const int rc = outlier_table_check(codes_dev, scales_dev, rows, cols, block, cb_host, out_idx_dev, out_val_dev,
                                        n_outliers, table_dev, table_bytes);
     if (rc != BOF4_OK) return rc;
-    const GemmTableLayout T = gemm_table_layout(rows, cols, n_outliers);
+    const GemmTableLayout T = gemm_table_layout(rows, cols);
     hipLaunchKernelGGL(gemm_list_kernel, dim3(T.row_tiles), dim3(256), 0, (hipStream_t)stream, out_idx_dev, out_val_dev,
                        (uint32_t)n_outliers, rows, (uint32_t)cols, T.lg, (uint32_t*)table_dev,
                        (uint32_t*)((char*)table_dev + T.entries));
@@ -1317,7 +1317,7 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
         return fail(BOF4_ERR_ARG, "bof4_gemm: misaligned pointer (packed matrix and x need 16 bytes, the table 8, the workspace 256)");
     const GemmWsLayout L = gemm_ws_layout(rows, cols, n_tokens);
     if (ws_bytes < L.total) return fail(BOF4_ERR_WORKSPACE, "bof4_gemm: workspace too small");
-    const GemmTableLayout T = gemm_table_layout(rows, cols, n_outliers);
+    const GemmTableLayout T = gemm_table_layout(rows, cols);
     const uint32_t* offsets_dev = (const uint32_t*)table_dev;
     const uint32_t* entries_dev = table_dev ? (const uint32_t*)((const char*)table_dev + T.entries) : nullptr;
     hipStream_t s = (hipStream_t)stream;

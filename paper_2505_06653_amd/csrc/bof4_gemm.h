@@ -101,8 +101,9 @@ __global__ __launch_bounds__(256) void gemm_pack_x_kernel(const uint16_t* __rest
 }
 
 // The outlier list in the order of the products' tiles, made once per matrix.  ptr[rt * n_groups + g] is where the
-// entries of row tile rt and column group g begin (a group: 2^log2_group chunks of 64 columns, as fine as the table's
-// size allows - one chunk for all but a few odd row counts), with one closing value; an entry is one 32-bit word:
+// entries of row tile rt and column group g begin (a group: 2^log2_group chunks of 64 columns, as fine as the room that
+// the size of the table leaves for a rows x cols matrix - one chunk wherever the last row tile is full, at most two for
+// any other matrix of 32 rows or more), with one closing value; an entry is one 32-bit word:
 //   bits 0 .. 15 the value as the decoder stores it (bfloat16), bits 16 .. 26 where it goes in the tile's decoded
 //   operand - 16-byte word (product j, lane) and place in it, j * 512 + lane * 8 + column % 8 -, bits 27 .. 31 which
 //   chunk of its group it belongs to.
@@ -112,6 +113,14 @@ __global__ __launch_bounds__(256) void gemm_pack_x_kernel(const uint16_t* __rest
 struct GemmListGeometry {
     uint32_t n_groups, log2_group;
 };
+// Where the entries of one group begin (lo) and end (hi): never past the list, never more than the group has positions,
+// and never backwards, whatever the table holds - the products take hi - lo as a count, so a table of another matrix
+// costs wrong numbers and no read outside the list.
+__device__ __forceinline__ void gemm_list_range(const uint32_t* __restrict__ p, uint32_t n_out, uint32_t log2_group,
+                                                uint32_t& lo, uint32_t& hi) {
+    lo = min(p[0], n_out);
+    hi = min(max(p[1], lo), lo + min(2048u << log2_group, n_out - lo));
+}
 __device__ __forceinline__ uint32_t list_lower_bound(const int64_t* __restrict__ out_idx, uint32_t n_out, int64_t target) {
     uint32_t lo = 0, hi = n_out;  // first entry >= target
     while (lo < hi) {
@@ -235,8 +244,7 @@ __global__ __launch_bounds__(64 * GEMM_MAX_WAVES) void gemm_kernel(
             e_lo[r] = e_hi[r] = 0u;
             if (rt < row_tiles && chunk < n_chunks) {
                 const uint32_t* p = list_ptr + (uint64_t)rt * lg.n_groups + (chunk >> lg.log2_group);
-                e_lo[r] = min(p[0], n_out);
-                e_hi[r] = min(p[1], n_out);
+                gemm_list_range(p, n_out, lg.log2_group, e_lo[r], e_hi[r]);
             }
         }
     }
@@ -431,8 +439,7 @@ __global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_wide_kernel(
                 e_lo = e_hi = 0u;
                 if (my_rt < row_tiles && c < ch1) {
                     const uint32_t* p = list_ptr + (uint64_t)my_rt * lg.n_groups + (c >> lg.log2_group);
-                    e_lo = min(p[0], n_out);
-                    e_hi = min(p[1], n_out);
+                    gemm_list_range(p, n_out, lg.log2_group, e_lo, e_hi);
                 }
             }
             o.lo = (uint32_t)__builtin_amdgcn_readlane((int)e_lo, (int)(nth & 63u));

@@ -158,7 +158,7 @@ def test_gemm_dense_outlier_rows_take_several_rounds_and_empty_rows_none(n_token
 @pytest.mark.parametrize("rows,cols,k", [(1, 4160, 1), (3, 2112, 2), (17, 8192, 3), (33, 6176, 5), (33, 6176, 3000),
                                          (64, 32768, 4), (40, 64, 2560)])
 def test_gemm_list_with_few_entries_and_with_all_positions(rows, cols, k):
-    """Row counts for which the list's offsets cover 1, 2, 4 or 32 chunks of 64 columns each (they have to fit the table's
+    """Row counts for which the list's offsets cover 1, 2, 16 or 32 chunks of 64 columns each (they have to fit the table's
     size), with the matrix's first and last position always listed; the last case lists every position."""
     block = 32
     cb, codes, scales, _, _ = quantized(rows, cols, block, 1, 0, seed=85)
@@ -168,6 +168,27 @@ def test_gemm_list_with_few_entries_and_with_all_positions(rows, cols, k):
     oi = np.unique(oi).astype(np.int64)
     ov = (rng.standard_normal(oi.size).astype(np.float32)).astype(np.float16).view(np.uint16)
     check(cb, codes, scales, oi, ov, rows, cols, block, rand_x(5, cols, 3))
+
+
+@pytest.mark.parametrize("rows,cols,n_tokens", [(70, 4096, 40), (300, 4096, 400)])
+def test_gemm_told_another_list_length_than_its_table_was_made_for(rows, cols, n_tokens):
+    """Both kernels, row counts for which the offsets' grouping is bound by the table's size: a longer length changes
+    nothing, a shorter one (the entries of the first row tile) leaves the other rows without a list."""
+    block = 64
+    cb, codes, scales, oi, ov = quantized(rows, cols, block, 1, 1, seed=87)
+    cd, sd = torch.from_numpy(codes).to(DEV), dev_u16(scales)
+    tab = binding.bof4_gemm_outlier_table(cd, sd, rows, cols, block, cb, dev_i64(oi), dev_u16(ov))
+    packed = binding.bof4_gemm_pack(cd, sd, rows, cols, block)
+    x = rand_x(n_tokens, cols, 5).to(DEV)
+    k, first = int(oi.size), int(np.searchsorted(oi, 32 * cols))
+    assert 64 < first < k
+    y = binding.bof4_gemm(packed, rows, cols, cb, x, tab, k)
+    assert torch.equal(binding.bof4_gemm(packed, rows, cols, cb, x, tab, k + 12345), y)
+    y_first = binding.bof4_gemm(packed, rows, cols, cb, x, tab, first)
+    only = [t[:first] for t in (dev_i64(oi), dev_u16(ov))]
+    tab_first = binding.bof4_gemm_outlier_table(cd, sd, rows, cols, block, cb, *[t.contiguous() for t in only])
+    assert torch.equal(y_first, binding.bof4_gemm(packed, rows, cols, cb, x, tab_first, first))
+    assert torch.equal(y_first[:, :32], y[:, :32]) and not torch.equal(y_first, y)
 
 
 @pytest.mark.parametrize("rows,cols,n_tokens,share", [
