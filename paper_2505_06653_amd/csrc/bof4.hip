@@ -1262,8 +1262,9 @@ int bof4_gemm_outlier_table(const uint8_t* codes_dev, const uint16_t* scales_dev
                                        n_outliers, table_dev, table_bytes);
     if (rc != BOF4_OK) return rc;
     const GemmTableLayout T = gemm_table_layout(rows, cols);
-    hipLaunchKernelGGL(gemm_list_kernel, dim3(T.row_tiles), dim3(256), 0, (hipStream_t)stream, out_idx_dev, out_val_dev,
-                       (uint32_t)n_outliers, rows, (uint32_t)cols, T.lg, (uint32_t*)table_dev,
+    hipLaunchKernelGGL(gemm_list_kernel, dim3(T.row_tiles < GEMM_LIST_WGS ? T.row_tiles : GEMM_LIST_WGS),
+                       dim3(T.row_tiles < 256 ? 1024 : 256), 0, (hipStream_t)stream, out_idx_dev, out_val_dev,
+                       (uint32_t)n_outliers, rows, (uint32_t)cols, T.row_tiles, T.lg, (uint32_t*)table_dev,
                        (uint32_t*)((char*)table_dev + T.entries));
     HIP_TRY(hipGetLastError());
     return BOF4_OK;

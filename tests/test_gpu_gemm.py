@@ -170,6 +170,27 @@ def test_gemm_list_with_few_entries_and_with_all_positions(rows, cols, k):
     check(cb, codes, scales, oi, ov, rows, cols, block, rand_x(5, cols, 3))
 
 
+def test_gemm_outlier_table_of_2_to_the_29_rows():
+    """More row tiles than a launch of one workgroup of 256 lanes per tile can hold (2^32 lanes): the offsets before and
+    behind the entries of the first, a middle and the last tile, and the entries themselves."""
+    rows, cols, block = 1 << 29, 32, 32
+    codes = torch.zeros(rows * cols // 2, dtype=torch.uint8, device=DEV)
+    scales = torch.zeros(rows * cols // block, dtype=torch.float16, device=DEV)
+    mid = (1 << 20) * 32 * cols  # the first row tile that a workgroup takes in its second turn
+    oi = np.array([5, mid + 33, rows * cols - 1], dtype=np.int64)
+    ov = np.array([1.0, 2.0, 3.0], dtype=np.float16)
+    tab = binding.bof4_gemm_outlier_table(codes, scales, rows, cols, block, np.linspace(-1, 1, 16), dev_i64(oi),
+                                          torch.from_numpy(ov).to(DEV)).view(torch.int32)
+    n_tiles = rows // 32
+    want = torch.ones(n_tiles + 1, dtype=torch.int32, device=DEV)  # one chunk of columns: one group
+    want[0], want[(1 << 20) + 1:], want[-1] = 0, 2, 3
+    assert torch.equal(tab[: n_tiles + 1], want)
+    at = (rows + 1 + 1) // 2 * 2  # behind one offset per row and the closing one, 8-byte aligned
+    place = [5, 1 * 8 + 1, 3 * 512 + 31 * 8 + 7]  # j * 512 + lane * 8 + column % 8: (row, column) (0, 5), (1, 1), (31, 31)
+    bits16 = [0x3F80, 0x4000, 0x4040]
+    assert tab[at: at + 3].tolist() == [b | p << 16 for b, p in zip(bits16, place)]
+
+
 @pytest.mark.parametrize("rows,cols,n_tokens", [(70, 4096, 40), (300, 4096, 400)])
 def test_gemm_told_another_list_length_than_its_table_was_made_for(rows, cols, n_tokens):
     """Both kernels, row counts for which the offsets' grouping is bound by the table's size: a longer length changes
