@@ -331,8 +331,8 @@ size_t bof4_gemv_outlier_table_bytes(uint64_t rows, uint64_t cols, uint64_t n_ou
  * Every product of two bfloat16 numbers is exact in binary32; the sums are binary32 (matrix cores, up to 128 tokens
  * per pass over the codes) in a fixed order: y is bit-reproducible and lies within (cols + 64) * 2^-24 * sum_c |W^ x|
  * of the exact sum, and is exact whenever every partial sum is a binary32 number.  The order of the additions depends
- * on rows, cols and n_tokens (how the columns are dealt out over workgroups), so the same token may differ in its last
- * bits between calls with different n_tokens; equal calls give equal bits.
+ * on rows, cols, n_tokens (how the columns are dealt out over workgroups) and on whether the workspace has its full size,
+ * so the same token may differ in its last bits between calls with different n_tokens; equal calls give equal bits.
  *
  * The matrix is read from a copy in the order of the matrix cores' operands, made once per matrix by bof4_gemm_pack
  * from what bof4_quantize wrote for n = rows * cols (row-major [rows x cols], cols a multiple of block):
@@ -345,10 +345,13 @@ size_t bof4_gemv_outlier_table_bytes(uint64_t rows, uint64_t cols, uint64_t n_ou
  *               file); may be NULL when n_outliers == 0.  With another n_outliers than the table was made for, nothing
  *               is read outside the shorter of the two lists
  *   x_dev       n_tokens x cols bfloat16 (device, 16-byte aligned), y_dev  n_tokens x rows binary32 (device)
- *   ws_dev      bof4_gemm_workspace_bytes(rows, cols, n_tokens) bytes (device, 256-byte aligned),
- *               BOF4_ERR_WORKSPACE if smaller: x reordered for the matrix cores and as much again (4 bytes per token
- *               slot and column, token slots in 32s), and - for matrices with too few rows to fill the chip - the
- *               partial results of the workgroups that share a row
+ *   ws_dev      bof4_gemm_workspace_bytes(rows, cols, n_tokens) bytes (device, 256-byte aligned): a size that never
+ *               falls as n_tokens rises, so one buffer for the most tokens serves every call with fewer.  It holds x
+ *               reordered for the matrix cores and the partial results of the workgroups that share a row (for
+ *               matrices with too few rows, or rows and tokens, to fill the chip).  What a call cannot do without is
+ *               4 bytes per token slot and column (token slots in 32s, columns in 64s), and for matrices with too few
+ *               rows to fill the chip, up to 64 partial results of up to 128 tokens; BOF4_ERR_WORKSPACE below that.
+ *               Between the two a call may take a slower kernel, whose order of additions is another
  * Limits: cols <= 32768 and a multiple of 32, n_tokens <= 65536.  The codes are read once per 128 tokens.  All three
  * calls only enqueue.
  */

@@ -1182,7 +1182,7 @@ uint32_t gemm_split(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
 bool gemm_is_wide(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     const uint64_t wg_tokens = GEMM_WIDE_TOK_TILES * GEMM_TOKENS, wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS;
     const uint64_t tok_groups = (n_tokens + wg_tokens - 1) / wg_tokens;
-    if (cols < 512 || (rows + wg_rows - 1) / wg_rows * tok_groups * GEMM_WIDE_MAX_SPLIT >= (1ull << 31)) return false;
+    if (cols < 512 || (rows + wg_rows - 1) / wg_rows * tok_groups >= (1ull << 23)) return false;  // 2^32 lanes in a launch
     const bool full = tok_groups * wg_tokens * 10 <= n_tokens * 11;  // hardly a token slot of the groups is empty
     if (n_tokens <= wg_tokens) return full && rows >= cols && rows * cols > (1ull << 26);
     if (rows * cols >= (1ull << 27)) return full;  // here it gains least
@@ -1190,13 +1190,14 @@ bool gemm_is_wide(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
            (full && (rows >= 16384 || cols >= 6144));
 }
 // Over how many workgroups its columns are split: what the model of its time says is fastest - rounds of 256 workgroups
-// (one per compute unit: its LDS), 1.4 us per chunk and 8 us to start and end, the partial results at 4 TB/s.
+// (one per compute unit: its LDS), 1.4 us per chunk and 8 us to start and end, the partial results at 4 TB/s.  The same
+// for every token count of a group of 128, so that the workspace can be sized for all smaller token counts.
 struct GemmWideSplit {
     uint32_t split, per_split;  // workgroups along the columns, chunks each
 };
-GemmWideSplit gemm_wide_split(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
+GemmWideSplit gemm_wide_split(uint64_t rows, uint64_t cols, uint64_t tok_groups) {
     const uint64_t wg_tokens = GEMM_WIDE_TOK_TILES * GEMM_TOKENS, wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS;
-    const uint64_t groups = (rows + wg_rows - 1) / wg_rows * ((n_tokens + wg_tokens - 1) / wg_tokens);
+    const uint64_t groups = (rows + wg_rows - 1) / wg_rows * tok_groups;
     const uint64_t chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK;
     GemmWideSplit best = {1, (uint32_t)chunks};
     double best_time = 0.0;
@@ -1204,16 +1205,19 @@ GemmWideSplit gemm_wide_split(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
         const uint64_t per = (chunks + want - 1) / want, split = (chunks + per - 1) / per;
         const double rounds = (double)((groups * split + 255) / 256);
         const double t = rounds * (6.0 + (double)per) * 1.4 +
-                         (split > 1 ? 4.0 + (double)(2 * split + 1) * (double)(n_tokens * rows) * 4.0 / 4e6 : 0.0);
+                         (split > 1 ? 4.0 + (double)(2 * split + 1) * (double)(tok_groups * wg_tokens * rows) * 4.0 / 4e6 : 0.0);
         if (want == 1 || t < best_time) best = {(uint32_t)split, (uint32_t)per}, best_time = t;
     }
     return best;
 }
 
-// Workspace of bof4_gemm: x in the order of the products, room for a second copy of it, the partial results.
+// Workspace of bof4_gemm: x in the order of the products, then the partial results of the workgroups that share a row.
+// gemm_kernel's lie behind `part`; the wide kernel's - all but the first part's, which goes to y - behind `wide_part`.
+// `total` is what a call cannot do without and what gemm_kernel takes; it holds room for a second copy of x that only the
+// wide kernel's partial results use (x transposed once stood there: buffers of that size are in use).
 constexpr uint32_t GEMM_MAX_TOKENS = 65536;
 struct GemmWsLayout {
-    size_t xp, part, total;
+    size_t xp, part, wide_part, total;
 };
 GemmWsLayout gemm_ws_layout(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     const uint64_t n_pad = (n_tokens + GEMM_TOKENS - 1) / GEMM_TOKENS * GEMM_TOKENS;
@@ -1221,11 +1225,24 @@ GemmWsLayout gemm_ws_layout(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     const uint64_t per_launch = n_pad < GEMM_TOKENS * GEMM_MAX_TILES ? n_pad : GEMM_TOKENS * GEMM_MAX_TILES;
     GemmWsLayout L;
     L.xp = 0;
-    L.part = align_up(align_up(L.xp + n_pad * chunks * GEMM_CHUNK * 2, 256) + cols * n_pad * 2, 256);  // (as documented)
-    const uint64_t wide = gemm_is_wide(rows, cols, n_tokens) ? gemm_wide_split(rows, cols, n_tokens).split : 1;
-    const uint64_t part = split > 1 ? split * per_launch * rows : 0, wide_part = wide > 1 ? wide * n_tokens * rows : 0;
-    L.total = L.part + 4 * (part > wide_part ? part : wide_part);
+    L.wide_part = align_up(L.xp + n_pad * chunks * GEMM_CHUNK * 2, 256);
+    L.part = align_up(L.wide_part + cols * n_pad * 2, 256);
+    L.total = L.part + (split > 1 ? split * per_launch * rows * 4 : 0);
     return L;
+}
+// What bof4_gemm_workspace_bytes returns: enough for the wide kernel at this and at every smaller token count (its split
+// falls as the token groups grow in number, so the largest need is not that of the most tokens).
+size_t gemm_ws_bytes(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
+    const uint64_t wg_tokens = GEMM_WIDE_TOK_TILES * GEMM_TOKENS;
+    size_t need = gemm_ws_layout(rows, cols, n_tokens).total;
+    for (uint64_t g = 1; (g - 1) * wg_tokens < n_tokens; ++g) {
+        const uint64_t t = g * wg_tokens < n_tokens ? g * wg_tokens : n_tokens;  // the group's most tokens
+        if (!gemm_is_wide(rows, cols, t)) continue;                               // and then none of its fewer ones
+        const uint64_t parts = gemm_wide_split(rows, cols, g).split - 1;
+        const size_t bytes = gemm_ws_layout(rows, cols, t).wide_part + parts * t * rows * 4;
+        if (bytes > need) need = bytes;
+    }
+    return need;
 }
 }  // namespace
 
@@ -1272,7 +1289,7 @@ int bof4_gemm_outlier_table(const uint8_t* codes_dev, const uint16_t* scales_dev
 
 size_t bof4_gemm_workspace_bytes(uint64_t rows, uint64_t cols, uint32_t n_tokens) {
     if (rows == 0 || cols == 0 || n_tokens == 0) return 0;
-    return gemm_ws_layout(rows, cols, n_tokens).total;
+    return gemm_ws_bytes(rows, cols, n_tokens);
 }
 
 size_t bof4_gemm_packed_bytes(uint64_t rows, uint64_t cols) {
@@ -1337,24 +1354,26 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
                            (const uint16_t*)x_dev, n_tokens, (uint32_t)cols, chunks, n_pad, (uint4*)xp);
     }
     timing_begin(s);
-    if (gemm_is_wide(rows, cols, n_tokens)) {
-        const GemmWideSplit W = gemm_wide_split(rows, cols, n_tokens);
-        const uint32_t tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
+    const uint32_t tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
+    const GemmWideSplit W = gemm_wide_split(rows, cols, tok_groups);
+    // (a workspace that holds the narrow kernel's partial results only gets the narrow kernel)
+    if (gemm_is_wide(rows, cols, n_tokens) &&
+        ws_bytes >= L.wide_part + (uint64_t)(W.split - 1) * n_tokens * rows * 4) {
         const uint32_t wide_groups = (T.row_tiles + GEMM_WIDE_WAVES - 1) / GEMM_WIDE_WAVES;
         // the matrix cores' chain of additions is no longer than an eighth of the columns, as with eight waves to a row
         const uint32_t eighth = (chunks + 7) / 8, flush = eighth < 8 ? 8 : eighth;
-        float* dst = W.split > 1 ? part : y_dev;
+        float* parts = (float*)((char*)ws_dev + L.wide_part);
 #define BOF4_LAUNCH_WIDE(OUT_)                                                                                       \
     hipLaunchKernelGGL((gemm_wide_kernel<OUT_>), dim3(tok_groups * wide_groups * W.split), dim3(64 * GEMM_WIDE_WAVES), \
                        0, s, (const char*)packed_dev, (uint32_t)rows, (uint32_t)cols, cb, offsets_dev, entries_dev,  \
                        (uint32_t)n_outliers, T.lg, T.row_tiles, (uint32_t)gemm_row_tiles(rows), xp, tok_tiles,       \
-                       tok_groups, W.per_split, flush, n_tokens, dst);
+                       tok_groups, W.per_split, flush, n_tokens, y_dev, parts);
         if (n_outliers > 0) { BOF4_LAUNCH_WIDE(true) } else { BOF4_LAUNCH_WIDE(false) }
 #undef BOF4_LAUNCH_WIDE
         if (W.split > 1) {
             const uint64_t count = (uint64_t)n_tokens * rows;
-            hipLaunchKernelGGL(gemm_sum_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, s, part, W.split,
-                               count, y_dev);
+            hipLaunchKernelGGL(gemm_sum_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, s, y_dev, parts,
+                               W.split - 1, count, y_dev);
         }
         timing_end(s);
         HIP_TRY(hipGetLastError());
@@ -1382,8 +1401,8 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
 #undef BOF4_LAUNCH_GEMM
         if (split > 1) {
             const uint64_t count = (uint64_t)nt * rows;
-            hipLaunchKernelGGL(gemm_sum_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, s, part, split,
-                               count, yt);
+            hipLaunchKernelGGL(gemm_sum_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, s, part,
+                               part + count, split - 1, count, yt);
         }
         tile0 += nt_tiles;
     }

@@ -402,7 +402,7 @@ __global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_wide_kernel(
     const char* __restrict__ packed, uint32_t rows, uint32_t cols, CodebookArgs cb, const uint32_t* __restrict__ list_ptr,
     const uint32_t* __restrict__ entries, uint32_t n_out, GemmListGeometry lg, uint32_t row_tiles, uint32_t packed_tiles,
     const uint4* __restrict__ xp, uint32_t tok_tiles, uint32_t tok_groups, uint32_t per_split, uint32_t flush,
-    uint32_t n_tokens, float* __restrict__ dst) {
+    uint32_t n_tokens, float* __restrict__ y, float* __restrict__ parts) {
     struct Shared {
         float tab[16];
         uint16_t unused[GEMM_WIDE_WAVES][64];  // where lanes without an entry write
@@ -604,7 +604,8 @@ __global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_wide_kernel(
         if (s + 1 < n_steps) step(s + 1, 1, o3, o4.q.x);
     }
 
-    float* out = dst + (uint64_t)part * n_tokens * rows;
+    // the first part goes to the result itself, where gemm_sum_kernel adds the others to it
+    float* out = part == 0 ? y : parts + (uint64_t)(part - 1) * n_tokens * rows;
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const uint32_t row = (rg * GEMM_WIDE_WAVES + wr + r) * GEMM_ROWS + (lane & 31);
@@ -620,13 +621,13 @@ __global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_wide_kernel(
     }
 }
 
-// y = the n_split partial results in order (count elements each).
-__global__ __launch_bounds__(256) void gemm_sum_kernel(const float* __restrict__ part, uint32_t n_split, uint64_t count,
-                                                       float* __restrict__ y) {
+// y = the partial results in order (count elements each): the first, which may stand in y itself, and n_more others.
+__global__ __launch_bounds__(256) void gemm_sum_kernel(const float* first, const float* __restrict__ more, uint32_t n_more,
+                                                       uint64_t count, float* y) {
     const uint64_t idx = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= count) return;
-    float s = 0.0f;
-    for (uint32_t k = 0; k < n_split; ++k) s += part[k * count + idx];
+    float s = first[idx];
+    for (uint32_t k = 0; k < n_more; ++k) s += more[k * count + idx];
     y[idx] = s;
 }
 

@@ -303,6 +303,40 @@ def test_gemm_is_bit_reproducible_and_respects_out_workspace_and_stream():
     assert torch.equal(y3[0], y1[33])
 
 
+@pytest.mark.parametrize("rows,cols,n_max,n_tokens", [(1024, 1024, 2000, 1030), (1000, 2048, 700, 350)])
+def test_gemm_workspace_of_more_tokens_and_of_the_least_size(rows, cols, n_max, n_tokens):
+    """A buffer for more tokens gives the same bits as the call's own; one of the least size (x twice, and the partial
+    results of gemm_kernel: two or four workgroups per row tile here, at most 128 tokens) is enough, and nothing behind
+    it is touched."""
+    block = 64
+    cb, codes, scales, oi, ov = quantized(rows, cols, block, 1, 1, seed=88)
+    cd, sd = torch.from_numpy(codes).to(DEV), dev_u16(scales)
+    tab = binding.bof4_gemm_outlier_table(cd, sd, rows, cols, block, cb, dev_i64(oi), dev_u16(ov))
+    packed = binding.bof4_gemm_pack(cd, sd, rows, cols, block)
+    x = rand_x(n_tokens, cols, 6)
+    xd = x.to(DEV)
+
+    def run(ws_bytes):
+        ws = torch.full((ws_bytes + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
+        y = binding.bof4_gemm(packed, rows, cols, cb, xd, tab, int(oi.size), ws=ws[:ws_bytes])
+        assert bool((ws[ws_bytes:] == 0x5A).all())
+        return y
+
+    y = run(binding.bof4_gemm_workspace_bytes(rows, cols, n_tokens))
+    assert torch.equal(run(binding.bof4_gemm_workspace_bytes(rows, cols, n_max)), y)
+    split = {1024: 2, 2048: 4}[cols]  # 16 or 32 chunks of 64 columns, at least eight per workgroup; 32 row tiles for 192
+    least = 4 * ((n_tokens + 31) // 32 * 32) * cols + split * 128 * rows * 4
+    y_least = run(least)
+    with pytest.raises(binding.Bof4Error) as e:
+        run(least - 256)
+    assert e.value.code == binding.BOF4_ERR_WORKSPACE
+    st, y_o, a = oracle.gemm(codes, scales, rows, cols, block, cb, inputs.bits(x).reshape(x.shape), oi, ov)
+    assert st == oracle.OK
+    for got in (y, y_least):
+        assert np.all(np.abs(got.cpu().numpy() - y_o) <= (cols + 64) * U * a)
+    assert not torch.equal(y, y_least)  # the least size takes the other kernel
+
+
 def test_gemm_pack_layout():
     """Per tile of 32 rows and 64 columns: 64 words of 16 bytes (row lane % 32, columns 32 (lane / 32) .. + 31), then
     64 constants; zeros past the last row and the last column."""

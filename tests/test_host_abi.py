@@ -178,3 +178,17 @@ def test_argument_validation_and_size_formulas_of_the_matrix_product_without_tou
     need = binding.bof4_gemv_outlier_table_bytes(10, 4096 + 64, 7)
     assert t(10, 4096 + 64, 7, ws, need - 8) == binding.BOF4_ERR_WORKSPACE
     assert t(10, 4096 + 32, 7, ws, need) == binding.BOF4_ERR_ARG
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 32), (40, 640), (1024, 1024), (4096, 4096), (4096, 11008), (10240, 8192),
+                                       (22016, 4096), (8192, 28672), (57344, 8192), (28672, 512), (500, 28672),
+                                       (3001, 3008), (33, 32768)])
+def test_gemm_workspace_never_shrinks_as_tokens_rise(rows, cols):
+    """One buffer for the largest batch serves every smaller one; and no call asks for less than x in the order of the
+    products and as much again, the size that a call cannot do without."""
+    last = 0
+    for n_tokens in list(range(1, 2600)) + [4096, 4097, 20000, 65536]:
+        size = binding.bof4_gemm_workspace_bytes(rows, cols, n_tokens)
+        assert size >= last, n_tokens
+        assert size >= 4 * ((n_tokens + 31) // 32 * 32) * cols
+        last = size
