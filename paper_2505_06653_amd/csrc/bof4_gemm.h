@@ -45,6 +45,7 @@ constexpr uint32_t GEMM_TARGET_WGS = 192;
 typedef __bf16 gemm_bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 gemm_bf16x2 __attribute__((ext_vector_type(2)));
 typedef float gemm_f32x2 __attribute__((ext_vector_type(2)));
+typedef float gemm_f32x2_any __attribute__((ext_vector_type(2), aligned(4)));  // two floats anywhere
 typedef float gemm_f32x16 __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ uint32_t gemm_pack_bf16(float lo, float hi) {
@@ -190,23 +191,46 @@ __global__ __launch_bounds__(1024) void gemm_list_kernel(const int64_t* __restri
     }
 }
 
+// Adds an accumulator to its sum and leaves in the accumulator what the addition rounded away (exactly where the sum is the
+// larger of the two, to within a rounding of the smaller elsewhere), so that cutting a chain of additions there costs
+// nothing of the sum.  The clamp is for sums that are not finite: an infinite sum stays what it is (inf - inf
+// would make it NaN), a NaN is in the sum already; no residue of finite numbers reaches 2^104.
+__device__ __forceinline__ void gemm_carry(gemm_f32x16& sum, gemm_f32x16& acc, int i) {
+    const float s0 = sum[i], a0 = acc[i], s1 = s0 + a0;
+    sum[i] = s1;
+    acc[i] = __builtin_amdgcn_fmed3f(a0 - (s1 - s0), -0x1p104f, 0x1p104f);
+}
+
 // Workgroup (b, s): R tiles of 32 rows (32 R b ..), the chunks s * waves + wave, + n_split * waves, ... of the row,
 // NT tiles of 32 tokens (tile0 ..).  Its sum goes to dst[(s * n_tokens + token) * rows + row], token counted from
 // the first of tile0: the result itself when n_split is 1, else one of n_split partial results that gemm_sum_kernel
 // adds.  With a list the wave parks the decoded operand of a tile in LDS, writes the tile's entries over their
 // placeholders and reads the operand back (one wave, one buffer: no barrier).  Against adding (value - placeholder) *
-// x per entry and token to the row sums afterwards, as this kernel did before, four matrices of a
-// Llama-70B-shaped layer with 0.9 % outliers take 388 us instead of 643 for 128 tokens.
+// x per entry and token to the row sums afterwards, as this kernel did before: 12288 x 4096 with 0.7 % outliers, 8 /
+// 32 / 64 / 128 tokens 20.2 / 20.4 / 31.1 / 49.7 -> 18.3 / 17.9 / 24.2 / 38.2 us.
+//   Outliers put half of a row's energy into a hundredth of its terms, and the roundings of a chain of additions grow
+// with what it has added up: with the entries inside the product the error of the sums was 1.03 to 1.4 times that of
+// adding them apart.  So with a list the matrix cores' chain is cut: after `flush` chunks the accumulators are added to a
+// second set (CARRY, where there are registers for one: 4 instructions per accumulator), or the chunks are taken in
+// n_runs = 2 runs with the workgroup's sum after each (RUNS: the largest tiles, and two tiles of rows with one of tokens,
+// which would lose its second workgroup per compute unit).  Without the cuts 128 tokens on 12288 x 4096 took 32 us.
+//   The waves' sums are added in binary64: 8 additions of 1 in 24 bits are as many roundings as a short chain has.  Two
+// buffers in turn save a barrier per tile, which pays for it: 28672 x 512 without a list, 128 tokens 21.0 -> 20.2 us.
 // The packed matrix holds a multiple of GEMM_MAX_R row tiles.
+template <int R, int NT>
+constexpr bool GEMM_CARRY = R == 1 || NT == 2;
 template <int R, int NT, bool OUTLIERS>
 __global__ __launch_bounds__(64 * GEMM_MAX_WAVES) void gemm_kernel(
     const char* __restrict__ packed, uint32_t rows, uint32_t cols, CodebookArgs cb, const uint32_t* __restrict__ list_ptr,
     const uint32_t* __restrict__ entries, uint32_t n_out, GemmListGeometry lg, uint32_t row_tiles,
-    const uint4* __restrict__ xp, uint32_t tile0, uint32_t n_tokens, float* __restrict__ dst) {
+    const uint4* __restrict__ xp, uint32_t tile0, uint32_t n_tokens, uint32_t flush, uint32_t n_runs, float* __restrict__ dst) {
+    constexpr uint32_t N_RED = R * NT > 1 && !(OUTLIERS && R * NT > 6) ? 2 : 1;  // (the largest one would spill)
     struct Shared {
         float tab[16];
-        float red[GEMM_MAX_WAVES * 16 * 64];         // per wave: accumulator register i of lane l at [i * 64 + l]; in
-                                                     // the loop over chunks, with a list, the wave's decoded operand
+        // per wave: accumulator registers 4 k .. 4 k + 3 of lane l at [(k * 64 + l) * 4], for two tiles in turn; in the
+        // loop over chunks, with a list, the wave's decoded operand
+        float red[N_RED][GEMM_MAX_WAVES * 16 * 64];
+        float half[OUTLIERS && !GEMM_CARRY<R, NT> ? R * NT * 16 * 64 : 2];  // the workgroup's sums over the first run
     };
     __shared__ __attribute__((aligned(16))) Shared sh;
     const uint32_t tid = threadIdx.x, lane = tid & 63, n_waves = blockDim.x >> 6;
@@ -217,13 +241,8 @@ __global__ __launch_bounds__(64 * GEMM_MAX_WAVES) void gemm_kernel(
     const uint32_t n_chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK;
     const uint32_t stride = gridDim.y * n_waves;
 
-    gemm_f32x16 acc[R][NT];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[r][t][i] = 0.0f;
+    constexpr bool CARRY = OUTLIERS && GEMM_CARRY<R, NT>, RUNS = OUTLIERS && !GEMM_CARRY<R, NT>;
+    gemm_f32x16 acc[R][NT], sum[CARRY ? R : 1][CARRY ? NT : 1];
 
     // What the chunk after this one needs (codes, constants and - where the registers allow it - x) is on its way
     // while this one is decoded and multiplied, in two sets of registers used in turn.  Past the last chunk the last
@@ -274,8 +293,7 @@ __global__ __launch_bounds__(64 * GEMM_MAX_WAVES) void gemm_kernel(
         }
         if (X_AHEAD) fetch_x(o, chunk);
     };
-    float* mine = sh.red + wave * 16 * 64;
-    uint16_t* parked = reinterpret_cast<uint16_t*>(mine);
+    uint16_t* parked = reinterpret_cast<uint16_t*>(sh.red[0] + wave * 16 * 64);
     auto patch = [&](uint32_t e, uint32_t chunk) {
         if ((e >> 27) == (chunk & ((1u << lg.log2_group) - 1u))) parked[(e >> 16) & 2047u] = (uint16_t)e;
     };
@@ -330,49 +348,126 @@ __global__ __launch_bounds__(64 * GEMM_MAX_WAVES) void gemm_kernel(
                 }
         }
     };
-    Operands o0, o1;
+    // Adds the waves' accumulators of every tile, in wave order and in binary64, and stores the sums: for the second
+    // half of the chunks (or all of them) the result, for the first half the record that the second half starts from.
+    // Accumulator i of lane l: row 8 (i / 4) + 4 (l / 32) + i % 4 of the tile, token l % 32; a thread adds two
+    // neighbouring rows of one token.
+    float* out = dst + (uint64_t)blockIdx.y * n_tokens * rows;
+    auto reduce = [&](const uint32_t run, const bool last_run) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t r0 = (blockIdx.x * R + r) * GEMM_ROWS;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                // what stood here has been read: with two buffers the barrier of the tile in between says so
+                if (N_RED == 1 && (r > 0 || t > 0)) __syncthreads();
+                float* red = sh.red[(r * NT + t) % N_RED];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float4 v = make_float4(acc[r][t][4 * k], acc[r][t][4 * k + 1], acc[r][t][4 * k + 2], acc[r][t][4 * k + 3]);
+                    *reinterpret_cast<float4*>(red + ((wave * 4 + k) * 64 + lane) * 4) = v;
+                }
+                __syncthreads();
+                for (uint32_t p = tid; p < 8 * 64; p += blockDim.x) {
+                    double s0 = 0.0, s1 = 0.0;
+                    float2* first = reinterpret_cast<float2*>(sh.half) + (RUNS ? (r * NT + t) * 8 * 64 + p : 0);
+                    if (RUNS && run > 0u) {
+                        s0 = first->x;
+                        s1 = first->y;
+                    }
+                    const float2* v = reinterpret_cast<const float2*>(red) + p;
+                    if (n_waves == GEMM_MAX_WAVES) {  // all reads under way at once
+                        float2 w[GEMM_MAX_WAVES];
+#pragma unroll
+                        for (uint32_t wv = 0; wv < GEMM_MAX_WAVES; ++wv) w[wv] = v[wv * 8 * 64];
+#pragma unroll
+                        for (uint32_t wv = 0; wv < GEMM_MAX_WAVES; ++wv) {
+                            s0 += w[wv].x;
+                            s1 += w[wv].y;
+                        }
+                    } else {
+                        for (uint32_t wv = 0; wv < n_waves; ++wv) {
+                            s0 += v[wv * 8 * 64].x;
+                            s1 += v[wv * 8 * 64].y;
+                        }
+                    }
+                    if (!last_run) {
+                        *first = make_float2((float)s0, (float)s1);
+                        continue;
+                    }
+                    const uint32_t l = (p >> 1) & 63, row = r0 + 8 * (p >> 7) + 4 * (l >> 5) + 2 * (p & 1), n = 32 * t + (l & 31);
+                    if (n >= n_tokens) continue;
+                    float* o = out + (uint64_t)n * rows + row;
+                    if (row + 1 < rows) {
+                        const gemm_f32x2_any v = {(float)s0, (float)s1};
+                        *reinterpret_cast<gemm_f32x2_any*>(o) = v;
+                    } else if (row < rows) {
+                        *o = (float)s0;
+                    }
+                }
+            }
+        }
+    };
+
     uint32_t ch = ch_first;
     const uint32_t last = n_chunks - 1;
     const uint32_t n_iter = ch < n_chunks ? (last - ch) / stride + 1 : 0;
     uint32_t nth = 0;  // how many chunks this wave has taken
-    fetch(o0, min(ch, last), 0);
-    if (n_iter & 1u) {  // an odd one first, so that the rest goes in pairs
-        multiply(o0, ch, 0);
-        ch += stride;
-        nth = 1;
-        fetch(o0, min(ch, last), min(nth, 63u));
-    }
-    for (uint32_t it = n_iter >> 1; it > 0; --it) {  // o0 holds chunk ch
-        fetch(o1, ch + stride, nth + 1);
-        __builtin_amdgcn_sched_barrier(0);  // the loads first, then the arithmetic
-        multiply(o0, ch, nth);
-        fetch(o0, min(ch + 2 * stride, last), min(nth + 2, 63u));
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(o1, ch + stride, nth + 1);
-        ch += 2 * stride;
-        nth += 2;
-    }
-
-    float* out = dst + (uint64_t)blockIdx.y * n_tokens * rows;
+    uint32_t until_flush = flush;
+    auto carry = [&]() __attribute__((always_inline)) {
+        if constexpr (CARRY) {
+            if (--until_flush == 0u) {
+                until_flush = flush;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const uint32_t r0 = (blockIdx.x * R + r) * GEMM_ROWS;
+                for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            if (r > 0 || t > 0) __syncthreads();  // the sums of the round before have been read
+                    for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) mine[i * 64 + lane] = acc[r][t][i];
-            __syncthreads();
-            // The waves' results in wave order.  Accumulator i of lane l: row 8 (i / 4) + 4 (l / 32) + i % 4 of the
-            // tile, token l % 32.
-            for (uint32_t idx = tid; idx < 16 * 64; idx += blockDim.x) {
-                float s = 0.0f;
-                for (uint32_t wv = 0; wv < n_waves; ++wv) s += sh.red[wv * 16 * 64 + idx];
-                const uint32_t i = idx >> 6, l = idx & 63;
-                const uint32_t mr = 8 * (i >> 2) + 4 * (l >> 5) + (i & 3u), n = 32 * t + (l & 31);
-                if (r0 + mr < rows && n < n_tokens) out[(uint64_t)n * rows + r0 + mr] = s;
+                        for (int i = 0; i < 16; ++i) gemm_carry(sum[r][t], acc[r][t], i);
             }
         }
+    };
+    Operands o0, o1;
+    fetch(o0, min(ch, last), 0);
+    for (uint32_t run = 0; run < (RUNS ? n_runs : 1u); ++run) {  // o0 holds chunk ch
+        const bool last_run = !RUNS || run + 1 == n_runs;
+        const uint32_t todo = last_run ? n_iter - nth : (n_iter + 1) / 2;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    acc[r][t][i] = 0.0f;
+                    if constexpr (CARRY) sum[r][t][i] = 0.0f;
+                }
+        if (todo & 1u) {  // an odd one first, so that the rest goes in pairs
+            multiply(o0, ch, nth);
+            carry();
+            ch += stride;
+            nth += 1;
+            fetch(o0, min(ch, last), min(nth, 63u));
+        }
+        for (uint32_t it = todo >> 1; it > 0; --it) {  // o0 holds chunk ch
+            fetch(o1, ch + stride, nth + 1);
+            __builtin_amdgcn_sched_barrier(0);  // the loads first, then the arithmetic
+            multiply(o0, ch, nth);
+            carry();
+            fetch(o0, min(ch + 2 * stride, last), min(nth + 2, 63u));
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(o1, ch + stride, nth + 1);
+            carry();
+            ch += 2 * stride;
+            nth += 2;
+        }
+        if constexpr (CARRY) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[r][t] += sum[r][t];
+        }
+        reduce(run, last_run);
+        if (!last_run) __syncthreads();  // `red` is the waves' own again
     }
 }
 
@@ -626,9 +721,9 @@ __global__ __launch_bounds__(256) void gemm_sum_kernel(const float* first, const
                                                        uint64_t count, float* y) {
     const uint64_t idx = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= count) return;
-    float s = first[idx];
+    double s = first[idx];
     for (uint32_t k = 0; k < n_more; ++k) s += more[k * count + idx];
-    y[idx] = s;
+    y[idx] = (float)s;
 }
 
 }  // namespace bof4

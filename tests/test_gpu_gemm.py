@@ -231,6 +231,61 @@ def test_gemm_wide_tile(rows, cols, n_tokens, share):
     check(cb, codes, scales, oi, ov, rows, cols, block, rand_x(n_tokens, cols, 3))
 
 
+def _rms_error_and_bound(rows, cols, n_tokens, listed, chain, split, seed=7):
+    """The root mean square error of a product of random codes, over that of the results (binary64 on the GPU); and what
+    gemm_kernel makes of it where every entry of the list is added apart from the decoded matrix.  `chain` chunks are 4 *
+    chain additions in a row inside the matrix cores, then come eight waves and `split` workgroups; each rounds what has
+    been added up so far (2^-24 / sqrt(3), over sqrt(2) for where in its binade a number lies: mean square U^2 / 6).
+    The matrix cores also truncate, with one sign: (additions in a row)^2 / 375 roundings more, from dense products of 4 to
+    112 in a row, which this formula gives to 4 % from 16 on and to 8 % below.  Listed positions carry half of the sums' energy here; added apart,
+    they halve the rest's error and add 2.5 roundings (a few terms, then one addition of the two sums).  10 % is for
+    the sample of 10^5 results and more."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    block, n = 64, rows * cols
+    codes = torch.randint(0, 256, (n // 2,), generator=g, device=DEV, dtype=torch.uint8)
+    scales = (torch.rand(n // block, generator=g, device=DEV) * 0.1 + 0.05).to(torch.float16)
+    cb = cb_for(block, 1)
+    oi = ov = tab = None
+    w = binding.bof4_dequantize(codes, scales, n, block, cb)
+    k = n // 150 if listed else 0
+    if k:
+        oi = torch.unique(torch.randint(0, n, (k,), generator=g, device=DEV))
+        k = oi.numel()
+        sigma = float(w.double().pow(2).mean().sqrt()) * (n / k) ** 0.5
+        ov = (torch.randn(k, generator=g, device=DEV) * sigma).to(torch.float16)
+        tab = binding.bof4_gemm_outlier_table(codes, scales, rows, cols, block, cb, oi, ov)
+        w = binding.bof4_dequantize(codes, scales, n, block, cb, oi, ov)
+    packed = binding.bof4_gemm_pack(codes, scales, rows, cols, block)
+    x = torch.randn((n_tokens, cols), generator=g, device=DEV).to(torch.bfloat16)
+    y = binding.bof4_gemm(packed, rows, cols, cb, x, tab, k).double()
+    ref = x.double() @ w.reshape(rows, cols).double().T
+    roundings = 4 * chain / 2 + (4 * chain) ** 2 / 375 + 35 / 8 + split / 2
+    if listed:
+        roundings = roundings / 2 + 2.5
+    bound = 1.1 * U / 6 ** 0.5 * roundings ** 0.5
+    print(f"rms error {float((y - ref).norm() / ref.norm()):.3e}, bound {bound:.3e}")
+    return float((y - ref).norm() / ref.norm()), bound
+
+
+@pytest.mark.parametrize("rows,cols,n_tokens,chain,split", [
+    (6176, 2112, 20, 5, 1), (12288, 4096, 32, 8, 1), (12288, 4096, 100, 8, 1), (8192, 28672, 8, 28, 2),
+    (12320, 2112, 70, 5, 1), (4096, 4096, 100, 4, 2), (16384, 1024, 100, 2, 1), (8000, 1024, 40, 2, 1)])
+def test_gemm_with_a_list_rounds_no_more_than_with_the_list_added_apart(rows, cols, n_tokens, chain, split):
+    """Both ways of cutting the chain of additions (a second set of accumulators; two runs), odd and even numbers of
+    chunks per wave."""
+    err, bound = _rms_error_and_bound(rows, cols, n_tokens, True, chain, split)
+    assert err <= bound, (err, bound)
+
+
+@pytest.mark.parametrize("rows,cols,n_tokens", [(6176, 2112, 5), (12320, 2112, 100)])
+def test_gemm_with_a_list_and_several_chunks_per_wave(rows, cols, n_tokens):
+    """33 chunks over eight waves, so that one wave takes five and the others four: cut after two, or into runs of three
+    and two."""
+    cb, codes, scales, oi, ov = quantized(rows, cols, 64, 1, 1, seed=89)
+    check(cb, codes, scales, oi, ov, rows, cols, 64, rand_x(n_tokens, cols, 15))
+
+
 @pytest.mark.parametrize("opq", [0, 1])
 def test_gemm_a_token_that_is_not_finite_stays_on_its_own(opq):
     """One token carries an infinity: its own results are not finite (every row multiplies it), every other token's are
