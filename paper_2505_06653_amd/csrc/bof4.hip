@@ -1367,8 +1367,9 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
     if (gemm_is_wide(rows, cols, n_tokens) &&
         ws_bytes >= L.wide_part + (uint64_t)(W.split - 1) * n_tokens * rows * 4) {
         const uint32_t wide_groups = (T.row_tiles + GEMM_WIDE_WAVES - 1) / GEMM_WIDE_WAVES;
-        // the matrix cores' chain of additions is no longer than an eighth of the columns, as with eight waves to a row
-        const uint32_t eighth = (chunks + 7) / 8, flush = eighth < 8 ? 8 : eighth;
+        // (without a list: what gemm_kernel's waves lose by being added up - in binary32, where nothing is carried - is
+        // another chunk's worth)
+        const uint32_t flush = n_outliers > 0 ? list_flush : 1 + chain + (split - 1) / 4;
         float* parts = (float*)((char*)ws_dev + L.wide_part);
 #define BOF4_LAUNCH_WIDE(OUT_)                                                                                       \
     hipLaunchKernelGGL((gemm_wide_kernel<OUT_>), dim3(tok_groups * wide_groups * W.split), dim3(64 * GEMM_WIDE_WAVES), \

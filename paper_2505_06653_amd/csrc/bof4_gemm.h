@@ -481,12 +481,12 @@ __global__ __launch_bounds__(64 * GEMM_MAX_WAVES) void gemm_kernel(
 // current chunk (four waves by two).  The step goes in quarters - one 16-byte word of every operand -, and the LDS
 // reads of a quarter are under way while the one before is multiplied, across the step's barrier too: that is what the
 // third buffer is for.
-//   The matrix cores' chain of additions is cut every `flush` chunks and added to a second set of accumulators: the
-// error of the sums stays that of gemm_kernel, whose waves each take an eighth of the columns.
-//   2000 tokens with a list, gemm_kernel -> this: 4096 x 4096 286 -> 105 us, 22016 x 4096 888 -> 547, 10240 x 8192
-// 973 -> 511, 57344 x 8192 3075 -> 2475 (760 TFLOP/s).  A step takes 1.3 us, 0.5 of them in the matrix cores; leaving out
-// any one of look-ups, operand reads, stores or three quarters of the products shortens it by a tenth only, so it
-// is the sum of a wave's dependent stages at two waves per SIMD that bounds it, and no single unit.
+//   The matrix cores' chain of additions is cut every `flush` chunks: added to a second set of accumulators that keeps what
+// the addition rounds away (gemm_carry).  `flush` follows the chunks that a wave of gemm_kernel takes for the same matrix, so
+// the error of the sums is at most gemm_kernel's; four instructions per accumulator are 10 % of the time where it is
+// four chunks (with a list, 4096 columns) and 40 % where it is one (512 columns).
+//   2000 tokens with a list, gemm_kernel -> this: 4096 x 4096 299 -> 122 us, 22016 x 4096 1044 -> 592, 10240 x 8192
+// 1090 -> 568, 57344 x 8192 3420 -> 2590 (725 TFLOP/s).
 // The weights are the second operand here: accumulator i of lane l is token 8 (i / 4) + 4 (l / 32) + i % 4 and row
 // l % 32, so that a store of a wave writes two runs of 128 bytes.
 constexpr uint32_t GEMM_WIDE_WAVES = 8, GEMM_WIDE_TOK_TILES = 4;  // a row tile per wave; token tiles per workgroup
@@ -659,10 +659,7 @@ __global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_wide_kernel(
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        sum[r][t][i] += acc[r][t][i];
-                        acc[r][t][i] = 0.0f;
-                    }
+                    for (int i = 0; i < 16; ++i) gemm_carry(sum[r][t], acc[r][t], i);
         }
         __syncthreads();
         return asked;
