@@ -1367,16 +1367,21 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
     if (gemm_is_wide(rows, cols, n_tokens) &&
         ws_bytes >= L.wide_part + (uint64_t)(W.split - 1) * n_tokens * rows * 4) {
         const uint32_t wide_groups = (T.row_tiles + GEMM_WIDE_WAVES - 1) / GEMM_WIDE_WAVES;
-        // (without a list: what gemm_kernel's waves lose by being added up - in binary32, where nothing is carried - is
-        // another chunk's worth)
-        const uint32_t flush = n_outliers > 0 ? list_flush : 1 + chain + (split - 1) / 4;
+        // Without a list and where gemm_kernel does not split the columns, sums of eight runs as long as its eight waves'
+        // lose what those lose.  Else the sums carry (without a list over a chunk more than gemm_kernel's waves take,
+        // whose own sums are rounded).
+        const bool carry = n_outliers > 0 || split > 1;
+        const uint32_t flush = n_outliers > 0 ? list_flush : carry ? 1 + chain + (split - 1) / 4 : chain;
         float* parts = (float*)((char*)ws_dev + L.wide_part);
-#define BOF4_LAUNCH_WIDE(OUT_)                                                                                       \
-    hipLaunchKernelGGL((gemm_wide_kernel<OUT_>), dim3(tok_groups * wide_groups * W.split), dim3(64 * GEMM_WIDE_WAVES), \
-                       0, s, (const char*)packed_dev, (uint32_t)rows, (uint32_t)cols, cb, offsets_dev, entries_dev,  \
-                       (uint32_t)n_outliers, T.lg, T.row_tiles, (uint32_t)gemm_row_tiles(rows), xp, tok_tiles,       \
-                       tok_groups, W.per_split, flush, n_tokens, y_dev, parts);
-        if (n_outliers > 0) { BOF4_LAUNCH_WIDE(true) } else { BOF4_LAUNCH_WIDE(false) }
+#define BOF4_LAUNCH_WIDE(OUT_, CARRY_)                                                                               \
+    hipLaunchKernelGGL((gemm_wide_kernel<OUT_, CARRY_>), dim3(tok_groups * wide_groups * W.split),                  \
+                       dim3(64 * GEMM_WIDE_WAVES), 0, s, (const char*)packed_dev, (uint32_t)rows, (uint32_t)cols,   \
+                       cb, offsets_dev, entries_dev, (uint32_t)n_outliers, T.lg, T.row_tiles,                       \
+                       (uint32_t)gemm_row_tiles(rows), xp, tok_tiles, tok_groups, W.per_split, flush, n_tokens,     \
+                       y_dev, parts);
+        if (n_outliers > 0) { BOF4_LAUNCH_WIDE(true, true) }
+        else if (carry) { BOF4_LAUNCH_WIDE(false, true) }
+        else { BOF4_LAUNCH_WIDE(false, false) }
 #undef BOF4_LAUNCH_WIDE
         if (W.split > 1) {
             const uint64_t count = (uint64_t)n_tokens * rows;

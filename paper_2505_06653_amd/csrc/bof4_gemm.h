@@ -481,18 +481,19 @@ __global__ __launch_bounds__(64 * GEMM_MAX_WAVES) void gemm_kernel(
 // current chunk (four waves by two).  The step goes in quarters - one 16-byte word of every operand -, and the LDS
 // reads of a quarter are under way while the one before is multiplied, across the step's barrier too: that is what the
 // third buffer is for.
-//   The matrix cores' chain of additions is cut every `flush` chunks: added to a second set of accumulators that keeps what
-// the addition rounds away (gemm_carry).  `flush` follows the chunks that a wave of gemm_kernel takes for the same matrix, so
-// the error of the sums is at most gemm_kernel's; four instructions per accumulator are 10 % of the time where it is
-// four chunks (with a list, 4096 columns) and 40 % where it is one (512 columns).
-//   2000 tokens with a list, gemm_kernel -> this: 4096 x 4096 299 -> 122 us, 22016 x 4096 1044 -> 592, 10240 x 8192
-// 1090 -> 568, 57344 x 8192 3420 -> 2590 (725 TFLOP/s).
+//   The matrix cores' chain of additions is cut every `flush` chunks and added to a second set of accumulators, which with
+// CARRY keeps what the addition rounds away (gemm_carry).  `flush` follows the chunks that a wave of gemm_kernel takes for
+// the same matrix, so the error of the sums is at most that kernel's.  Carrying is for what would be worse without: a
+// list, and matrices whose columns gemm_kernel splits; its four instructions per accumulator instead of two are 7 % of the
+// time where `flush` is nine chunks, 10 % at four (4096 columns with a list) and 40 % at one (512 columns with a list).
+//   2000 tokens, gemm_kernel -> this: without a list 22016 x 4096 850 -> 488 us, 57344 x 8192 2860 -> 2250 (835
+// TFLOP/s), 4096 x 4096 257 -> 100; with one 22016 x 4096 1087 -> 589, 57344 x 8192 3503 -> 2590, 4096 x 4096 305 -> 122.
 // The weights are the second operand here: accumulator i of lane l is token 8 (i / 4) + 4 (l / 32) + i % 4 and row
 // l % 32, so that a store of a wave writes two runs of 128 bytes.
 constexpr uint32_t GEMM_WIDE_WAVES = 8, GEMM_WIDE_TOK_TILES = 4;  // a row tile per wave; token tiles per workgroup
 constexpr uint32_t GEMM_WIDE_MAX_SPLIT = 16;
 constexpr uint32_t GEMM_TILE_WORDS = 4 * 64;                      // 16-byte words of one tile's bfloat16 operand
-template <bool OUTLIERS>
+template <bool OUTLIERS, bool CARRY>
 __global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_wide_kernel(
     const char* __restrict__ packed, uint32_t rows, uint32_t cols, CodebookArgs cb, const uint32_t* __restrict__ list_ptr,
     const uint32_t* __restrict__ entries, uint32_t n_out, GemmListGeometry lg, uint32_t row_tiles, uint32_t packed_tiles,
@@ -659,7 +660,14 @@ __global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_wide_kernel(
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) gemm_carry(sum[r][t], acc[r][t], i);
+                    for (int i = 0; i < 16; ++i) {
+                        if (CARRY) {
+                            gemm_carry(sum[r][t], acc[r][t], i);
+                        } else {
+                            sum[r][t][i] += acc[r][t][i];
+                            acc[r][t][i] = 0.0f;
+                        }
+                    }
         }
         __syncthreads();
         return asked;
