@@ -1171,44 +1171,57 @@ uint32_t gemm_split(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     return (uint32_t)(split < 1 ? 1 : split);
 }
 
-// Where gemm_wide_kernel takes the product over from gemm_kernel.  It computes whole groups of 128 tokens and costs the
-// same for one token of a group as for 128, and it starts later; gemm_kernel takes 32 tokens at a time.  Measured with
-// a list, gemm_kernel / the wide one in us:
-//   2000 tokens: 4096 x 4096 286 / 105, 22016 x 4096 888 / 547, 57344 x 8192 3075 / 2475, 8000 x 1024 155 / 66
-//    300 tokens: 4096 x 4096 53 / 39, 12288 x 4096 84 / 90, 22016 x 4096 154 / 173, 10240 x 8192 166 / 102, 8000 x 1024 28 / 30
-//    256 tokens: 22016 x 4096 117 / 91, 4096 x 11008 69 / 49, 57344 x 8192 390 / 338, 12288 x 4096 64 / 60, 8000 x 1024 21 / 30
-//    160 tokens: 12288 x 4096 49 / 57, 57344 x 8192 296 / 335
-//    128 tokens: 10240 x 8192 65 / 49, 57344 x 8192 204 / 184, 4096 x 4096 22 / 31, 8192 x 8192 41 / 42
-bool gemm_is_wide(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
-    const uint64_t wg_tokens = GEMM_WIDE_TOK_TILES * GEMM_TOKENS, wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS;
-    const uint64_t tok_groups = (n_tokens + wg_tokens - 1) / wg_tokens;
-    if (cols < 512 || (rows + wg_rows - 1) / wg_rows * tok_groups >= (1ull << 23)) return false;  // 2^32 lanes in a launch
-    const bool full = tok_groups * wg_tokens * 10 <= n_tokens * 11;  // hardly a token slot of the groups is empty
-    if (n_tokens <= wg_tokens) return full && rows >= cols && rows * cols > (1ull << 26);
-    if (rows * cols >= (1ull << 27)) return full;  // here it gains least
-    return n_tokens > 320 || (n_tokens > 256 && (cols >= 6144 || rows <= 4096)) ||
-           (full && (rows >= 16384 || cols >= 6144));
+// Where gemm_wide_kernel takes the product over from gemm_kernel, and over how many workgroups it splits the columns: by a
+// model of both kernels' times (us, from 21 shapes of 1 M to 470 M weights at 64 to 2000 tokens without a list, which it
+// gives to 7 and 6 %).  gemm_kernel takes up to four token tiles per launch, gemm_wide_kernel whole groups of 128
+// tokens at the same time for one token of a group as for 128; both go in rounds of 256 workgroups.  gemm_kernel / the wide
+// kernel, measured:
+//   2000 tokens: 4096 x 4096 261 / 100, 22016 x 4096 827 / 517, 8192 x 28672 1378 / 1219, 28672 x 512 309 / 138
+//    640 tokens: 13824 x 5120 209 / 256 (two rounds), 8192 x 28672 430 / 405, 24576 x 6144 356 / 258
+//    340 tokens: 22016 x 4096 152 / 168, 8000 x 1024 26 / 31, 10240 x 8192 160 / 99, 4096 x 4096 50 / 38
+//    128 tokens: 10240 x 8192 60 / 46, 57344 x 8192 184 / 165, 22016 x 4096 55 / 56, 4096 x 4096 18 / 29
+// (With a list both take 10 to 25 % longer, the wide kernel a little less.)
+double gemm_kernel_time(uint64_t rows, uint64_t cols, uint64_t tok_tiles) {
+    const uint64_t n_tokens = tok_tiles * GEMM_TOKENS, per_wg_tiles = gemm_row_tiles_per_wg(rows, cols, n_tokens);
+    const uint64_t split = gemm_split(rows, cols, n_tokens), chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK;
+    const uint64_t per_wg = (chunks + split - 1) / split, waves = per_wg < GEMM_MAX_WAVES ? per_wg : GEMM_MAX_WAVES;
+    const double rounds = (double)((gemm_row_tiles(rows) / per_wg_tiles * split + 255) / 256);
+    const double chain = (double)((per_wg + waves - 1) / waves);
+    auto launch = [&](uint64_t nt) {  // start, sums and stores per tile, steps; the partial results at 4.7 TB/s
+        const double step = per_wg_tiles == 2 ? 0.97 + 0.33 * (double)nt : 0.83 + 0.17 * (double)nt;
+        return 3.0 + rounds * (0.7 * (double)(per_wg_tiles * nt) + chain * step) +
+               (split > 1 ? 2.0 + (double)((split + 1) * nt * GEMM_TOKENS * rows) * 4.0 / 4.7e6 : 0.0);
+    };
+    return (double)(tok_tiles / GEMM_MAX_TILES) * launch(GEMM_MAX_TILES) +
+           (tok_tiles % GEMM_MAX_TILES ? launch(tok_tiles % GEMM_MAX_TILES) : 0.0) + 3e-6 * (double)(n_tokens * cols);
 }
-// Over how many workgroups its columns are split: what the model of its time says is fastest - rounds of 256 workgroups
-// (one per compute unit: its LDS), 1.4 us per chunk and 8 us to start and end, the partial results at 4 TB/s.  The same
-// for every token count of a group of 128, so that the workspace can be sized for all smaller token counts.
 struct GemmWideSplit {
     uint32_t split, per_split;  // workgroups along the columns, chunks each
+    double time;                // with x reordered and the partial results added
 };
-GemmWideSplit gemm_wide_split(uint64_t rows, uint64_t cols, uint64_t tok_groups) {
-    const uint64_t wg_tokens = GEMM_WIDE_TOK_TILES * GEMM_TOKENS, wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS;
-    const uint64_t groups = (rows + wg_rows - 1) / wg_rows * tok_groups;
-    const uint64_t chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK;
-    GemmWideSplit best = {1, (uint32_t)chunks};
-    double best_time = 0.0;
-    for (uint64_t want = 1; want <= GEMM_WIDE_MAX_SPLIT && want * 8 <= chunks; ++want) {
+GemmWideSplit gemm_wide_split(uint64_t rows, uint64_t cols, uint64_t tok_tiles) {
+    const uint64_t tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
+    const uint64_t groups = (rows + GEMM_WIDE_WAVES * GEMM_ROWS - 1) / (GEMM_WIDE_WAVES * GEMM_ROWS) * tok_groups;
+    const uint64_t chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK, slots = tok_groups * GEMM_WIDE_TOK_TILES * GEMM_TOKENS;
+    GemmWideSplit best = {1, (uint32_t)chunks, 0.0};
+    for (uint64_t want = 1; want <= GEMM_WIDE_MAX_SPLIT && (want == 1 || want * 8 <= chunks); ++want) {
         const uint64_t per = (chunks + want - 1) / want, split = (chunks + per - 1) / per;
-        const double rounds = (double)((groups * split + 255) / 256);
-        const double t = rounds * (6.0 + (double)per) * 1.4 +
-                         (split > 1 ? 4.0 + (double)(2 * split + 1) * (double)(tok_groups * wg_tokens * rows) * 4.0 / 4e6 : 0.0);
-        if (want == 1 || t < best_time) best = {(uint32_t)split, (uint32_t)per}, best_time = t;
+        const double time = (double)((groups * split + 255) / 256) * (9.2 + 1.15 * (double)per) +
+                            (split > 1 ? (double)((2 * split + 1) * slots * rows) * 4.0 / 7e6 : 0.0);
+        if (want == 1 || time < best.time) best = {(uint32_t)split, (uint32_t)per, time};
     }
+    best.time += 3.5 + 0.8e-6 * (double)(tok_tiles * GEMM_TOKENS * cols);
     return best;
+}
+// The split where the wide kernel takes the product, else split = 0.
+// 4 % and 1.5 us in hand for what the models do not know: of 924 measured cases the wide kernel was chosen where it is more
+// than 1 % slower in four (8 % at most), the other kernel where that is more than 5 % slower in fifty.
+GemmWideSplit gemm_wide_choice(uint64_t rows, uint64_t cols, uint64_t tok_tiles) {
+    const GemmWideSplit narrow = {0, 0, 0.0};
+    const uint64_t wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS, tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
+    if (cols < 512 || (rows + wg_rows - 1) / wg_rows * tok_groups >= (1ull << 23)) return narrow;  // 2^32 lanes a launch
+    const GemmWideSplit wide = gemm_wide_split(rows, cols, tok_tiles);
+    return 1.04 * wide.time + 1.5 < gemm_kernel_time(rows, cols, tok_tiles) ? wide : narrow;
 }
 
 // Workspace of bof4_gemm: x in the order of the products, then the partial results of the workgroups that share a row.
@@ -1233,13 +1246,12 @@ GemmWsLayout gemm_ws_layout(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
 // What bof4_gemm_workspace_bytes returns: enough for the wide kernel at this and at every smaller token count (its split
 // falls as the token groups grow in number, so the largest need is not that of the most tokens).
 size_t gemm_ws_bytes(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
-    const uint64_t wg_tokens = GEMM_WIDE_TOK_TILES * GEMM_TOKENS;
     size_t need = gemm_ws_layout(rows, cols, n_tokens).total;
-    for (uint64_t g = 1; (g - 1) * wg_tokens < n_tokens; ++g) {
-        const uint64_t t = g * wg_tokens < n_tokens ? g * wg_tokens : n_tokens;  // the group's most tokens
-        if (!gemm_is_wide(rows, cols, t)) continue;                               // and then none of its fewer ones
-        const uint64_t parts = gemm_wide_split(rows, cols, g).split - 1;
-        const size_t bytes = gemm_ws_layout(rows, cols, t).wide_part + parts * t * rows * 4;
+    for (uint64_t tiles = 1; (tiles - 1) * GEMM_TOKENS < n_tokens; ++tiles) {
+        const GemmWideSplit W = gemm_wide_choice(rows, cols, tiles);
+        if (W.split == 0) continue;
+        const uint64_t t = tiles * GEMM_TOKENS < n_tokens ? tiles * GEMM_TOKENS : n_tokens;  // the most tokens in them
+        const size_t bytes = gemm_ws_layout(rows, cols, t).wide_part + (uint64_t)(W.split - 1) * t * rows * 4;
         if (bytes > need) need = bytes;
     }
     return need;
@@ -1362,9 +1374,9 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
     }
     timing_begin(s);
     const uint32_t tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
-    const GemmWideSplit W = gemm_wide_split(rows, cols, tok_groups);
+    const GemmWideSplit W = gemm_wide_choice(rows, cols, tok_tiles);
     // (a workspace that holds the narrow kernel's partial results only gets the narrow kernel)
-    if (gemm_is_wide(rows, cols, n_tokens) &&
+    if (W.split > 0 &&
         ws_bytes >= L.wide_part + (uint64_t)(W.split - 1) * n_tokens * rows * 4) {
         const uint32_t wide_groups = (T.row_tiles + GEMM_WIDE_WAVES - 1) / GEMM_WIDE_WAVES;
         // Without a list and where gemm_kernel does not split the columns, sums of eight runs as long as its eight waves'
