@@ -1358,9 +1358,9 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
     // Chunks in one chain of additions.  gemm_kernel: with a list half of what a wave takes, which holds its error to that of
     // adding the entries apart where they carry half of the sums' energy (measured 0.94 to 1.04 of it over twelve shapes;
     // 0.56 to 0.75 with the entries of Student-t weights).  Additions over more workgroups were that many more roundings, in
-    // binary32; in binary64 they leave room for a chunk more per four of them.
+    // binary32; in binary64 they leave room for a chunk more per two of them (per four in longer chains).
     const uint32_t chain = (per_wg + waves - 1) / waves;  // that a wave of gemm_kernel takes, at most
-    const uint32_t list_flush = (chain > 3 ? chain / 2 : 1) + (split - 1) / 4;
+    const uint32_t half_chain = chain > 3 ? chain / 2 : 1, list_flush = half_chain + (split - 1) / (chain > 3 ? 4 : 2);
     const uint32_t n_runs = n_outliers > 0 && chain > list_flush ? 2 : 1;
     const uint32_t per_wg_tiles = gemm_row_tiles_per_wg(rows, cols, n_tokens);
     const uint32_t row_groups = (uint32_t)(gemm_row_tiles(rows) / per_wg_tiles);
@@ -1383,7 +1383,7 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
         // lose what those lose.  Else the sums carry (without a list over a chunk more than gemm_kernel's waves take,
         // whose own sums are rounded).
         const bool carry = n_outliers > 0 || split > 1;
-        const uint32_t flush = n_outliers > 0 ? list_flush : carry ? 1 + chain + (split - 1) / 4 : chain;
+        const uint32_t flush = n_outliers > 0 ? half_chain + (split - 1) / 4 : carry ? 1 + chain + (split - 1) / 4 : chain;
         float* parts = (float*)((char*)ws_dev + L.wide_part);
 #define BOF4_LAUNCH_WIDE(OUT_, CARRY_)                                                                               \
     hipLaunchKernelGGL((gemm_wide_kernel<OUT_, CARRY_>), dim3(tok_groups * wide_groups * W.split),                  \
