@@ -1180,7 +1180,8 @@ uint32_t gemm_split(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
 //    640 tokens: 13824 x 5120 209 / 256 (two rounds), 8192 x 28672 430 / 405, 24576 x 6144 356 / 258
 //    340 tokens: 22016 x 4096 152 / 168, 8000 x 1024 26 / 31, 10240 x 8192 160 / 99, 4096 x 4096 50 / 38
 //    128 tokens: 10240 x 8192 60 / 46, 57344 x 8192 184 / 165, 22016 x 4096 55 / 56, 4096 x 4096 18 / 29
-// (With a list both take 10 to 25 % longer, the wide kernel a little less.)
+// With a list both take longer, gemm_kernel by some 10 % more:
+//    128 tokens: 22016 x 4096 71 / 64, 4096 x 11008 42 / 36;  256 tokens: 12288 x 4096 75 / 65, 32000 x 4096 148 / 108
 double gemm_kernel_time(uint64_t rows, uint64_t cols, uint64_t tok_tiles) {
     const uint64_t n_tokens = tok_tiles * GEMM_TOKENS, per_wg_tiles = gemm_row_tiles_per_wg(rows, cols, n_tokens);
     const uint64_t split = gemm_split(rows, cols, n_tokens), chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK;
@@ -1213,15 +1214,16 @@ GemmWideSplit gemm_wide_split(uint64_t rows, uint64_t cols, uint64_t tok_tiles) 
     best.time += 3.5 + 0.8e-6 * (double)(tok_tiles * GEMM_TOKENS * cols);
     return best;
 }
-// The split where the wide kernel takes the product, else split = 0.
-// 4 % and 1.5 us in hand for what the models do not know: of 924 measured cases the wide kernel was chosen where it is more
-// than 1 % slower in four (8 % at most), the other kernel where that is more than 5 % slower in fifty.
-GemmWideSplit gemm_wide_choice(uint64_t rows, uint64_t cols, uint64_t tok_tiles) {
+// The split where the wide kernel takes the product, else split = 0.  4 % and 1.5 us in hand for what the models do not
+// know: of the 462 measured cases without a list the wide kernel is chosen where it is more than 1 % slower in one (1.4 %),
+// of those with one in seven (14 % at most); the other kernel where that is more than 5 % slower in eight and seventeen.
+GemmWideSplit gemm_wide_choice(uint64_t rows, uint64_t cols, uint64_t tok_tiles, bool list) {
     const GemmWideSplit narrow = {0, 0, 0.0};
-    const uint64_t wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS, tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
+    const uint64_t wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS;
+    const uint64_t tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
     if (cols < 512 || (rows + wg_rows - 1) / wg_rows * tok_groups >= (1ull << 23)) return narrow;  // 2^32 lanes a launch
     const GemmWideSplit wide = gemm_wide_split(rows, cols, tok_tiles);
-    return 1.04 * wide.time + 1.5 < gemm_kernel_time(rows, cols, tok_tiles) ? wide : narrow;
+    return 1.04 * wide.time + 1.5 < (list ? 1.1 : 1.0) * gemm_kernel_time(rows, cols, tok_tiles) ? wide : narrow;
 }
 
 // Workspace of bof4_gemm: x in the order of the products, then the partial results of the workgroups that share a row.
@@ -1248,7 +1250,7 @@ GemmWsLayout gemm_ws_layout(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
 size_t gemm_ws_bytes(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     size_t need = gemm_ws_layout(rows, cols, n_tokens).total;
     for (uint64_t tiles = 1; (tiles - 1) * GEMM_TOKENS < n_tokens; ++tiles) {
-        const GemmWideSplit W = gemm_wide_choice(rows, cols, tiles);
+        const GemmWideSplit W = gemm_wide_choice(rows, cols, tiles, true);  // (and so wherever it is without a list)
         if (W.split == 0) continue;
         const uint64_t t = tiles * GEMM_TOKENS < n_tokens ? tiles * GEMM_TOKENS : n_tokens;  // the most tokens in them
         const size_t bytes = gemm_ws_layout(rows, cols, t).wide_part + (uint64_t)(W.split - 1) * t * rows * 4;
@@ -1374,7 +1376,7 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
     }
     timing_begin(s);
     const uint32_t tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
-    const GemmWideSplit W = gemm_wide_choice(rows, cols, tok_tiles);
+    const GemmWideSplit W = gemm_wide_choice(rows, cols, tok_tiles, n_outliers > 0);
     // (a workspace that holds the narrow kernel's partial results only gets the narrow kernel)
     if (W.split > 0 &&
         ws_bytes >= L.wide_part + (uint64_t)(W.split - 1) * n_tokens * rows * 4) {
