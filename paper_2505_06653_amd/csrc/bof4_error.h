@@ -192,8 +192,8 @@ __global__ __launch_bounds__(256, 2) void seg_error_kernel(const uint4* __restri
 // Adds the per-workgroup records (256 partial sums per quantity, each in index order, then sixteen of sixteen, in order)
 // and writes the result in the layout of bof4_error_stats: [0] sse, [1] sae, [2] max, [3] outliers, [4] n (integers).
 // Word 4 is stored last, at system scope, so that a host watching it may read the record as soon as it changes.
-// One wave that added 32 records per lane, a load's latency each, took 12 us of a 71 us call on 10001 x 4224 weights;
-// here a lane adds at most two (the call: 73 -> 63 us).
+// One wave that added 32 records per lane, a load's latency each, took 12 us of a 72 us call on 10001 x 4224 weights;
+// here a lane adds at most two (the call: 72.1 -> 63.5 us).
 __global__ __launch_bounds__(1024) void error_final_kernel(const double* __restrict__ partials, uint32_t n_part,
                                                            uint64_t n, double* __restrict__ out) {
     const uint32_t tid = threadIdx.x, q = tid & 3, part = tid >> 2;  // 256 lanes per quantity

@@ -486,6 +486,8 @@ __global__ __launch_bounds__(64 * GEMM_MAX_WAVES) void gemm_kernel(
 // the same matrix, so the error of the sums is at most that kernel's.  Carrying is for what would be worse without: a
 // list, and matrices whose columns gemm_kernel splits; its four instructions per accumulator instead of two are 7 % of the
 // time where `flush` is nine chunks, 10 % at four (4096 columns with a list) and 40 % at one (512 columns with a list).
+//   What bounds it: of a chunk's 2745 clocks the LDS unit is busy 1440, the vector units 1135, the matrix cores 1024
+// (12288 x 4096, 2000 tokens; with a list 3515, 1470, 1695, 1024); two waves per SIMD overlap them in part.
 //   2000 tokens, gemm_kernel -> this: without a list 22016 x 4096 850 -> 488 us, 57344 x 8192 2860 -> 2250 (835
 // TFLOP/s), 4096 x 4096 257 -> 100; with one 22016 x 4096 1087 -> 589, 57344 x 8192 3503 -> 2590, 4096 x 4096 305 -> 122.
 // The weights are the second operand here: accumulator i of lane l is token 8 (i / 4) + 4 (l / 32) + i % 4 and row
@@ -691,8 +693,8 @@ __global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_wide_kernel(
         op = read_operands(0, 0);
     }
     // Three steps to a round, so that neither the buffers' places nor the registers of what is on its way move: a copy
-    // of a register that is being loaded would wait for the load (each step then takes as long as memory's latency:
-    // 57344 x 8192, 128 tokens 176 us).
+    // of a register that is being loaded would wait for the load, and each step would take as long as memory's latency
+    // (keeping them in place made the largest matrices 3 to 5 % faster).
     uint32_t s = 0;
     for (uint32_t rounds = n_steps / 3; rounds > 0; --rounds, s += 3) {
         const Ahead o4 = step(s, 0, o2, o3.q.x);
