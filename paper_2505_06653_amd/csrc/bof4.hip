@@ -158,7 +158,7 @@ BinTable make_bin_table(const CodebookArgs& cb) {
 
 // ------------------------------------------------------------------------------------------------ workspace
 constexpr uint32_t QTILE = 2048;         // weights per quantise tile (256 threads x 8)
-size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+constexpr size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct QuantWsLayout {
     size_t header, tile_cnt, tile_base, tile_off, stage_idx, stage_val, total;
@@ -249,14 +249,30 @@ static_assert(pass_grid(false, true, false) <= PASS_GRID_MAX && pass_grid(false,
 // times what the windows of the one-pass search let through on a large tensor, five times what a second pass
 // leaves), at most 2^27; below 2^29 weights n / 16, because the windows are wider there (fewer samples to place them:
 // 4 to 5 % of the weights at 2^26) and a wave's share of the list is small enough for its fill to vary.
-// The MAE step samples one tile in 16 to place its windows, from 16384 wave tiles (2^26 weights at block 64) up: below
-// that the second pass over the weights costs less than it would save.
-constexpr uint32_t MAE_SAMPLE_MASK = 15;
+// The MAE step places its windows by the largest power of two in the tiles that leaves 2000 of them or more, at most one in
+// 64: about one for each wave of the sampling pass.  Fewer make the windows wider, more take longer (655 M weights, one in
+// 32 / 16 / 8 / 4 / 2: 572 / 594 / 643 / 740 / 900 us; 65 M: 138 at one in 16, 134 / 134 / 149).  From 16384 tiles (2^26
+// weights at block 64) up, 129 us against 174 for a second pass over the weights; at 8200 tiles it is 115 against 124, but
+// the windows let so much through that the list is three quarters full; at 4096 tiles it is 99 against 90.
+constexpr uint64_t MAE_SAMPLED_TILES = 2000;
 constexpr uint64_t MAE_SAMPLING_MIN_TILES = 16384;
+uint32_t mae_sample_mask(uint64_t tiles) {
+    uint32_t one_in = 2;
+    while (one_in < 64 && tiles / (2 * one_in) >= MAE_SAMPLED_TILES) one_in *= 2;
+    return one_in - 1;
+}
 uint64_t mae_cand_entries(uint64_t n) {
     const uint64_t e = n < (1ull << 29) ? n / 16 : n / 32;
     return e < (1ull << 27) ? e : (1ull << 27);
 }
+// Two waves per SIMD of mae_pass_kernel, three of mae_window_kernel.
+constexpr uint32_t MAE_PASS_GRID = 2048 / MAE_PASS_WAVES, MAE_WINDOW_GRID = 3072 / WAVES_PER_WG;
+constexpr uint32_t MAE_SLOTS = MAE_PASS_GRID * MAE_PASS_WAVES * MAE_SLOTS_PER_PASS_WAVE;  // at most
+static_assert(MAE_WINDOW_GRID <= MAE_MAX_WGS && MAE_PASS_GRID <= MAE_MAX_WGS &&
+                  MAE_WINDOW_GRID * WAVES_PER_WG * MAE_SLOTS_PER_WINDOW_WAVE == MAE_SLOTS,
+              "both kernels add their sums up over the same slots");
+// The room for counts, floating-point partials and the list's fill is what a count per wave once took (workspaces of that
+// size are in use).
 struct MaeWsLayout {
     size_t hist, state, cnt_part, sae_part, record, cand_count, cand_full, cand, total;
 };
@@ -265,10 +281,16 @@ MaeWsLayout mae_ws_layout(uint64_t n) {
     size_t o = 0;
     L.hist = o;     o += 16 * 256 * 8;
     L.state = o;    o += align_up(16 * sizeof(MaeLevelState), 256);
-    L.cnt_part = o; o += align_up((size_t)17 * SEG_GRID * WAVES_PER_WG * 8, 256);
-    L.sae_part = o; o += align_up((size_t)SEG_GRID * 2 * 8, 256);
+    L.cnt_part = o;
+    L.sae_part = L.cnt_part + align_up((size_t)17 * MAE_MAX_WGS * 8, 256);
+    L.cand_count = L.sae_part + align_up((size_t)MAE_SLOTS * 2 * 8, 256);
+    constexpr size_t room = align_up((size_t)17 * SEG_GRID * WAVES_PER_WG * 8, 256) + align_up((size_t)SEG_GRID * 2 * 8, 256) +
+                            align_up((size_t)SEG_GRID * WAVES_PER_WG * 4, 256);
+    static_assert(align_up((size_t)17 * MAE_MAX_WGS * 8, 256) +
+                      align_up((size_t)MAE_SLOTS * 2 * 8, 256) +
+                      (size_t)MAE_MAX_WGS * WAVES_PER_WG * 4 <= room, "the records fit where they stood");
+    o += room;
     L.record = o;   o += align_up(MAE_REC * 8, 256);
-    L.cand_count = o; o += align_up((size_t)SEG_GRID * WAVES_PER_WG * 4, 256);
     L.cand_full = o;  o += 256;
     L.cand = o;       o += align_up(mae_cand_entries(n) * 8, 256);
     L.total = o;
@@ -1658,8 +1680,8 @@ int bof4_lloyd_step_mae(const void* w_dev, uint64_t n, uint32_t block, const dou
     const uint32_t seg = block < 64 ? block : 64;
     const uint64_t n_seg = n / seg;
     const uint64_t tiles = (n_seg + 63) / 64;
-    const uint64_t wantg = (tiles + WAVES_PER_WG - 1) / WAVES_PER_WG;
-    const uint32_t sgrid = (uint32_t)(wantg < SEG_GRID ? wantg : SEG_GRID);
+    const uint64_t wantg = (tiles + MAE_PASS_WAVES - 1) / MAE_PASS_WAVES;
+    const uint32_t sgrid = (uint32_t)(wantg < MAE_PASS_GRID ? wantg : MAE_PASS_GRID);
     const uint4* w = (const uint4*)w_dev;
     double* direct = (double*)device_view_of_host(out_host);
     if (direct) out_host->n_used = FLAG_PENDING;  // the word the last kernel writes last
@@ -1669,65 +1691,85 @@ int bof4_lloyd_step_mae(const void* w_dev, uint64_t n, uint32_t block, const dou
     uint32_t* cand_count = (uint32_t*)(base + ML.cand_count);
     uint32_t* cand_full = (uint32_t*)(base + ML.cand_full);
     unsigned long long* cand = (unsigned long long*)(base + ML.cand);
-    const uint32_t cand_waves = sgrid * WAVES_PER_WG;
-    const uint32_t cand_cap = (uint32_t)(mae_cand_entries(n) / cand_waves);
+    const uint32_t n_slots = sgrid * MAE_PASS_WAVES * MAE_SLOTS_PER_PASS_WAVE;
     const bool zero_region_searched = !((skip_mask >> bt.code_of_zero) & 1u);
-    const bool use_list = passes >= 3 && cand_cap >= 8 && !(opq && zero_region_searched);
-    // One pass over all the weights instead of two (large tensors): a sampling pass over one tile in 16 tells the full
-    // first pass which first digits to write to the list (bof4_mae.h).
+    const bool use_list = passes >= 3 && mae_cand_entries(n) / (sgrid * MAE_PASS_WAVES) >= 8 && !(opq && zero_region_searched);
+    // One pass over all the weights instead of two (large tensors): a sampling pass over one tile in 16 tells
+    // mae_window_kernel which first digits to write to the list (bof4_mae.h).
     const bool sampling = use_list && tiles >= MAE_SAMPLING_MIN_TILES && std::getenv("BOF4_MAE_NO_SAMPLING") == nullptr;
+    const uint32_t cand_waves = sampling ? MAE_WINDOW_GRID * WAVES_PER_WG : sgrid * MAE_PASS_WAVES;
+    const uint32_t cand_cap = (uint32_t)(mae_cand_entries(n) / cand_waves);
     hipLaunchKernelGGL(mae_init_kernel, dim3(16), dim3(256), 0, s, lc, state, hist);
-#define BOF4_LAUNCH_MAE(II, FIRST_, CAPTURE_, CAND_, GATE_, SAMPLE_)                                                  \
-    if (bt.fast && opq) hipLaunchKernelGGL((mae_pass_kernel<II, true, true, FIRST_, CAPTURE_>), dim3(sgrid), dim3(256), \
+#define BOF4_LAUNCH_MAE(II, KIND_, CAND_, FULL_, SAMPLE_)                                                            \
+    if (bt.fast && opq) hipLaunchKernelGGL((mae_pass_kernel<II, true, true, KIND_>), dim3(sgrid), dim3(64 * MAE_PASS_WAVES),          \
                                            0, s, w, n_seg, cb, bt, signed_norm, T2, state, hist, cnt_part, sae_part,  \
-                                           CAND_, cand_count, cand_cap, GATE_, unweighted, SAMPLE_);                  \
-    else if (bt.fast) hipLaunchKernelGGL((mae_pass_kernel<II, true, false, FIRST_, CAPTURE_>), dim3(sgrid), dim3(256),  \
+                                           CAND_, cand_count, cand_cap, FULL_, cand_waves, unweighted, SAMPLE_);                  \
+    else if (bt.fast) hipLaunchKernelGGL((mae_pass_kernel<II, true, false, KIND_>), dim3(sgrid), dim3(64 * MAE_PASS_WAVES),           \
                                          0, s, w, n_seg, cb, bt, signed_norm, T2, state, hist, cnt_part, sae_part,    \
-                                         CAND_, cand_count, cand_cap, GATE_, unweighted, SAMPLE_);                    \
-    else if (opq) hipLaunchKernelGGL((mae_pass_kernel<II, false, true, FIRST_, CAPTURE_>), dim3(sgrid), dim3(256), 0,   \
+                                         CAND_, cand_count, cand_cap, FULL_, cand_waves, unweighted, SAMPLE_);                    \
+    else if (opq) hipLaunchKernelGGL((mae_pass_kernel<II, false, true, KIND_>), dim3(sgrid), dim3(64 * MAE_PASS_WAVES), 0,            \
                                      s, w, n_seg, cb, bt, signed_norm, T2, state, hist, cnt_part, sae_part, CAND_,    \
-                                     cand_count, cand_cap, GATE_, unweighted, SAMPLE_);                               \
-    else hipLaunchKernelGGL((mae_pass_kernel<II, false, false, FIRST_, CAPTURE_>), dim3(sgrid), dim3(256), 0, s, w,     \
+                                     cand_count, cand_cap, FULL_, cand_waves, unweighted, SAMPLE_);                               \
+    else hipLaunchKernelGGL((mae_pass_kernel<II, false, false, KIND_>), dim3(sgrid), dim3(64 * MAE_PASS_WAVES), 0, s, w,              \
                             n_seg, cb, bt, signed_norm, T2, state, hist, cnt_part, sae_part, CAND_, cand_count,       \
-                            cand_cap, GATE_, unweighted, SAMPLE_);
-#define BOF4_LAUNCH_MAE_BLOCK(FIRST_, CAPTURE_, CAND_, GATE_, SAMPLE_)                 \
-    switch (block) {                                                                   \
-        case 32: BOF4_LAUNCH_MAE(32, FIRST_, CAPTURE_, CAND_, GATE_, SAMPLE_) break;   \
-        case 64: BOF4_LAUNCH_MAE(64, FIRST_, CAPTURE_, CAND_, GATE_, SAMPLE_) break;   \
-        case 128: BOF4_LAUNCH_MAE(128, FIRST_, CAPTURE_, CAND_, GATE_, SAMPLE_) break; \
-        default: BOF4_LAUNCH_MAE(256, FIRST_, CAPTURE_, CAND_, GATE_, SAMPLE_) break;  \
+                            cand_cap, FULL_, cand_waves, unweighted, SAMPLE_);
+#define BOF4_LAUNCH_MAE_BLOCK(KIND_, CAND_, FULL_, SAMPLE_)                 \
+    switch (block) {                                                         \
+        case 32: BOF4_LAUNCH_MAE(32, KIND_, CAND_, FULL_, SAMPLE_) break;   \
+        case 64: BOF4_LAUNCH_MAE(64, KIND_, CAND_, FULL_, SAMPLE_) break;   \
+        case 128: BOF4_LAUNCH_MAE(128, KIND_, CAND_, FULL_, SAMPLE_) break; \
+        default: BOF4_LAUNCH_MAE(256, KIND_, CAND_, FULL_, SAMPLE_) break;  \
     }
+#define BOF4_LAUNCH_MAE_WINDOW_AS(II, FAST_, OPQ_)                                                                    \
+    hipLaunchKernelGGL((mae_window_kernel<II, FAST_, OPQ_>), dim3(MAE_WINDOW_GRID), dim3(256), 0, s, w, n_seg, cb, bt,      \
+                       signed_norm, T2, state, hist, cnt_part, sae_part, cand, cand_count, cand_cap, cand_full, unweighted);
+#define BOF4_LAUNCH_MAE_WINDOW(II)                                                      \
+    if (bt.fast && opq) { BOF4_LAUNCH_MAE_WINDOW_AS(II, true, true) }                   \
+    else if (bt.fast) { BOF4_LAUNCH_MAE_WINDOW_AS(II, true, false) }                    \
+    else if (opq) { BOF4_LAUNCH_MAE_WINDOW_AS(II, false, true) }                        \
+    else { BOF4_LAUNCH_MAE_WINDOW_AS(II, false, false) }
     unsigned long long* const no_cand = nullptr;
     const uint32_t* const no_gate = nullptr;
+    auto select = [&](const uint32_t* gate, bool first, bool last, bool wrote_list, bool check_window) {
+        hipLaunchKernelGGL(mae_select_kernel, dim3(1), dim3(1024), 0, s, state, hist, cnt_part, sae_part,
+                           sampling ? MAE_WINDOW_GRID : sgrid, sampling ? sgrid : 0u, n_slots, gate, first ? 1 : 0, last ? 1 : 0,
+                           (uint32_t)skip_mask, wrote_list ? cand_count : (const uint32_t*)nullptr, cand_waves, cand_cap,
+                           cand_full, check_window ? 1 : 0, direct ? direct : rec_dev, unweighted);
+    };
     if (sampling) {
-        BOF4_LAUNCH_MAE_BLOCK(true, false, no_cand, no_gate, MAE_SAMPLE_MASK)
-        hipLaunchKernelGGL(mae_predict_kernel, dim3(1), dim3(1024), 0, s, state, hist, cnt_part, sgrid,
-                           (uint32_t)skip_mask);
-    }
-    for (uint32_t p = 0; p < passes; ++p) {
-        const bool first = p == 0;
-        // the pass that writes the list: the first one if it captures by windows, else the second
-        const uint32_t list_pass = sampling ? 0u : 1u;
-        const bool writes_list = use_list && p == list_pass, reads_list = use_list && p > list_pass;
-        unsigned long long* cand_w = writes_list ? cand : nullptr;
-        const uint32_t* gate = reads_list ? cand_full : nullptr;  // the scan only runs if the list cannot be used
-        if (first) timing_begin(s);
-        if (reads_list)
-            hipLaunchKernelGGL(mae_list_kernel, dim3(sgrid), dim3(256), 0, s, cand, cand_count, cand_cap, cand_full,
-                               state, hist, unweighted);
-        if (first && sampling) {
-            BOF4_LAUNCH_MAE_BLOCK(true, true, cand_w, gate, 0u)
-        } else if (first) {
-            BOF4_LAUNCH_MAE_BLOCK(true, false, cand_w, gate, 0u)
-        } else {
-            BOF4_LAUNCH_MAE_BLOCK(false, false, cand_w, gate, 0u)
+        const uint32_t sample_mask = mae_sample_mask(tiles);
+        BOF4_LAUNCH_MAE_BLOCK(MAE_SAMPLE, no_cand, no_gate, sample_mask)
+        hipLaunchKernelGGL(mae_predict_kernel, dim3(1), dim3(1024), 0, s, state, hist, (double)n / (sample_mask + 1),
+                           (uint32_t)skip_mask, (double)cand_cap * cand_waves / (sample_mask + 1), cand_full);
+        timing_begin(s);
+        switch (block) {
+            case 32: BOF4_LAUNCH_MAE_WINDOW(32) break;
+            case 64: BOF4_LAUNCH_MAE_WINDOW(64) break;
+            case 128: BOF4_LAUNCH_MAE_WINDOW(128) break;
+            default: BOF4_LAUNCH_MAE_WINDOW(256) break;
         }
-        if (first) timing_end(s);
-        hipLaunchKernelGGL(mae_select_kernel, dim3(1), dim3(1024), 0, s, state, hist, cnt_part, sae_part, sgrid,
-                           first ? 1 : 0, p + 1 == passes ? 1 : 0, (uint32_t)skip_mask,
-                           writes_list ? cand_count : (const uint32_t*)nullptr, cand_waves, cand_cap, cand_full,
-                           (writes_list && sampling) ? 1 : 0, direct ? direct : rec_dev, unweighted);
+        timing_end(s);
+        select(no_gate, true, false, true, true);
+        // only if the list cannot be used: the first pass over all the weights after all
+        BOF4_LAUNCH_MAE_BLOCK(MAE_FIRST, no_cand, cand_full, 0u)
+        select(cand_full, true, false, false, false);
     }
+    for (uint32_t p = sampling ? 1 : 0; p < passes; ++p) {
+        const bool first = p == 0;
+        const bool writes_list = use_list && !sampling && p == 1, reads_list = use_list && p > (sampling ? 0u : 1u);
+        unsigned long long* cand_w = writes_list || reads_list ? cand : nullptr;
+        const uint32_t* full = reads_list ? cand_full : nullptr;
+        if (first) {
+            timing_begin(s);
+            BOF4_LAUNCH_MAE_BLOCK(MAE_FIRST, cand_w, full, 0u)
+            timing_end(s);
+        } else {
+            BOF4_LAUNCH_MAE_BLOCK(MAE_LATER, cand_w, full, 0u)
+        }
+        select(no_gate, first, p + 1 == passes, writes_list, false);
+    }
+#undef BOF4_LAUNCH_MAE_WINDOW
+#undef BOF4_LAUNCH_MAE_WINDOW_AS
 #undef BOF4_LAUNCH_MAE_BLOCK
 #undef BOF4_LAUNCH_MAE
     HIP_TRY(hipGetLastError());

@@ -15,10 +15,11 @@
 // Every wave appends to a region of its own; if one of them runs full (a tensor of equal numbers), the later passes
 // scan the weights as before.
 // Large tensors get by with ONE pass over all the weights: a first-digit histogram over one tile in 16 (picked by a
-// hash of the tile number) says where every region's median will be to within a few digits; the full first pass then
-// writes the elements whose first digit lies in that window to the list while it fills the exact histogram.  If the
-// exact first digit of every region falls inside its window (it does unless the sampled tiles differ from the rest),
-// all later passes read the list; if not, they scan the weights, as they do when the list runs full.
+// hash of the tile number) says where every region's median will be to within a few digits; the full pass
+// (mae_window_kernel) then adds up what lies below that window and in all, and writes the elements inside to the list.
+// If the exact first digit of every region falls inside its window (it does unless the sampled tiles differ from the
+// rest), all later passes read the list; if not, or if the list runs full, the first pass and all others scan the
+// weights.
 //
 // What is computed is "the smallest x_k with 2 * sum_{x_j <= x_k} a_j >= sum_j a_j" - the lower weighted median,
 // which minimises sum a_j |x_j - c|.  (The closing formula of appendix B.4 names the element before it; its own
@@ -36,7 +37,7 @@ struct MaeLevelState {
     uint32_t pad;     // 1: the caller does not want this region's median (no search after the first pass)
     unsigned long long base;   // weight of the elements whose sub lies below prefix << hi
     unsigned long long total;  // weight of the whole region
-    uint32_t win_lo;   // first digits win_lo .. win_lo + win_len - 1: what a capturing first pass writes to the list
+    uint32_t win_lo;   // first digits win_lo .. win_lo + win_len - 1: what mae_window_kernel writes to the list
     uint32_t win_len;
 };
 // Per-region constants from the host: key range of the region.
@@ -45,6 +46,76 @@ struct MaeLevelConst {
     uint32_t bits[16];  // significant bits of (key of upper bound - klo)
 };
 constexpr int MAE_REC = 51;  // doubles of the result record (layout of bof4_mae_stats)
+constexpr uint32_t MAE_PASS_WAVES = 8;  // waves that share one histogram in mae_pass_kernel: one workgroup per compute unit
+constexpr uint32_t MAE_MAX_WGS = 768;  // most workgroups of a pass: the stride of the counts' records
+// Tile t belongs to slot t mod n_slots.  The two floating-point sums are added up per slot, in ascending order of its
+// tiles, and then over the slots in order, so that they do not depend on which kernel read the weights: a wave of
+// mae_pass_kernel takes 3 slots, one of mae_window_kernel (whose grid holds half as many waves again) 2.
+constexpr uint32_t MAE_SLOTS_PER_PASS_WAVE = 3;
+constexpr uint32_t MAE_SLOTS_PER_WINDOW_WAVE = 2;
+// Bins of all regions' windows together in mae_window_kernel.
+constexpr uint32_t MAE_WINDOW_BINS = 1024;
+// A wave-uniform number to scalar registers (divisions leave it in vector registers).
+__device__ __forceinline__ uint64_t wave_uniform(uint64_t v) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32;
+}
+struct MaeTiles {
+    uint64_t t, slot;  // the wave's next tile and its slot; slot >= n_slots: none
+    uint64_t n_waves, n_slots, step, end;
+    // Which tiles the sampling pass looks at: one in (sample_mask + 1), spread by a multiplicative hash so that the choice
+    // does not follow the rows and columns of the matrices behind the tensor.  Its waves take contiguous stretches, in
+    // which the hash is spread evenly (its sums are not used).
+    uint32_t sample_mask;
+    __device__ __forceinline__ bool more() const { return slot < n_slots; }
+    __device__ __forceinline__ void settle() {  // to the first tile from t on that counts
+        while (more()) {
+            if (t >= end) t = slot = slot + n_waves;
+            else if (sample_mask != 0u && (((uint32_t)t * 0x9E3779B1u) >> 16 & sample_mask) != 0u) t += step;
+            else break;
+        }
+    }
+    __device__ __forceinline__ MaeTiles next() const {
+        MaeTiles m = *this;
+        m.t += step;
+        m.settle();
+        return m;
+    }
+};
+__device__ __forceinline__ MaeTiles mae_tiles(uint64_t wave, uint64_t n_waves, uint32_t slots_per_wave, uint64_t n_tiles,
+                                              uint32_t sample_mask) {
+    MaeTiles m = {wave, wave, n_waves, n_waves * slots_per_wave, n_waves * slots_per_wave, n_tiles, sample_mask};
+    if (sample_mask != 0u) {
+        m.t = wave_uniform(n_tiles * wave / n_waves);
+        m.end = wave_uniform(n_tiles * (wave + 1) / n_waves);
+        m.step = 1;
+        m.n_slots = n_waves;
+    }
+    m.settle();
+    return m;
+}
+struct MaeSlotSums {
+    uint64_t slot;
+    double sae, w_est;
+    // The wave goes on in `next_slot`: store the sums of the slots before it (all lanes), of which it worked on `slot`.
+    __device__ __forceinline__ void close_until(uint64_t next_slot, uint64_t n_waves, uint32_t lane, double* __restrict__ sae_part) {
+        if (slot >= next_slot) return;
+        double s = sae, we = w_est;
+#pragma unroll
+        for (int mk = 32; mk >= 1; mk >>= 1) {
+            s += __shfl_xor(s, mk, 64);
+            we += __shfl_xor(we, mk, 64);
+        }
+        for (; slot < next_slot; slot += n_waves) {
+            if (lane == 0) {
+                sae_part[2 * slot] = s;
+                sae_part[2 * slot + 1] = we;
+            }
+            s = we = 0.0;
+        }
+        sae = w_est = 0.0;
+    }
+};
 
 // Order-preserving map from binary32 to uint32 (negative numbers reversed below the positive ones).
 __device__ __forceinline__ uint32_t order_key(float x) {
@@ -74,17 +145,13 @@ __global__ __launch_bounds__(256) void mae_init_kernel(MaeLevelConst lc, MaeLeve
     }
 }
 
-// Which tiles the sampling pass looks at: one in (sample_mask + 1), spread by a multiplicative hash so that the choice
-// does not follow the rows and columns of the matrices behind the tensor.
-__host__ __device__ inline bool mae_tile_sampled(uint64_t t, uint32_t sample_mask) {
-    return ((((uint32_t)t * 0x9E3779B1u) >> 16) & sample_mask) == 0u;
-}
-
-// One pass over the weights.  FIRST also counts the regions' elements and accumulates the error sum
-// sum |block constant| |x - level| at the current codebook; with CAPTURE it writes the elements whose first digit lies
-// in the region's window to the list.  sample_mask != 0: only the sampled tiles.
-template <int I, bool FAST, bool OPQ, bool FIRST, bool CAPTURE = false>
-__global__ __launch_bounds__(256, 2) void mae_pass_kernel(const uint4* __restrict__ w, uint64_t n_seg, CodebookArgs cb,
+// One pass over the weights, by KIND: the first one also counts the regions' elements and accumulates the error sum
+// sum |block constant| |x - level| at the current codebook; the sampling pass is a first one over the sampled tiles
+// without either (a third of its vector work).  A later pass reads the list (n_stretches stretches of at most cand_cap
+// entries, cand_count of them) where there is one and *full says that it can be used, and the weights where not.
+enum MaePass { MAE_SAMPLE, MAE_FIRST, MAE_LATER };
+template <int I, bool FAST, bool OPQ, MaePass KIND>
+__global__ __launch_bounds__(64 * MAE_PASS_WAVES, 2) void mae_pass_kernel(const uint4* __restrict__ w, uint64_t n_seg, CodebookArgs cb,
                                                            BinTable bt, int signed_norm, double T2,
                                                            const MaeLevelState* __restrict__ state,
                                                            unsigned long long* __restrict__ hist_g,
@@ -92,63 +159,100 @@ __global__ __launch_bounds__(256, 2) void mae_pass_kernel(const uint4* __restric
                                                            double* __restrict__ sae_part,
                                                            unsigned long long* __restrict__ cand,
                                                            uint32_t* __restrict__ cand_count, uint32_t cand_cap,
-                                                           const uint32_t* __restrict__ gate, int unweighted,
-                                                           uint32_t sample_mask) {
+                                                           const uint32_t* __restrict__ full, uint32_t n_stretches,
+                                                           int unweighted, uint32_t sample_mask) {
     using C = SegCfg<I>;
-    static_assert(FIRST || !CAPTURE, "only the first pass captures by window");
-    // `gate`: this launch only matters if the word it points to is set (the scan that stands in for a list that ran
-    // full).  `cand`: append the elements that still count to this wave's stretch of the list.
-    if (gate != nullptr && *gate == 0u) return;
+    constexpr bool FIRST = KIND != MAE_LATER, SUMS = KIND == MAE_FIRST;
+    // full != nullptr, a first pass: this launch only matters if the word is set.  cand != nullptr where no list is read:
+    // append the elements that still count to this wave's stretch of the list.
+    const bool from_list = full != nullptr && *full == 0u;
+    if (FIRST && from_list) return;
     struct Shared {  // one object, so that the table sits at LDS offset 0 (reachable by an immediate offset)
         uint2 tab[BIN_TABLE_ENTRIES];
         uint4 info[16];    // per region: klo, (lo | hi << 8 | digit mask << 16), then prefix and active flag; in
                            // the first pass (no prefix yet, every region active, its key range has exactly hi bits):
-                           // klo, (lo | window start << 8 | window length << 16), the region's level as binary64
+                           // klo, lo, the region's level as binary64
         unsigned long long hist[16 * 256];
-        uint32_t cntcol[WAVES_PER_WG * 8 * 64];  // per lane, two 16-bit counters per word: regions 2p and 2p + 1
-        char stage[WAVES_PER_WG * C::STAGE_BYTES];
-        uint16_t tie[WAVES_PER_WG * TIE_BUF_HALFWORDS] __attribute__((aligned(16)));
+        uint32_t cntcol[MAE_PASS_WAVES * 8 * 64];  // per lane, two 16-bit counters per word: regions 2p and 2p + 1
+        unsigned long long cnt[17];              // the workgroup's counts of the regions, and of outliers
+        char stage[MAE_PASS_WAVES * C::STAGE_BYTES] __attribute__((aligned(16)));  // (off 16 bytes: 35 % slower)
+        uint16_t tie[MAE_PASS_WAVES * TIE_BUF_HALFWORDS] __attribute__((aligned(16)));
     };
     __shared__ __attribute__((aligned(16))) Shared sh;
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     bin_table_fill(sh.tab, bt, tid, blockDim.x);
+    if (tid < 17) sh.cnt[tid] = 0ull;
     if (tid < 16) {
         const MaeLevelState s = state[tid];
         const uint32_t hi = s.hi, lo = hi > 8 ? hi - 8 : 0;
         const uint32_t packed = lo | (hi << 8) | (((1u << (hi - lo)) - 1u) << 16);
         if (FIRST) {
             const unsigned long long lv = (unsigned long long)__double_as_longlong(cb.cb64[tid]);
-            sh.info[tid] = make_uint4(s.klo, lo | (s.win_lo << 8) | (s.win_len << 16), (uint32_t)lv, (uint32_t)(lv >> 32));
+            sh.info[tid] = make_uint4(s.klo, lo, (uint32_t)lv, (uint32_t)(lv >> 32));
         } else {
             sh.info[tid] = make_uint4(s.klo, packed, s.prefix, (hi != 0 && s.total != 0ull && s.pad == 0u) ? 1u : 0u);
         }
     }
-    for (uint32_t i = tid; i < 16 * 256; i += 256) sh.hist[i] = 0ull;
+    for (uint32_t i = tid; i < 16 * 256; i += 64 * MAE_PASS_WAVES) sh.hist[i] = 0ull;
     uint32_t* cntcol = sh.cntcol + wave * 8 * 64;
-    if (FIRST) {
+    if (SUMS) {
 #pragma unroll
         for (int p = 0; p < 8; ++p) cntcol[p * 64 + lane] = 0u;
     }
     __syncthreads();
+    if (KIND == MAE_LATER && from_list) {
+        const uint64_t n_waves = (uint64_t)gridDim.x * MAE_PASS_WAVES;
+        // every stretch in two halves, its even and odd runs of 512 entries: 3072 stretches deal out evenly to 2048 waves
+        constexpr uint32_t AHEAD = 8, RUN = 64 * AHEAD;  // loads in flight per lane
+        for (uint64_t half = (uint64_t)blockIdx.x * MAE_PASS_WAVES + wave; half < 2ull * n_stretches; half += n_waves) {
+            const uint32_t count = cand_count[half >> 1];  // at most cand_cap, or the list would count as full
+            const unsigned long long* mine = cand + (half >> 1) * cand_cap;
+            for (uint32_t i0 = ((uint32_t)half & 1u) * RUN + lane; i0 < count; i0 += 2 * RUN) {
+                unsigned long long e[AHEAD];
+#pragma unroll
+                for (uint32_t u = 0; u < AHEAD; ++u) e[u] = mine[min(i0 + 64 * u, count - 1)];
+#pragma unroll
+                for (uint32_t u = 0; u < AHEAD; ++u) {
+                    const uint32_t sub = (uint32_t)e[u], l = (uint32_t)(e[u] >> 32) & 15u, m15 = (uint32_t)(e[u] >> 36) & 0x7fffu;
+                    const uint4 inf = sh.info[l];
+                    const uint32_t lo = inf.y & 0xffu, hi = (inf.y >> 8) & 0xffu, dmask = inf.y >> 16;
+                    if (i0 + 64 * u < count && inf.w != 0u && (sub >> hi) == inf.z) {
+                        const float a = f16_bits_to_f32(m15);
+                        const unsigned long long W =
+                            (a < 65536.0f) ? (unweighted ? 1ull : (unsigned long long)((double)a * 16777216.0)) : 0ull;
+                        atomicAdd(&sh.hist[l * 256 + ((sub >> lo) & dmask)], W);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        for (uint32_t i = tid; i < 16 * 256; i += 64 * MAE_PASS_WAVES) {
+            const unsigned long long v = sh.hist[i];
+            if (v != 0ull) atomicAdd(&hist_g[i], v);
+        }
+        return;
+    }
+    const bool writes_list = KIND == MAE_LATER && cand != nullptr && full == nullptr;
     const uint2* tab = sh.tab;
     const uint32_t lane_off = bin_lane_offset(threadIdx.x & 63u);
     char* stage = sh.stage + wave * C::STAGE_BYTES;
     uint16_t* tie_buf = sh.tie + wave * TIE_BUF_HALFWORDS;
     const uint64_t n_vec = n_seg * C::NV;
     const uint64_t n_tiles = (n_seg + 63) / 64;
-    const uint64_t n_waves = (uint64_t)gridDim.x * WAVES_PER_WG;
-    const uint64_t gw = (uint64_t)blockIdx.x * WAVES_PER_WG + wave;
-    const uint64_t t0 = n_tiles * gw / n_waves, t1 = n_tiles * (gw + 1) / n_waves;
+    const uint64_t n_waves = (uint64_t)gridDim.x * MAE_PASS_WAVES;
+    const uint64_t gw = (uint64_t)blockIdx.x * MAE_PASS_WAVES + wave;
 
     // outliers were zeroed: they ran through the loop as x = +0 of the zero region and are taken out again
     const uint32_t cz = bt.code_of_zero;
     const uint32_t key0 = order_key(0.0f);
-    double sae = 0.0, w_est = 0.0;
+    MaeTiles at = mae_tiles(gw, n_waves, MAE_SLOTS_PER_PASS_WAVE, n_tiles, sample_mask);
+    MaeSlotSums sums = {gw, 0.0, 0.0};
     uint32_t kout = 0, tiles_since_flush = 0;
     uint32_t wave_cand = 0;  // entries this wave has appended to the list (wave-uniform; may pass the capacity)
     uint2* my_cand = reinterpret_cast<uint2*>(cand) + gw * cand_cap;  // this wave's stretch of the list
     // The 16-bit lane counters are added up over the wave before they can overflow; lane l < 16 keeps the wave's count
-    // of region l.  (Every wave adding its counts to 17 shared words at the end of the kernel cost more than the pass.)
+    // of region l.  (Every wave adding its counts to 17 words in memory at the end of the kernel cost more than the pass.)
     unsigned long long wave_cnt = 0ull;
     auto flush_counts = [&]() {
 #pragma unroll
@@ -167,18 +271,14 @@ __global__ __launch_bounds__(256, 2) void mae_pass_kernel(const uint4* __restric
     };
     uint4 G[C::NV];
     uint32_t R[C::NR];
-    // the wave's tiles in turn - all of them, or those the sampling picks (wave-uniform)
-    auto next_tile = [&](uint64_t t) {
-        while (sample_mask != 0u && t < t1 && !mae_tile_sampled(t, sample_mask)) ++t;
-        return t;
-    };
-    uint64_t t_first = next_tile(t0);
-    if (t_first < t1) tile_issue_loads<I>(w, t_first * 64 * C::NV, n_vec, lane, G);
-    for (uint64_t t = t_first, t_next; t < t1; t = t_next) {
-        t_next = next_tile(t + 1);
+    if (at.more()) tile_issue_loads<I>(w, at.t * 64 * C::NV, n_vec, lane, G);
+    if (SUMS) sums.close_until(at.slot, n_waves, lane, sae_part);
+    for (MaeTiles next; at.more(); at = next) {  // wave-uniform
+        next = at.next();
+        const uint64_t t = at.t;
         wave_lds_fence();
         tile_stage<I>(stage, lane, G);
-        if (t_next < t1) tile_issue_loads<I>(w, t_next * 64 * C::NV, n_vec, lane, G);
+        if (next.more()) tile_issue_loads<I>(w, next.t * 64 * C::NV, n_vec, lane, G);
         wave_lds_fence();
         tile_fetch<I>(stage, lane, R);
         const uint64_t seg = t * 64 + lane;
@@ -239,9 +339,8 @@ __global__ __launch_bounds__(256, 2) void mae_pass_kernel(const uint4* __restric
                     if (FIRST) {
                         // the region's keys span exactly its hi bits, of which the first pass takes the top 8 (all of
                         // them if there are fewer): sub >> lo is the digit, and every element counts
-                        const uint32_t digit = sub >> (inf[e].y & 31u);
-                        bin[e] = code[e] * 256 + digit;
-                        counts[e] = CAPTURE && (digit - ((inf[e].y >> 8) & 255u)) < (inf[e].y >> 16);
+                        bin[e] = code[e] * 256 + (sub >> (inf[e].y & 31u));
+                        counts[e] = false;
                     } else {
                         const uint32_t lo = inf[e].y & 0xffu, hi = (inf[e].y >> 8) & 0xffu, dmask = inf[e].y >> 16;
                         counts[e] = inf[e].w != 0u && (sub >> hi) == inf[e].z;
@@ -253,23 +352,12 @@ __global__ __launch_bounds__(256, 2) void mae_pass_kernel(const uint4* __restric
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
                         atomicAdd(&sh.hist[bin[e]], W);
+                        if (!SUMS) continue;
                         atomicAdd(&cntcol[(code[e] >> 1) * 64 + lane], 1u << ((code[e] & 1u) * 16u));
                         dsum += fabs((double)x[e] - __hiloint2double((int)inf[e].w, (int)inf[e].z));
                         // pin the addition here: left alone, the compiler sinks all of them below the loop and keeps
                         // every x and level alive until then (it spilled 300 registers)
                         asm volatile("" : "+v"(dsum));
-                    }
-                    if (CAPTURE && __builtin_amdgcn_ballot_w64(any) != 0) {  // about one weight in 100 is captured
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const unsigned long long who = __builtin_amdgcn_ballot_w64(counts[e]);
-                            if (who == 0ull) continue;  // wave-uniform
-                            const uint32_t pos = wave_cand + __builtin_amdgcn_mbcnt_hi(
-                                (uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
-                            if (counts[e] && pos < cand_cap)  // entry: key | region << 32 | constant << 36
-                                my_cand[pos] = make_uint2(subk[e], code[e] | m15_shifted);
-                            wave_cand += (uint32_t)__builtin_popcountll(who);
-                        }
                     }
                 } else if (__builtin_amdgcn_ballot_w64(any) != 0) {  // later passes: one weight in 256 still counts
 #pragma unroll
@@ -277,7 +365,7 @@ __global__ __launch_bounds__(256, 2) void mae_pass_kernel(const uint4* __restric
                         const unsigned long long who = __builtin_amdgcn_ballot_w64(counts[e]);
                         if (who == 0ull) continue;  // wave-uniform: three times out of four nobody's element e counts
                         if (counts[e]) atomicAdd(&sh.hist[bin[e]], W);
-                        if (cand != nullptr) {  // wave-uniform
+                        if (writes_list) {  // wave-uniform
                             const uint32_t pos = wave_cand + __builtin_amdgcn_mbcnt_hi(
                                 (uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
                             if (counts[e] && pos < cand_cap)  // entry: key | region << 32 | constant << 36
@@ -295,108 +383,424 @@ __global__ __launch_bounds__(256, 2) void mae_pass_kernel(const uint4* __restric
                 const bool counts = FIRST ? true : (inf.w != 0u && (sub >> hi) == inf.z);
                 if (counts)
                     atomicAdd(&sh.hist[cz * 256 + ((sub >> lo) & dmask)], 0ull - (unsigned long long)k_out * W);
-                if (FIRST) {
+                if (SUMS) {
                     atomicAdd(&cntcol[(cz >> 1) * 64 + lane], 0u - (k_out << ((cz & 1u) * 16u)));
                     dsum -= (double)k_out * fabs(__hiloint2double((int)inf.w, (int)inf.z));
                     kout += k_out;
                 }
             }
-            if (FIRST) {
-                sae = fma(a_sum, dsum, sae);
-                w_est = fma(a_sum, (double)(C::SEG - k_out), w_est);
+            if (SUMS) {
+                sums.sae = fma(a_sum, dsum, sums.sae);
+                sums.w_est = fma(a_sum, (double)(C::SEG - k_out), sums.w_est);
             }
         }
-        if (FIRST && ++tiles_since_flush == 65535u / C::SEG) {
+        if (SUMS) sums.close_until(next.slot, n_waves, lane, sae_part);
+        if (SUMS && ++tiles_since_flush == 65535u / C::SEG) {
             flush_counts();
             tiles_since_flush = 0;
         }
     }
-    if (FIRST) {
+    if (SUMS) {
         flush_counts();
-        // counts leave as per-wave partials [17][waves], the two floating-point sums as per-workgroup partials (added
-        // later in a fixed order)
-        unsigned long long kc = kout;
-        double s = sae, we = w_est;
+        // counts leave as one record per workgroup, [17][MAE_MAX_WGS]
+        uint32_t kc = kout;
 #pragma unroll
-        for (int mk = 32; mk >= 1; mk >>= 1) {
-            kc += (unsigned long long)__shfl_xor((long long)kc, mk, 64);
-            s += __shfl_xor(s, mk, 64);
-            we += __shfl_xor(we, mk, 64);
-        }
-        if (lane < 17) cnt_part[lane * n_waves + gw] = lane == 16 ? kc : wave_cnt;
-        __shared__ double wave_sums[WAVES_PER_WG][2];
-        if (lane == 0) {
-            wave_sums[wave][0] = s;
-            wave_sums[wave][1] = we;
-        }
+        for (int mk = 32; mk >= 1; mk >>= 1) kc += (uint32_t)__shfl_xor((int)kc, mk, 64);
+        if (lane < 17) atomicAdd(&sh.cnt[lane], lane == 16 ? (unsigned long long)kc : wave_cnt);
         __syncthreads();
-        if (tid == 0) {
-            double s0 = 0.0, s1 = 0.0;
-            for (int k = 0; k < WAVES_PER_WG; ++k) {
-                s0 += wave_sums[k][0];
-                s1 += wave_sums[k][1];
-            }
-            sae_part[2 * blockIdx.x] = s0;
-            sae_part[2 * blockIdx.x + 1] = s1;
-        }
+        if (tid < 17) cnt_part[tid * MAE_MAX_WGS + blockIdx.x] = sh.cnt[tid];
     }
-    if (cand != nullptr && lane == 0) cand_count[gw] = wave_cand;
+    if (writes_list && lane == 0) cand_count[gw] = wave_cand;
     __syncthreads();
-    // 64-bit integer atomics: exact and order-free (measured: no slower than writing per-workgroup partials)
-    for (uint32_t i = tid; i < 16 * 256; i += 256) {
+    // 64-bit integer atomics: exact and order-free.  Eight waves share a histogram: with four, twice the atomics, a step on
+    // 16.8 M weights took 97 us instead of 90.
+    for (uint32_t i = tid; i < 16 * 256; i += 64 * MAE_PASS_WAVES) {
         const unsigned long long v = sh.hist[i];
         if (v != 0ull) atomicAdd(&hist_g[i], v);
     }
 }
 
-// A pass over the list instead of the weights: every wave reads the stretch the wave of the same number wrote.  Does
-// nothing when the list ran full (*full != 0: the gated scan of the weights runs instead).
-__global__ __launch_bounds__(256) void mae_list_kernel(const unsigned long long* __restrict__ cand,
-                                                       const uint32_t* __restrict__ cand_count, uint32_t cand_cap,
-                                                       const uint32_t* __restrict__ full,
-                                                       const MaeLevelState* __restrict__ state,
-                                                       unsigned long long* __restrict__ hist_g, int unweighted) {
+// bits = 2 bits + the lane's bit of `who` (an addition with carry; all lanes active).
+__device__ __forceinline__ void shift_in(uint32_t& bits, uint64_t who) {
+    uint64_t carry;
+    asm("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(bits), "=s"(carry) : "s"(who));
+}
+// The one pass over all the weights of a large tensor.  The windows tell which elements can still be a median, so of
+// all the others only the weight in all and below the window is needed, per region; both follow from counts per block,
+// because a block's elements weigh the same.  Per weight one 32-bit LDS addition to a lane-private column (16 regions x
+// 64 lanes: no two lanes share a bank) counts the element, and in the upper half-word whether it lies below its
+// region's window; once per tile the columns are folded, with the block's weight, into binary64 registers that hold
+// whole numbers below 2^53, and every 31 tiles those go to 64-bit integers.  Elements inside the window (about one in 100)
+// are marked in a bit map per lane; after the tile the wave lists them, one lane takes each, reads its weight again, adds
+// it to the histogram of first digits and writes it to the list.  At the end what lies below and above the window joins the
+// bins beside it, so that the selection finds an ordinary first-digit histogram.
+//   What bounds it: vector instructions, 21.8 per weight (17 for the weight itself, the rest for the fold, the block constant
+// and the list), which keep the vector units busy for 83 % of the time; the LDS unit for 36 %.  855 M weights, block 64: 1043
+// to 1093 us with a histogram of all elements (a 64-bit addition to a random bin and one for the count: 42 clocks of the LDS
+// unit per 64 weights), now 655 to 680; the whole step 1240 -> 785 us.  Four waves per SIMD spill, and every reload waits for
+// the next tile's pieces: 870 us.
+template <int I, bool FAST, bool OPQ>
+__global__ __launch_bounds__(256, 3) void mae_window_kernel(const uint4* __restrict__ w, uint64_t n_seg, CodebookArgs cb,
+                                                            BinTable bt, int signed_norm, double T2,
+                                                            const MaeLevelState* __restrict__ state,
+                                                            unsigned long long* __restrict__ hist_g,
+                                                            unsigned long long* __restrict__ cnt_part,
+                                                            double* __restrict__ sae_part,
+                                                            unsigned long long* __restrict__ cand,
+                                                            uint32_t* __restrict__ cand_count, uint32_t cand_cap,
+                                                            const uint32_t* __restrict__ full, int unweighted) {
+    using C = SegCfg<I>;
     if (*full != 0u) return;
-    __shared__ uint4 info[16];
-    __shared__ unsigned long long hist[16 * 256];
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    struct Shared {  // one object, so that the table sits at LDS offset 0 (reachable by an immediate offset)
+        uint2 tab[BIN_TABLE_ENTRIES];
+        u32x4 info[16];  // per region: the level as binary64, the window's first value and the first one past it
+        uint4 key[16];   // per region: klo, lo, the digit of its first bin, that bin's place
+        unsigned long long hist[MAE_WINDOW_BINS];
+        unsigned long long mass[16], below[16], cnt[17];
+        uint32_t cols[WAVES_PER_WG * 16 * 64];
+        uint16_t tie[WAVES_PER_WG * TIE_BUF_HALFWORDS] __attribute__((aligned(16)));
+    };
+    __shared__ __attribute__((aligned(16))) Shared sh;
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    bin_table_fill(sh.tab, bt, tid, blockDim.x);
+    if (tid < 17) sh.cnt[tid] = 0ull;
     if (tid < 16) {
         const MaeLevelState s = state[tid];
-        const uint32_t hi = s.hi, lo = hi > 8 ? hi - 8 : 0;
-        info[tid] = make_uint4(lo, hi, s.prefix, (hi != 0 && s.total != 0ull && s.pad == 0u) ? 1u : 0u);
+        const uint32_t lo = s.hi > 8 ? s.hi - 8 : 0;
+        // The window as binary32 numbers, which compare -0 and +0 as equal: where an edge lies between the two zeros both
+        // belong to the window.  No window: nothing is below, nothing inside.
+        constexpr uint64_t KEY_INF = 0xff800000ull, KEY_ZERO = 0x80000000ull;
+        float first = -__builtin_inff(), past = -__builtin_inff();
+        if (s.win_len != 0u) {
+            const uint64_t k0 = s.klo + ((uint64_t)s.win_lo << lo), k1 = s.klo + ((uint64_t)(s.win_lo + s.win_len) << lo);
+            first = key_to_float((uint32_t)min(k0, KEY_INF));
+            past = k1 == KEY_ZERO ? __uint_as_float(1u) : key_to_float((uint32_t)min(k1, KEY_INF));
+        }
+        const unsigned long long lv = (unsigned long long)__double_as_longlong(cb.cb64[tid]);
+        sh.info[tid] = u32x4{(uint32_t)lv, (uint32_t)(lv >> 32), __float_as_uint(first), __float_as_uint(past)};
+        uint32_t place = 0;  // a bin for each digit of the window and for the digits next to it
+        for (uint32_t l = 0; l < tid; ++l) place += state[l].win_len + 2;
+        sh.key[tid] = make_uint4(s.klo, lo, s.win_lo - 1, place);
+        sh.mass[tid] = sh.below[tid] = 0ull;
     }
-    for (uint32_t i = tid; i < 16 * 256; i += 256) hist[i] = 0ull;
+    for (uint32_t i = tid; i < MAE_WINDOW_BINS; i += 256) sh.hist[i] = 0ull;
+    uint32_t* col = sh.cols + wave * 16 * 64;
+#pragma unroll
+    for (int l = 0; l < 16; ++l) col[l * 64 + lane] = 0u;
     __syncthreads();
+    constexpr uint32_t ONE = 1u, ONE_BELOW = 0x10001u;
+    const uint2* tab = sh.tab;
+    const uint32_t lane_off = bin_lane_offset(lane);
+    uint16_t* tie_buf = sh.tie + wave * TIE_BUF_HALFWORDS;
+    const uint64_t n_tiles = (n_seg + 63) / 64;
+    const uint64_t n_waves = (uint64_t)gridDim.x * WAVES_PER_WG;
     const uint64_t gw = (uint64_t)blockIdx.x * WAVES_PER_WG + wave;
-    const uint32_t count = cand_count[gw];  // at most cand_cap, or the list would count as full
-    const unsigned long long* mine = cand + gw * cand_cap;
-    for (uint32_t i = lane; i < count; i += 64) {
-        const unsigned long long e = mine[i];
-        const uint32_t sub = (uint32_t)e, l = (uint32_t)(e >> 32) & 15u, m15 = (uint32_t)(e >> 36) & 0x7fffu;
-        const uint4 inf = info[l];
-        if (inf.w != 0u && (sub >> inf.y) == inf.z) {
-            const float a = f16_bits_to_f32(m15);
-            const unsigned long long W =
-                (a < 65536.0f) ? (unweighted ? 1ull : (unsigned long long)((double)a * 16777216.0)) : 0ull;
-            atomicAdd(&hist[l * 256 + ((sub >> inf.x) & ((1u << (inf.y - inf.x)) - 1u))], W);
+    // fold: regions 4 p + k (k = 0 .. 3) of the blocks of lanes lane ^ c (c = 0 .. 3), as in the Lloyd pass
+    const uint32_t p4 = (lane & 3u) * 4u;
+    uint32_t* fold_col[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) fold_col[c] = col + p4 * 64 + (lane ^ (uint32_t)c);
+
+    MaeTiles tiles = mae_tiles(gw, n_waves, MAE_SLOTS_PER_WINDOW_WAVE, n_tiles, 0u);
+    MaeSlotSums sums = {gw, 0.0, 0.0};
+    double mass[4], below[4];  // in units of 2^-24 (unweighted: of one), whole numbers
+    uint32_t cnt[4], kout = 0, tiles_since_flush = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        mass[k] = below[k] = 0.0;
+        cnt[k] = 0;
+    }
+    auto flush_masses = [&]() {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            atomicAdd(&sh.mass[p4 + k], (unsigned long long)mass[k]);
+            atomicAdd(&sh.below[p4 + k], (unsigned long long)below[k]);
+            mass[k] = below[k] = 0.0;
+        }
+    };
+    uint32_t wave_cand = 0;  // entries this wave has appended to the list (wave-uniform; may pass the capacity)
+    uint2* my_cand = reinterpret_cast<uint2*>(cand) + gw * cand_cap;  // this wave's stretch of the list
+    // What a block's elements weigh: |block constant| in units of 2^-24; a constant beyond binary16 (infinite) carries no
+    // weight (unweighted: every element of a block with a finite constant weighs one).
+    auto weight_of = [&](float a) { return a < 65536.0f ? (unweighted ? 1.0 : (double)a * 16777216.0) : 0.0; };
+    // An element inside its window: to the histogram and to place `pos` of the list.
+    auto capture = [&](uint32_t raw, float m_own, bool fast, uint32_t pos) {
+        const float f = bf16_bits_to_f32(raw);
+        float x;
+        uint32_t code;
+        if (fast) {  // wave-uniform
+            x = div_fast(f, make_block_div(m_own));
+            const uint2 en = bin_lookup(tab, x, lane_off);
+            code = en.y + (x > __uint_as_float(en.x) ? 1u : 0u);
+        } else {
+            x = (m_own == 0.0f) ? 0.0f : f / m_own;
+            code = (uint32_t)assign_code_generic(x, cb);
+        }
+        const float a = fabsf(m_own);
+        const uint4 key = sh.key[code];
+        const uint32_t sub = order_key(x) - key.x;
+        atomicAdd(&sh.hist[key.w + (sub >> key.y) - key.z], (unsigned long long)weight_of(a));
+        if (pos < cand_cap)  // entry: key | region << 32 | constant << 36
+            my_cand[pos] = make_uint2(sub, code | ((f32_to_f16_bits(a) & 0x7fffu) << 4));
+    };
+
+    uint32_t R[C::NR], Rn[C::NR];
+    if (tiles.more()) {
+        const uint4* p = own_segment<I>(w, tiles.t, n_seg, lane);
+#pragma unroll
+        for (int k = 0; k < C::NV; ++k) {
+            const uint4 q = p[k];
+            R[4 * k] = q.x;
+            R[4 * k + 1] = q.y;
+            R[4 * k + 2] = q.z;
+            R[4 * k + 3] = q.w;
         }
     }
+    sums.close_until(tiles.slot, n_waves, lane, sae_part);
+    // The last tile's elements inside their windows, one per lane: their weights are sent for again (their lines were
+    // fetched a moment ago) before the next tile's pieces and used after that tile.  Loads come back in order: sent for
+    // after those pieces, each tile would wait for the next one to arrive from memory.
+    uint32_t pend_n = 0, pend_entry = 0;
+    float pend_m = 0.0f;
+    bool pend_fast = false;
+    const uint16_t* pend_w = nullptr;
+    for (MaeTiles next; tiles.more(); tiles = next) {  // wave-uniform
+        next = tiles.next();
+        const uint64_t t = tiles.t;
+        // (after the wave's last tile this requests that tile once more: cached, and never used)
+        const uint4* pn = own_segment<I>(w, next.more() ? next.t : t, n_seg, lane);
+        uint32_t pend_raw = 0;
+        if (pend_n != 0u) pend_raw = pend_w[(pend_entry >> 6) * C::SEG + (pend_entry & 63u)];
+        __builtin_amdgcn_sched_barrier(0);
+        const bool active = t * 64 + lane < n_seg;
+        uint32_t k_out = 0;
+        if (OPQ) {
+            uint32_t omap[2];
+            opq_zero_outliers<I>(R, opq_theta<I>(R, T2), omap);
+            k_out = active ? opq_count(omap) : 0u;
+        }
+        uint32_t maxabs, sign;
+        block_constant<I>(R, lane, signed_norm != 0, maxabs, sign, tie_buf);
+        const float m = bf16_bits_to_f32(maxabs | (sign << 15));
+        const float m_eff = f16_bits_to_f32(f32_to_f16_bits(m));
+        const float a = fabsf(m_eff);
+        const double a_sum = unweighted ? 1.0 : (double)a;  // what an element's |x - level| counts with in the error sum
+        const bool fast = FAST && __builtin_amdgcn_ballot_w64(!maxabs_is_ordinary(maxabs)) == 0;
+        const BlockDiv dv = make_block_div(m_eff);
+        double dsum = 0.0;
+        uint32_t inside[2] = {0, 0};  // element 32 h + i: bit 31 - i of word h
+        // Batches of four weights in a pipeline: while the regions of one batch are read, the next one's bins are; two
+        // dependent LDS reads per weight, and neither is waited for right after it is sent.
+        constexpr int B = 4;
+        auto region_work = [&](const int b0, const float (&x)[B], const uint32_t (&code)[B], u32x4 (&inf)[B])
+            __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = 0; e < B; ++e) {
+                asm volatile("" : "+v"(inf[e]));  // one read of 16 bytes (the compiler reads the level a second time)
+                const bool from_first = x[e] >= __uint_as_float(inf[e].z);
+                const uint64_t in = __builtin_amdgcn_ballot_w64(from_first) &
+                                    __builtin_amdgcn_ballot_w64(x[e] < __uint_as_float(inf[e].w));
+                atomicAdd(&col[code[e] * 64 + lane], from_first ? ONE : ONE_BELOW);
+                shift_in(inside[b0 >> 5], in);
+                dsum += fabs((double)x[e] - __hiloint2double((int)inf[e].y, (int)inf[e].x));
+                // pin the addition here: left alone, the compiler sinks all of them below the loop and keeps every x and
+                // level alive until then (it spilled 300 registers)
+                asm volatile("" : "+v"(dsum));
+            }
+        };
+        auto next_piece = [&](const int b0) __attribute__((always_inline)) {
+            if (b0 % 8 == 0) {  // (these registers of R are free after the batch: the next tile's piece moves in)
+                const uint4 q = pn[b0 / 8];
+                Rn[b0 / 2] = q.x;
+                Rn[b0 / 2 + 1] = q.y;
+                Rn[b0 / 2 + 2] = q.z;
+                Rn[b0 / 2 + 3] = q.w;
+            }
+        };
+        if (fast) {
+            float x[B], xn[B];
+            uint2 en[B];
+            auto send = [&](const int b0, float (&to)[B]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int e = 0; e < B; ++e) {
+                    to[e] = div_fast(seg_f32(R, b0 + e), dv);
+                    en[e] = bin_lookup(tab, to[e], lane_off);
+                }
+            };
+            send(0, x);
+#pragma unroll
+            for (int b0 = 0; b0 < C::SEG; b0 += B) {
+                uint32_t code[B];
+                u32x4 inf[B];
+#pragma unroll
+                for (int e = 0; e < B; ++e) {
+                    code[e] = en[e].y + (x[e] > __uint_as_float(en[e].x) ? 1u : 0u);
+                    inf[e] = sh.info[code[e]];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (b0 + B < C::SEG) send(b0 + B, xn);
+                if (b0 % 8 == 8 - B) next_piece(b0 + B - 8);
+                __builtin_amdgcn_sched_barrier(0);
+                region_work(b0, x, code, inf);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < B; ++e) x[e] = xn[e];
+            }
+        } else {
+#pragma unroll
+            for (int b0 = 0; b0 < C::SEG; b0 += B) {
+                float x[B];
+                uint32_t code[B];
+                u32x4 inf[B];
+#pragma unroll
+                for (int e = 0; e < B; ++e) {
+                    const float f = seg_f32(R, b0 + e);
+                    x[e] = (m_eff == 0.0f) ? 0.0f : f / m_eff;
+                    code[e] = (uint32_t)assign_code_generic(x[e], cb);
+                    inf[e] = sh.info[code[e]];
+                }
+                if (b0 % 8 == 8 - B) next_piece(b0 + B - 8);
+                region_work(b0, x, code, inf);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (OPQ && k_out != 0u) {  // the zeroed outliers ran through as x = +0: take them out again
+            uint32_t cz = bt.code_of_zero;
+            asm volatile("" : "+s"(cz));  // (the address here, not in a spilled register: its load would wait for the next tile)
+            const u32x4 info_z = sh.info[cz];
+            const uint32_t inc_z = 0.0f >= __uint_as_float(info_z.z) ? ONE : ONE_BELOW;
+            atomicAdd(&col[cz * 64 + lane], 0u - k_out * inc_z);
+            dsum -= (double)k_out * fabs(__hiloint2double((int)info_z.y, (int)info_z.x));
+            kout += k_out;
+        }
+        if (t * 64 + 64 > n_seg) {  // wave-uniform: the ragged last tile of the tensor
+            wave_lds_fence();
+            if (!active) {
+#pragma unroll
+                for (int l = 0; l < 16; ++l) col[l * 64 + lane] = 0u;
+                inside[0] = inside[1] = 0u;
+            }
+        }
+        if (active) {
+            sums.sae = fma(a_sum, dsum, sums.sae);
+            sums.w_est = fma(a_sum, (double)(C::SEG - k_out), sums.w_est);
+        }
+        // fold (all lanes)
+        wave_lds_fence();
+        {
+            const float aw = a < 65536.0f ? (unweighted ? 0x1p-24f : a) : 0.0f;
+            const float aq[4] = {aw, quad_xor<1>(aw), quad_xor<2>(aw), quad_xor<3>(aw)};
+            uint32_t v[16];
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[4 * c + k] = atomicExch(fold_col[c] + k * 64, 0u);  // read and clear
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double ac = (double)aq[c] * 16777216.0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t n = v[4 * c + k] & 0xffffu;
+                    mass[k] = fma(ac, (double)n, mass[k]);
+                    below[k] = fma(ac, (double)(v[4 * c + k] >> 16), below[k]);
+                    cnt[k] += n;
+                }
+            }
+        }
+        // a tile adds at most 4 blocks x 64 elements x 2^40 to a sum: 31 tiles stay below 2^53
+        if (++tiles_since_flush == 31u) {
+            flush_masses();
+            tiles_since_flush = 0;
+        }
+        if (pend_n != 0u) {  // wave-uniform
+            if (lane < pend_n) capture(pend_raw, pend_m, pend_fast, wave_cand + lane);
+            wave_cand += pend_n;
+        }
+        // List this tile's elements inside their windows, (lane, element) in order, in the tie buffer (free here).
+        uint32_t k_in = (uint32_t)__builtin_popcount(inside[0]) + (uint32_t)__builtin_popcount(inside[1]);
+        const uint32_t incl = wave_inclusive_scan_u32(k_in);
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        pend_n = min(total, 64u);
+        if (total != 0u) {  // wave-uniform
+            auto pop = [&]() {  // the first marked element
+                const uint32_t h = inside[0] != 0u ? 0u : 1u, word = h == 0u ? inside[0] : inside[1];
+                const uint32_t i = (uint32_t)__builtin_clz(word), cleared = word & ~(0x80000000u >> i);
+                if (h == 0u) inside[0] = cleared;
+                else inside[1] = cleared;
+                return 32u * h + i;
+            };
+            pend_w = reinterpret_cast<const uint16_t*>(w) + t * 64 * C::SEG;
+            pend_fast = fast;
+            // up to TIE_BUF_HALFWORDS at a time: the last 64 of them wait, the others are done with here
+            uint32_t at = incl - k_in;
+            for (uint32_t from = 0; from < total; from += TIE_BUF_HALFWORDS) {
+                while ((inside[0] | inside[1]) != 0u && at < from + TIE_BUF_HALFWORDS)
+                    tie_buf[at++ - from] = (uint16_t)(pop() | (lane << 6));
+                wave_lds_fence();
+                const uint32_t n = min(total - from, (uint32_t)TIE_BUF_HALFWORDS);
+                for (uint32_t i0 = 0; i0 < n; i0 += 64) {
+                    pend_entry = i0 + lane < n ? tie_buf[i0 + lane] : 0u;
+                    pend_m = __shfl(m_eff, (int)(pend_entry >> 6), 64);
+                    pend_n = min(n - i0, 64u);
+                    if (from + i0 + 64 < total) {
+                        if (lane < pend_n)
+                            capture(pend_w[(pend_entry >> 6) * C::SEG + (pend_entry & 63u)], pend_m, fast, wave_cand + lane);
+                        wave_cand += pend_n;
+                    }
+                }
+                wave_lds_fence();  // the buffer is read: it is filled again, or the search for the block constants uses it
+            }
+        }
+        sums.close_until(next.slot, n_waves, lane, sae_part);
+#pragma unroll
+        for (int d = 0; d < C::NR; ++d) R[d] = Rn[d];
+    }
+    if (pend_n != 0u) {
+        if (lane < pend_n)
+            capture(pend_w[(pend_entry >> 6) * C::SEG + (pend_entry & 63u)], pend_m, pend_fast, wave_cand + lane);
+        wave_cand += pend_n;
+    }
+    flush_masses();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) atomicAdd(&sh.cnt[p4 + k], (unsigned long long)cnt[k]);
+    atomicAdd(&sh.cnt[16], (unsigned long long)kout);
+    if (lane == 0) cand_count[gw] = wave_cand;
     __syncthreads();
-    for (uint32_t i = tid; i < 16 * 256; i += 256) {
-        const unsigned long long v = hist[i];
-        if (v != 0ull) atomicAdd(&hist_g[i], v);
+    if (tid < 17) cnt_part[tid * MAE_MAX_WGS + blockIdx.x] = sh.cnt[tid];
+    // what lies below the window to the bin before it, what lies above to the bin behind it: 16 lanes per region
+    const uint32_t l = tid >> 4, n_bins = state[l].win_len + 2, place = sh.key[l].w;
+    unsigned long long in = 0ull;
+    for (uint32_t i = tid & 15u; i < n_bins; i += 16) in += sh.hist[place + i];
+#pragma unroll
+    for (int mk = 8; mk >= 1; mk >>= 1) in += (unsigned long long)__shfl_xor((long long)in, mk, 64);
+    __syncthreads();
+    if ((tid & 15u) == 0u) {
+        sh.hist[place] += sh.below[l];
+        sh.hist[place + n_bins - 1] += sh.mass[l] - sh.below[l] - in;
+    }
+    __syncthreads();
+    for (uint32_t i = tid & 15u; i < n_bins; i += 16) {
+        const unsigned long long v = sh.hist[place + i];
+        const uint32_t digit = state[l].win_lo + i - 1;  // (the bins outside 0 .. 255 stay empty)
+        if (v != 0ull && digit < 256u) atomicAdd(&hist_g[l * 256 + digit], v);
     }
 }
 
-// After the sampling pass: one wave per region reads the sampled first-digit histogram, finds where the sample's
-// weighted median lies, and sets the window of first digits that the full first pass will capture: the sampled place
+// After the sampling pass (over `sampled` elements): one wave per region reads the sampled first-digit histogram, finds
+// where the sample's weighted median lies, and sets the window of first digits that the full first pass will capture: the sampled place
 // plus or minus six standard deviations of a sampled quantile (0.5 / sqrt(samples), widened by half for the unequal
 // weights), converted to digits by the share of the region's weight that the median's digit holds, at least half a
-// digit to either side.  Clears the bins.  The search state proper is left alone.
+// digit to either side.  Clears the bins.  The search state proper is left alone.  If the windows would fill more
+// than four fifths of the list's room (few values, many of them equal) or have more digits than mae_window_kernel has
+// bins, *cand_full says at once that the list cannot be used.
 __global__ __launch_bounds__(1024) void mae_predict_kernel(MaeLevelState* __restrict__ state,
                                                            unsigned long long* __restrict__ hist,
-                                                           const unsigned long long* __restrict__ cnt_part,
-                                                           uint32_t n_part, uint32_t skip_mask) {
+                                                           double sampled, uint32_t skip_mask, double list_room,
+                                                           uint32_t* __restrict__ cand_full) {
+    __shared__ double expected[16];
+    __shared__ uint32_t bins[16];
+    __shared__ double share[16];
     const uint32_t lane = threadIdx.x & 63, l = threadIdx.x >> 6;  // wave l = region l
     unsigned long long b[4], sum = 0ull;
 #pragma unroll
@@ -412,13 +816,15 @@ __global__ __launch_bounds__(1024) void mae_predict_kernel(MaeLevelState* __rest
         if (lane >= (uint32_t)d) incl += up;
     }
     const unsigned long long total = (unsigned long long)__shfl((long long)incl, 63, 64);
-    const uint32_t n_waves = n_part * WAVES_PER_WG;
-    unsigned long long samples = 0ull;
-    for (uint32_t i = lane; i < n_waves; i += 64) samples += cnt_part[l * n_waves + i];
-#pragma unroll
-    for (int mk = 32; mk >= 1; mk >>= 1) samples += (unsigned long long)__shfl_xor((long long)samples, mk, 64);
+    // the region's elements, by its share of the weight
+    if (lane == 0) share[l] = (double)total;
+    __syncthreads();
+    double all = 0.0;
+    for (int i = 0; i < 16; ++i) all += share[i];
+    const double samples = all > 0.0 ? sampled * ((double)total / all) : 0.0;
     uint32_t win_lo = 0, win_len = 0;
-    if (total != 0ull && samples != 0ull && ((skip_mask >> l) & 1u) == 0u) {  // wave-uniform
+    double captured = 0.0;  // elements of the sample inside the window
+    if (total != 0ull && ((skip_mask >> l) & 1u) == 0u) {  // wave-uniform
         const unsigned long long ballot = __builtin_amdgcn_ballot_w64(2ull * incl >= total);
         const uint32_t L = ballot ? (uint32_t)__builtin_ctzll(ballot) : 63u;
         unsigned long long c = incl - sum;  // weight below this lane's four bins
@@ -440,7 +846,7 @@ __global__ __launch_bounds__(1024) void mae_predict_kernel(MaeLevelState* __rest
         const double mass_d = (double)(unsigned long long)__shfl((long long)mass, (int)L, 64);
         const double tot = (double)total;
         const double place = (double)digit + (mass_d > 0.0 ? (0.5 * tot - below_d) / mass_d : 0.5);
-        const double sigma_q = 0.75 / sqrt((double)samples);
+        const double sigma_q = 0.75 / sqrt(samples);
         double half = mass_d > 0.0 ? 6.0 * sigma_q * tot / mass_d : 256.0;
         if (half < 0.5) half = 0.5;
         if (half > 256.0) half = 256.0;
@@ -448,10 +854,29 @@ __global__ __launch_bounds__(1024) void mae_predict_kernel(MaeLevelState* __rest
         const int lo_i = lo_d < 0.0 ? 0 : (int)lo_d, hi_i = hi_d > 255.0 ? 255 : (int)hi_d;
         win_lo = (uint32_t)lo_i;
         win_len = hi_i >= lo_i ? (uint32_t)(hi_i - lo_i + 1) : 0u;
+        double inside = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (4 * lane + k - win_lo < win_len) inside += (double)b[k];
+#pragma unroll
+        for (int mk = 32; mk >= 1; mk >>= 1) inside += __shfl_xor(inside, mk, 64);
+        captured = inside / tot * samples;
     }
     if (lane == 0) {
         state[l].win_lo = win_lo;
         state[l].win_len = win_len;
+        expected[l] = captured;
+        bins[l] = win_len + 2;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double sum_captured = 0.0;
+        uint32_t sum_bins = 0;
+        for (int i = 0; i < 16; ++i) {
+            sum_captured += expected[i];
+            sum_bins += bins[i];
+        }
+        *cand_full = sum_captured > 0.8 * list_room || sum_bins > MAE_WINDOW_BINS ? 1u : 0u;
     }
 }
 
@@ -463,16 +888,19 @@ __global__ __launch_bounds__(1024) void mae_select_kernel(MaeLevelState* __restr
                                                           unsigned long long* __restrict__ hist,
                                                           const unsigned long long* __restrict__ cnt_part,
                                                           const double* __restrict__ sae_part, uint32_t n_part,
-                                                          int first, int last, uint32_t skip_mask,
+                                                          uint32_t n_part_scan, uint32_t n_slots,
+                                                          const uint32_t* __restrict__ gate, int first, int last, uint32_t skip_mask,
                                                           const uint32_t* __restrict__ cand_count,
                                                           uint32_t cand_waves, uint32_t cand_cap,
                                                           uint32_t* __restrict__ cand_full, int check_window,
                                                           double* __restrict__ out, int unweighted) {
     const uint32_t lane = threadIdx.x & 63, l = threadIdx.x >> 6;  // wave l = region l
+    if (gate != nullptr && *gate == 0u) return;  // as for the passes: this launch follows one that did nothing
     // after the pass that wrote the list: did every wave's stretch hold its entries?  (and, below, if the list was
-    // captured by windows: does every region's digit lie inside its window?)
-    uint32_t list_bad = 0;
-    if (cand_count != nullptr)
+    // captured by windows: was the pass run at all, and does every region's digit lie inside its window?  If not, the state
+    // stays as it is: a first pass over all the weights starts the search again.)
+    uint32_t list_bad = check_window ? *cand_full : 0u;
+    if (cand_count != nullptr && list_bad == 0u)
         for (uint32_t i = threadIdx.x; i < cand_waves; i += 1024) list_bad |= cand_count[i] > cand_cap ? 1u : 0u;
     MaeLevelState s = state[l];
     unsigned long long b[4], sum = 0ull;
@@ -520,26 +948,28 @@ __global__ __launch_bounds__(1024) void mae_select_kernel(MaeLevelState* __restr
         s.hi = lo;
         if (check_window && !((digit - s.win_lo) < s.win_len)) list_bad = 1u;
     }
-    if (lane == 0) state[l] = s;
+    int any_bad = 0;
     if (cand_count != nullptr) {  // uniform
-        const int any = __syncthreads_or((int)list_bad);
-        if (threadIdx.x == 0) *cand_full = any ? 1u : 0u;
+        any_bad = __syncthreads_or((int)list_bad);
+        if (threadIdx.x == 0) *cand_full = any_bad ? 1u : 0u;
     }
+    if (lane == 0 && !(check_window && any_bad)) state[l] = s;
     if (!last) return;
     __shared__ double med[16], den[16];
     __shared__ unsigned long long cnt[17];
-    const uint32_t n_waves = n_part * WAVES_PER_WG;
+    // the records of mae_window_kernel, or of mae_pass_kernel where that did not do
+    const uint32_t n_rec = (n_part_scan != 0u && *cand_full != 0u) ? n_part_scan : n_part;
     unsigned long long k_l = 0ull, k_out = 0ull;
-    for (uint32_t i0 = lane; i0 < n_waves; i0 += 64 * 8) {  // eight independent loads in flight (integers: any order)
-        unsigned long long a[8], b[8];
+    for (uint32_t i0 = lane; i0 < n_rec; i0 += 64 * 4) {  // four independent loads in flight (integers: any order)
+        unsigned long long a[4], b[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < 4; ++u) {
             const uint32_t i = i0 + 64 * u;
-            a[u] = i < n_waves ? cnt_part[l * n_waves + i] : 0ull;
-            b[u] = (l == 15 && i < n_waves) ? cnt_part[16 * n_waves + i] : 0ull;
+            a[u] = i < n_rec ? cnt_part[l * MAE_MAX_WGS + i] : 0ull;
+            b[u] = (l == 15 && i < n_rec) ? cnt_part[16 * MAE_MAX_WGS + i] : 0ull;
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < 4; ++u) {
             k_l += a[u];
             k_out += b[u];
         }
@@ -556,22 +986,29 @@ __global__ __launch_bounds__(1024) void mae_select_kernel(MaeLevelState* __restr
         cnt[l] = k_l;
         if (l == 15) cnt[16] = k_out;
     }
-    __syncthreads();
-    // the floating-point partials in a fixed order: lane i of wave 0 adds records 8 i .. 8 i + 7, then the 64 sums in order
-    __shared__ double part_sum[64][2];
-    if (l == 0) {
+    // the slots' sums in a fixed order: thread i adds its run of them, a butterfly the lanes of a wave, thread 0 the waves
+    __shared__ double part_sum[16][2];
+    {
+        const uint32_t per = (n_slots + 1023) / 1024;
         double s0 = 0.0, s1 = 0.0;
-        for (uint32_t p = 8 * lane; p < min(8 * lane + 8, n_part); ++p) {
+        for (uint32_t p = per * threadIdx.x; p < min(per * (threadIdx.x + 1), n_slots); ++p) {
             s0 += sae_part[2 * p];
             s1 += sae_part[2 * p + 1];
         }
-        part_sum[lane][0] = s0;
-        part_sum[lane][1] = s1;
+#pragma unroll
+        for (int mk = 32; mk >= 1; mk >>= 1) {
+            s0 += __shfl_xor(s0, mk, 64);
+            s1 += __shfl_xor(s1, mk, 64);
+        }
+        if (lane == 0) {
+            part_sum[l][0] = s0;
+            part_sum[l][1] = s1;
+        }
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         double sae = 0.0, w_est = 0.0;
-        for (int i = 0; i < 64; ++i) {
+        for (int i = 0; i < 16; ++i) {
             sae += part_sum[i][0];
             w_est += part_sum[i][1];
         }

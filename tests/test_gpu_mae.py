@@ -229,6 +229,50 @@ def test_mae_one_pass_search_with_opq(block, signed, weighted, capfd, monkeypatc
     assert abs(got["sae"] - o["sae"]) <= RTOL * o["sae"]
 
 
+@pytest.mark.parametrize("case", ["zeros", "clumps", "close levels", "few values"])
+@pytest.mark.parametrize("block", [32])
+def test_mae_one_pass_search_edges(block, case, capfd, monkeypatch):
+    """The one-pass search just above the size from which it samples, ragged tail: the region around zero wanted, its
+    median among zeros of both signs (a window's edge may lie between them); tiles in which several hundred elements lie inside a
+    window (they are listed in several goes); a codebook with two levels closer than a bin of the search table; and a tensor
+    of few values, for which no list is tried.  Medians, masses and counts as the oracle's, and the error sum bit for bit
+    that of the passes over all the weights."""
+    tile = 64 * block
+    n = (16384 + 3) * tile + 3 * block
+    g = torch.Generator().manual_seed(300 + block)
+    w = torch.randn(n, generator=g)
+    cb, skip, usable = mae_cb(block, 1), codebooks.PIN_BOF4S, 1
+    if case == "zeros":
+        z = torch.randint(0, 64, (n,), generator=g)
+        w[z == 0], w[z == 1] = 0.0, -0.0
+        skip = 0xffff ^ (1 << 7)
+    elif case == "clumps":
+        tiles = w[: 64 * tile].reshape(64, 64, block)  # the first tile of 64 waves: seven blocks of nearly equal weights
+        tiles[:, 5:40:5, 0], tiles[:, 5:40:5, 1:] = 1.0, 0.34 + 0.001 * torch.rand((64, 7, block - 1), generator=g)
+    elif case == "close levels":
+        cb = cb.copy()
+        cb[10] = cb[9] + 0.004
+    else:
+        w, usable = torch.randint(-6, 7, (n,), generator=g).float(), 0
+    w = w.to(torch.bfloat16)
+    st, o = oracle.lloyd_step_mae(inputs.bits(w), block, cb, 1)
+    assert st == oracle.OK
+    monkeypatch.setenv("BOF4_MAE_TRACE", "1")
+    capfd.readouterr()
+    wd = w.to(DEV)
+    got = binding.bof4_lloyd_step_mae(wd, block, cb, 1, skip_mask=skip)
+    trace = capfd.readouterr().err
+    assert "sampling 1" in trace and f"list unusable {1 - usable}" in trace, trace
+    assert case != "zeros" or o["median"][7] == 0.0
+    wanted = np.array([not ((skip >> l) & 1) for l in range(16)])
+    assert np.array_equal(got["median"][wanted], o["median"][wanted], equal_nan=True)
+    assert np.array_equal(got["den"], o["den"]) and np.array_equal(got["cnt"], o["cnt"])
+    assert abs(got["sae"] - o["sae"]) <= RTOL * o["sae"]
+    monkeypatch.setenv("BOF4_MAE_NO_SAMPLING", "1")
+    two = binding.bof4_lloyd_step_mae(wd, block, cb, 1, skip_mask=skip)
+    assert np.array_equal(two["median"], got["median"], equal_nan=True) and two["sae"] == got["sae"]
+
+
 @pytest.mark.parametrize("block,signed", [(32, 1), (64, 0), (256, 1)])
 def test_mae_step_on_blocks_whose_constant_binary16_stores_with_fewer_bits(block, signed):
     """A block maximum below binary16's normal range loses bits when stored (1.4375 x 2^-24 becomes 2^-24): the
