@@ -347,8 +347,9 @@ size_t bof4_gemv_outlier_table_bytes(uint64_t rows, uint64_t cols, uint64_t n_ou
  *   x_dev       n_tokens x cols bfloat16 (device, 16-byte aligned), y_dev  n_tokens x rows binary32 (device)
  *   ws_dev      bof4_gemm_workspace_bytes(rows, cols, n_tokens) bytes (device, 256-byte aligned): a size that never
  *               falls as n_tokens rises, so one buffer for the most tokens serves every call with fewer.  It holds x
- *               reordered for the matrix cores and the partial results of the workgroups that share a row (for
- *               matrices with too few rows, or rows and tokens, to fill the chip).  What a call cannot do without is
+ *               reordered for the matrix cores, the partial results of the workgroups that share a row (for
+ *               matrices with too few rows, or rows and tokens, to fill the chip), and for several hundred tokens and more
+ *               the decoded matrix or, of a large one, slabs of it (2 bytes per weight, at most 256 MiB).  What a call cannot do without is
  *               4 bytes per token slot and column (token slots in 32s, columns in 64s), and for matrices with too few
  *               rows to fill the chip, up to 64 partial results of up to 128 tokens; BOF4_ERR_WORKSPACE below that.
  *               Between the two a call may take a slower kernel, whose order of additions is another

@@ -1248,6 +1248,84 @@ GemmWideSplit gemm_wide_choice(uint64_t rows, uint64_t cols, uint64_t tok_tiles,
     return 1.04 * wide.time + 1.5 < (list ? 1.1 : 1.0) * gemm_kernel_time(rows, cols, tok_tiles) ? wide : narrow;
 }
 
+// Chunks in one chain of additions.  gemm_kernel: with a list half of what a wave takes, which holds its error to that of
+// adding the entries apart where they carry half of the sums' energy (measured 0.94 to 1.04 of it over twelve shapes;
+// 0.56 to 0.75 with the entries of Student-t weights).  Additions over more workgroups were that many more roundings, in
+// binary32; in binary64 they leave room for a chunk more per two of them (per four in longer chains).
+// The 256 x 128 tile: without a list and where gemm_kernel does not split the columns, sums of eight runs as long as its
+// eight waves' lose what those lose.  Else the sums carry (without a list over a chunk more than gemm_kernel's waves take,
+// whose own sums are rounded).
+struct GemmChains {
+    uint32_t waves, list_flush, n_runs;  // gemm_kernel
+    uint32_t wide_flush;                 // gemm_wide_kernel, gemm_decoded_kernel
+    bool wide_carry;
+};
+GemmChains gemm_chains(uint64_t rows, uint64_t cols, uint64_t n_tokens, bool list) {
+    const uint32_t split = gemm_split(rows, cols, n_tokens);
+    const uint32_t chunks = (uint32_t)((cols + GEMM_CHUNK - 1) / GEMM_CHUNK), per_wg = (chunks + split - 1) / split;
+    GemmChains C;
+    C.waves = per_wg < GEMM_MAX_WAVES ? per_wg : GEMM_MAX_WAVES;
+    const uint32_t chain = (per_wg + C.waves - 1) / C.waves;  // that a wave of gemm_kernel takes, at most
+    const uint32_t half_chain = chain > 3 ? chain / 2 : 1;
+    C.list_flush = half_chain + (split - 1) / (chain > 3 ? 4 : 2);
+    C.n_runs = list && chain > C.list_flush ? 2 : 1;
+    C.wide_carry = list || split > 1;
+    C.wide_flush = list ? half_chain + (split - 1) / 4 : C.wide_carry ? 1 + chain + (split - 1) / 4 : chain;
+    return C;
+}
+
+// Where the matrix is decoded first (gemm_decode_kernel, gemm_decoded_kernel), in slabs of whole row groups of at most
+// GEMM_DECODED_BYTES: what is decoded should still be in the 256 MB cache behind the L2s when it is multiplied (0.46 ps per
+// weight to decode 180 MB, 0.9 for 300 MB and more).  By a model of its time (us; 15 shapes at 192 to 2500 tokens): it
+// takes products from about 640 tokens on with a list, 1000 without one.  The other kernel / decoded first, measured:
+//   with a list      4096 x 4096, 512 / 1000 / 2000 tokens 52 / 81 / 127 -> 49 / 71 / 102, 12288 x 4096 106 / 213 / 353 -> 90 /
+//                    161 / 252, 22016 x 4096 215 / 331 / 649 -> 180 / 261 / 482, 8192 x 28672 320 / 648 / 1305 -> 371 / 573 / 1042
+//   without a list   4096 x 4096, 512 / 1000 / 2000 tokens 45 / 67 / 103 -> 48 / 66 / 93, 12288 x 4096 86 / 174 / 286 -> 85 /
+//                    151 / 236, 22016 x 4096 172 / 273 / 522 -> 162 / 239 / 442, 8192 x 28672 297 / 569 / 1185 -> 362 / 557 / 1020
+constexpr uint64_t GEMM_DECODED_BYTES = 256ull << 20;
+struct GemmDecodedPlan {
+    uint32_t slab_tiles;        // row tiles per slab, 0: not this way
+    uint32_t split, per_split;  // workgroups along the columns, chunks each
+    double time;
+    size_t slab_bytes;
+};
+GemmDecodedPlan gemm_decoded_plan(uint64_t rows, uint64_t cols, uint64_t tok_tiles) {
+    const uint64_t tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
+    const uint64_t groups = (rows + GEMM_WIDE_WAVES * GEMM_ROWS - 1) / (GEMM_WIDE_WAVES * GEMM_ROWS);
+    const uint64_t chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK, slots = tok_groups * GEMM_WIDE_TOK_TILES * GEMM_TOKENS;
+    const uint64_t group_bytes = chunks * GEMM_WIDE_WAVES * GEMM_TILE_WORDS * 16, most = GEMM_DECODED_BYTES / group_bytes;
+    const uint64_t least_slabs = (groups + most - 1) / most;
+    GemmDecodedPlan best = {0, 0, 0, 0.0, 0};
+    for (uint64_t n_slabs = least_slabs; n_slabs <= least_slabs + 2 && n_slabs <= groups; ++n_slabs) {
+        const uint64_t slab = (groups + n_slabs - 1) / n_slabs, last = groups - (n_slabs - 1) * slab;
+        if ((n_slabs - 1) * slab >= groups) continue;
+        for (uint64_t want = 1; want <= GEMM_WIDE_MAX_SPLIT && (want == 1 || want * 8 <= chunks); ++want) {
+            const uint64_t per = (chunks + want - 1) / want, split = (chunks + per - 1) / per;
+            const uint64_t rounds = (n_slabs - 1) * ((slab * tok_groups * split + 255) / 256) + (last * tok_groups * split + 255) / 256;
+            const double time = (split > 1 ? 2.0 + (double)((2 * split + 1) * slots * rows) * 4.0 / 7e6 : 0.0) + 4.0 * (double)n_slabs +
+                                (double)rounds * (7.5 + 0.82 * (double)per) +
+                                (slab * group_bytes > (200ull << 20) ? 0.9e-6 : 0.46e-6) * (double)(rows * cols);
+            if (best.slab_tiles == 0 || time < best.time)
+                best = {(uint32_t)(slab * GEMM_WIDE_WAVES), (uint32_t)split, (uint32_t)per, time, (size_t)(slab * group_bytes)};
+        }
+    }
+    best.time += 6.0 + 0.8e-6 * (double)(tok_tiles * GEMM_TOKENS * cols);
+    return best;
+}
+// The plan where the product is decoded first, else slab_tiles = 0.
+GemmDecodedPlan gemm_decoded_choice(uint64_t rows, uint64_t cols, uint64_t tok_tiles, bool list) {
+    const GemmDecodedPlan no = {0, 0, 0, 0.0, 0};
+    const uint64_t wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS, tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
+    if (tok_groups < 2 || cols < 512 || (rows + wg_rows - 1) / wg_rows * tok_groups >= (1ull << 23)) return no;
+    const GemmWideSplit W = gemm_wide_choice(rows, cols, tok_tiles, list);
+    // (what carrying costs: 21 % of the wide kernel's time where a chain is four chunks, 11 % at eight)
+    const double flush = (double)gemm_chains(rows, cols, tok_tiles * GEMM_TOKENS, list).wide_flush;
+    const double other = W.split > 0 ? W.time * (list ? 1.0 + 0.85 / (flush < 3.0 ? 3.0 : flush) : 1.0)
+                                     : (list ? 1.1 : 1.0) * gemm_kernel_time(rows, cols, tok_tiles);
+    const GemmDecodedPlan D = gemm_decoded_plan(rows, cols, tok_tiles);
+    return 0.98 * D.time * (list ? 1.0 + 0.3 / flush : 1.0) + 1.0 < other ? D : no;
+}
+
 // Workspace of bof4_gemm: x in the order of the products, then the partial results of the workgroups that share a row.
 // gemm_kernel's lie behind `part`; the wide kernel's - all but the first part's, which goes to y - behind `wide_part`.
 // `total` is what a call cannot do without and what gemm_kernel takes; it holds room for a second copy of x that only the
@@ -1255,6 +1333,9 @@ GemmWideSplit gemm_wide_choice(uint64_t rows, uint64_t cols, uint64_t tok_tiles,
 constexpr uint32_t GEMM_MAX_TOKENS = 65536;
 struct GemmWsLayout {
     size_t xp, part, wide_part, total;
+    size_t decoded(uint64_t split, uint64_t n_tokens, uint64_t rows) const {  // behind the partial results of the 256 x 128 tile
+        return align_up(wide_part + (split - 1) * n_tokens * rows * 4, 256);
+    }
 };
 GemmWsLayout gemm_ws_layout(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     const uint64_t n_pad = (n_tokens + GEMM_TOKENS - 1) / GEMM_TOKENS * GEMM_TOKENS;
@@ -1267,16 +1348,23 @@ GemmWsLayout gemm_ws_layout(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     L.total = L.part + (split > 1 ? split * per_launch * rows * 4 : 0);
     return L;
 }
-// What bof4_gemm_workspace_bytes returns: enough for the wide kernel at this and at every smaller token count (its split
-// falls as the token groups grow in number, so the largest need is not that of the most tokens).
+// What bof4_gemm_workspace_bytes returns: enough for every kernel at this and at every smaller token count (the split falls
+// as the token groups grow in number, so the largest need is not that of the most tokens).
 size_t gemm_ws_bytes(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     size_t need = gemm_ws_layout(rows, cols, n_tokens).total;
     for (uint64_t tiles = 1; (tiles - 1) * GEMM_TOKENS < n_tokens; ++tiles) {
-        const GemmWideSplit W = gemm_wide_choice(rows, cols, tiles, true);  // (and so wherever it is without a list)
-        if (W.split == 0) continue;
         const uint64_t t = tiles * GEMM_TOKENS < n_tokens ? tiles * GEMM_TOKENS : n_tokens;  // the most tokens in them
-        const size_t bytes = gemm_ws_layout(rows, cols, t).wide_part + (uint64_t)(W.split - 1) * t * rows * 4;
-        if (bytes > need) need = bytes;
+        // (with a list the wide tile is chosen wherever it is without one; so is decoding first)
+        const GemmWideSplit W = gemm_wide_choice(rows, cols, tiles, true);
+        if (W.split > 0) {
+            const size_t bytes = gemm_ws_layout(rows, cols, t).wide_part + (uint64_t)(W.split - 1) * t * rows * 4;
+            if (bytes > need) need = bytes;
+        }
+        const GemmDecodedPlan D = gemm_decoded_choice(rows, cols, tiles, true);
+        if (D.slab_tiles > 0) {
+            const size_t bytes = gemm_ws_layout(rows, cols, t).decoded(D.split, t, rows) + D.slab_bytes;
+            if (bytes > need) need = bytes;
+        }
     }
     return need;
 }
@@ -1376,16 +1464,8 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
     const uint32_t* entries_dev = table_dev ? (const uint32_t*)((const char*)table_dev + T.entries) : nullptr;
     hipStream_t s = (hipStream_t)stream;
     const CodebookArgs cb = make_codebook_args(cb_host);
-    const uint32_t split = gemm_split(rows, cols, n_tokens);
-    const uint32_t chunks = (uint32_t)((cols + GEMM_CHUNK - 1) / GEMM_CHUNK), per_wg = (chunks + split - 1) / split;
-    const uint32_t waves = per_wg < GEMM_MAX_WAVES ? per_wg : GEMM_MAX_WAVES;
-    // Chunks in one chain of additions.  gemm_kernel: with a list half of what a wave takes, which holds its error to that of
-    // adding the entries apart where they carry half of the sums' energy (measured 0.94 to 1.04 of it over twelve shapes;
-    // 0.56 to 0.75 with the entries of Student-t weights).  Additions over more workgroups were that many more roundings, in
-    // binary32; in binary64 they leave room for a chunk more per two of them (per four in longer chains).
-    const uint32_t chain = (per_wg + waves - 1) / waves;  // that a wave of gemm_kernel takes, at most
-    const uint32_t half_chain = chain > 3 ? chain / 2 : 1, list_flush = half_chain + (split - 1) / (chain > 3 ? 4 : 2);
-    const uint32_t n_runs = n_outliers > 0 && chain > list_flush ? 2 : 1;
+    const uint32_t split = gemm_split(rows, cols, n_tokens), chunks = (uint32_t)((cols + GEMM_CHUNK - 1) / GEMM_CHUNK);
+    const GemmChains C = gemm_chains(rows, cols, n_tokens, n_outliers > 0);
     const uint32_t per_wg_tiles = gemm_row_tiles_per_wg(rows, cols, n_tokens);
     const uint32_t row_groups = (uint32_t)(gemm_row_tiles(rows) / per_wg_tiles);
     const uint32_t n_pad = (n_tokens + GEMM_TOKENS - 1) / GEMM_TOKENS * GEMM_TOKENS, tok_tiles = n_pad / GEMM_TOKENS;
@@ -1399,29 +1479,53 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
     timing_begin(s);
     const uint32_t tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
     const GemmWideSplit W = gemm_wide_choice(rows, cols, tok_tiles, n_outliers > 0);
-    // (a workspace that holds the narrow kernel's partial results only gets the narrow kernel)
+    float* wide_parts = (float*)((char*)ws_dev + L.wide_part);
+    // (a smaller workspace gets the next kernel that it has room for: down to what gemm_kernel needs)
+    const GemmDecodedPlan D = gemm_decoded_choice(rows, cols, tok_tiles, n_outliers > 0);
+    if (D.slab_tiles > 0 && ws_bytes >= L.decoded(D.split, n_tokens, rows) + D.slab_bytes) {
+        uint4* decoded = (uint4*)((char*)ws_dev + L.decoded(D.split, n_tokens, rows));
+        for (uint32_t rt0 = 0; rt0 < T.row_tiles; rt0 += D.slab_tiles) {
+            const uint32_t n_rt = T.row_tiles - rt0 < D.slab_tiles ? T.row_tiles - rt0 : D.slab_tiles;
+            const uint64_t jobs = (uint64_t)n_rt * ((chunks + GEMM_DECODE_TILES - 1) / GEMM_DECODE_TILES);
+            const uint32_t groups = (n_rt + GEMM_WIDE_WAVES - 1) / GEMM_WIDE_WAVES;
+#define BOF4_LAUNCH_DECODE(OUT_)                                                                                       \
+    hipLaunchKernelGGL((gemm_decode_kernel<OUT_>), dim3((uint32_t)((jobs + GEMM_DECODE_WAVES - 1) / GEMM_DECODE_WAVES)), \
+                       dim3(64 * GEMM_DECODE_WAVES), 0, s, (const char*)packed_dev, rt0, n_rt, chunks, cb,             \
+                       offsets_dev, entries_dev, (uint32_t)n_outliers, T.lg, T.row_tiles, decoded);
+#define BOF4_LAUNCH_DECODED(CARRY_)                                                                                    \
+    hipLaunchKernelGGL((gemm_decoded_kernel<CARRY_>), dim3(tok_groups * groups * D.split), dim3(64 * GEMM_WIDE_WAVES), \
+                       0, s, decoded, rt0 * GEMM_ROWS, n_rt, (uint32_t)rows, chunks, xp, tok_tiles, tok_groups,        \
+                       D.per_split, C.wide_flush, n_tokens, y_dev, wide_parts);
+            if (n_outliers > 0) { BOF4_LAUNCH_DECODE(true) } else { BOF4_LAUNCH_DECODE(false) }
+            if (C.wide_carry) { BOF4_LAUNCH_DECODED(true) } else { BOF4_LAUNCH_DECODED(false) }
+#undef BOF4_LAUNCH_DECODE
+#undef BOF4_LAUNCH_DECODED
+        }
+        if (D.split > 1) {
+            const uint64_t count = (uint64_t)n_tokens * rows;
+            hipLaunchKernelGGL(gemm_sum_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, s, y_dev, wide_parts,
+                               D.split - 1, count, y_dev);
+        }
+        timing_end(s);
+        HIP_TRY(hipGetLastError());
+        return BOF4_OK;
+    }
     if (W.split > 0 &&
         ws_bytes >= L.wide_part + (uint64_t)(W.split - 1) * n_tokens * rows * 4) {
         const uint32_t wide_groups = (T.row_tiles + GEMM_WIDE_WAVES - 1) / GEMM_WIDE_WAVES;
-        // Without a list and where gemm_kernel does not split the columns, sums of eight runs as long as its eight waves'
-        // lose what those lose.  Else the sums carry (without a list over a chunk more than gemm_kernel's waves take,
-        // whose own sums are rounded).
-        const bool carry = n_outliers > 0 || split > 1;
-        const uint32_t flush = n_outliers > 0 ? half_chain + (split - 1) / 4 : carry ? 1 + chain + (split - 1) / 4 : chain;
-        float* parts = (float*)((char*)ws_dev + L.wide_part);
 #define BOF4_LAUNCH_WIDE(OUT_, CARRY_)                                                                               \
     hipLaunchKernelGGL((gemm_wide_kernel<OUT_, CARRY_>), dim3(tok_groups * wide_groups * W.split),                  \
                        dim3(64 * GEMM_WIDE_WAVES), 0, s, (const char*)packed_dev, (uint32_t)rows, (uint32_t)cols,   \
                        cb, offsets_dev, entries_dev, (uint32_t)n_outliers, T.lg, T.row_tiles,                       \
-                       (uint32_t)gemm_row_tiles(rows), xp, tok_tiles, tok_groups, W.per_split, flush, n_tokens,     \
-                       y_dev, parts);
+                       (uint32_t)gemm_row_tiles(rows), xp, tok_tiles, tok_groups, W.per_split, C.wide_flush, n_tokens,     \
+                       y_dev, wide_parts);
         if (n_outliers > 0) { BOF4_LAUNCH_WIDE(true, true) }
-        else if (carry) { BOF4_LAUNCH_WIDE(false, true) }
+        else if (C.wide_carry) { BOF4_LAUNCH_WIDE(false, true) }
         else { BOF4_LAUNCH_WIDE(false, false) }
 #undef BOF4_LAUNCH_WIDE
         if (W.split > 1) {
             const uint64_t count = (uint64_t)n_tokens * rows;
-            hipLaunchKernelGGL(gemm_sum_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, s, y_dev, parts,
+            hipLaunchKernelGGL(gemm_sum_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, s, y_dev, wide_parts,
                                W.split - 1, count, y_dev);
         }
         timing_end(s);
@@ -1435,9 +1539,9 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
         float* yt = y_dev + (uint64_t)t0 * rows;
         float* dst = split > 1 ? part : yt;
 #define BOF4_LAUNCH_GEMM(R_, NT_, OUT_)                                                                           \
-    hipLaunchKernelGGL((gemm_kernel<R_, NT_, OUT_>), dim3(row_groups, split), dim3(64 * waves), 0, s,             \
+    hipLaunchKernelGGL((gemm_kernel<R_, NT_, OUT_>), dim3(row_groups, split), dim3(64 * C.waves), 0, s,           \
                        (const char*)packed_dev, (uint32_t)rows, (uint32_t)cols, cb, offsets_dev, entries_dev,     \
-                       (uint32_t)n_outliers, T.lg, T.row_tiles, xp, tile0, nt, list_flush, n_runs, dst);
+                       (uint32_t)n_outliers, T.lg, T.row_tiles, xp, tile0, nt, C.list_flush, C.n_runs, dst);
 #define BOF4_LAUNCH_GEMM_NT(R_, OUT_)                                                                             \
     if (nt_tiles == 4) { BOF4_LAUNCH_GEMM(R_, 4, OUT_) } else if (nt_tiles == 3) { BOF4_LAUNCH_GEMM(R_, 3, OUT_) } \
     else if (nt_tiles == 2) { BOF4_LAUNCH_GEMM(R_, 2, OUT_) } else { BOF4_LAUNCH_GEMM(R_, 1, OUT_) }

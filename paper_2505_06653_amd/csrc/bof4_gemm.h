@@ -723,6 +723,263 @@ __global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_wide_kernel(
     }
 }
 
+// Many more tokens: the matrix is decoded once, to bfloat16 in the order of the products' operands (gemm_decode_kernel, a
+// 4096-byte tile per 32 rows and 64 columns, list entries in place), and multiplied by gemm_decoded_kernel, which has
+// nothing to decode.  gemm_wide_kernel decodes a weight once per 128 tokens.
+// One wave per GEMM_DECODE_TILES tiles of one row tile, all of whose codes are on their way at once.  Bound by memory: 50 M
+// weights in 23 us (5.7 TB/s) where what it writes stays in the 256 MB cache behind the L2s, half of that beyond.
+constexpr uint32_t GEMM_DECODE_TILES = 4, GEMM_DECODE_WAVES = 4;
+template <bool OUTLIERS>
+__global__ __launch_bounds__(64 * GEMM_DECODE_WAVES) void gemm_decode_kernel(
+    const char* __restrict__ packed, uint32_t first_rt, uint32_t n_rt, uint32_t n_chunks, CodebookArgs cb,
+    const uint32_t* __restrict__ list_ptr, const uint32_t* __restrict__ entries, uint32_t n_out, GemmListGeometry lg,
+    uint32_t row_tiles, uint4* __restrict__ decoded) {
+    struct Shared {
+        float tab[16];
+        uint4 parked[OUTLIERS ? GEMM_DECODE_WAVES : 1][OUTLIERS ? 4 * 64 : 1];
+    };
+    __shared__ __attribute__((aligned(16))) Shared sh;
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid < 16) sh.tab[tid] = cb.lv32[tid];
+    __syncthreads();
+    const char* tab = reinterpret_cast<const char*>(sh.tab);
+    const uint32_t runs = (n_chunks + GEMM_DECODE_TILES - 1) / GEMM_DECODE_TILES;
+    const uint64_t job = (uint64_t)blockIdx.x * GEMM_DECODE_WAVES + wave;
+    if (job >= (uint64_t)n_rt * runs) return;
+    const uint32_t rt_local = (uint32_t)(job / runs), ch0 = (uint32_t)(job % runs) * GEMM_DECODE_TILES;
+    const uint32_t n = min(GEMM_DECODE_TILES, n_chunks - ch0), rt = first_rt + rt_local;
+    uint4 q[GEMM_DECODE_TILES];
+    uint16_t m[GEMM_DECODE_TILES];
+#pragma unroll
+    for (uint32_t i = 0; i < GEMM_DECODE_TILES; ++i) {
+        const char* tile = packed + ((uint64_t)rt * n_chunks + ch0 + min(i, n - 1)) * GEMM_TILE_BYTES;
+        q[i] = load_stream(reinterpret_cast<const uint4*>(tile) + lane);
+        m[i] = __builtin_nontemporal_load(reinterpret_cast<const uint16_t*>(tile + 1024) + lane);
+    }
+    uint32_t e_lo = 0, e_hi = 0, en[GEMM_DECODE_TILES], lo[GEMM_DECODE_TILES], n_en[GEMM_DECODE_TILES];
+    if (OUTLIERS) {
+        if (rt < row_tiles && lane < n)
+            gemm_list_range(list_ptr + (uint64_t)rt * lg.n_groups + ((ch0 + lane) >> lg.log2_group), n_out, lg.log2_group, e_lo, e_hi);
+#pragma unroll
+        for (uint32_t i = 0; i < GEMM_DECODE_TILES; ++i) {
+            lo[i] = (uint32_t)__builtin_amdgcn_readlane((int)e_lo, (int)i);
+            n_en[i] = (uint32_t)__builtin_amdgcn_readlane((int)e_hi, (int)i) - lo[i];
+            en[i] = lane < n_en[i] ? entries[lo[i] + lane] : 0u;
+        }
+    }
+    uint4* out = decoded + ((uint64_t)rt_local * n_chunks + ch0) * GEMM_TILE_WORDS + lane;
+#pragma unroll
+    for (uint32_t i = 0; i < GEMM_DECODE_TILES; ++i) {
+        if (i >= n) break;  // wave-uniform
+        const float msc = f16_bits_to_f32(m[i]);
+        const uint32_t w[4] = {q[i].x, q[i].y, q[i].z, q[i].w};
+        uint4 A[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t even = (w[j] << 2) & 0x3c3c3c3cu, odd = (w[j] >> 2) & 0x3c3c3c3cu;
+            const uint32_t oe[4] = {byte_of<0>(even), byte_of<1>(even), byte_of<2>(even), byte_of<3>(even)};
+            const uint32_t oo[4] = {byte_of<0>(odd), byte_of<1>(odd), byte_of<2>(odd), byte_of<3>(odd)};
+            uint32_t a[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float le = *reinterpret_cast<const float*>(tab + oe[k]);
+                const float lv = *reinterpret_cast<const float*>(tab + oo[k]);
+                a[k] = gemm_pack_bf16(msc * le, msc * lv);  // the decoder's product and rounding
+            }
+            A[j] = make_uint4(a[0], a[1], a[2], a[3]);
+        }
+        if (OUTLIERS && n_en[i] != 0u) {  // wave-uniform
+            uint4* word = sh.parked[wave] + lane;
+            uint16_t* parked = reinterpret_cast<uint16_t*>(sh.parked[wave]);
+            const uint32_t place = (ch0 + i) & ((1u << lg.log2_group) - 1u);
+            wave_lds_fence();
+#pragma unroll
+            for (int j = 0; j < 4; ++j) word[64 * j] = A[j];
+            wave_lds_fence();
+            if (lane < n_en[i] && (en[i] >> 27) == place) parked[(en[i] >> 16) & 2047u] = (uint16_t)en[i];
+            for (uint32_t k = 64u + lane; k < n_en[i]; k += 64u) {  // a tile with more entries than lanes
+                const uint32_t e = entries[lo[i] + k];
+                if ((e >> 27) == place) parked[(e >> 16) & 2047u] = (uint16_t)e;
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int j = 0; j < 4; ++j) A[j] = word[64 * j];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[i * GEMM_TILE_WORDS + 64 * j] = A[j];
+    }
+}
+
+// The product over the decoded tiles, with the tile and the steps of gemm_wide_kernel: 256 rows x 128 tokens per
+// workgroup of eight waves, one chunk of 64 columns per step, three LDS buffers, each wave bringing in one row tile of the
+// chunk after the next and its share of x, the quarter's LDS reads under way while the one before is multiplied.  The same
+// additions in the same order: where the columns are split alike, the results are gemm_wide_kernel's bit for bit.
+//   What bounds it: of a chunk's 2150 clocks the matrix cores are busy 1024, the LDS unit 912, the vector units 767 (12288 x
+// 4096, 2000 tokens, with a list, at the 1.81 GHz that the card holds meanwhile); 1.04 to 1.19 PFLOP/s, where a large product
+// of the library reaches 1.17 to 1.22.  One product per two LDS reads in the order of issue: 2 to 3 % faster than four products
+// after four reads; the waves' priority raised for the products 4 to 8 % slower; the tiles' sums carried in turns no difference.
+//   2000 tokens with a list, gemm_wide_kernel -> decoding and this: 4096 x 4096 127 -> 102 us, 12288 x 4096 353 -> 252, 22016 x
+// 4096 649 -> 482, 8192 x 28672 1305 -> 1042.
+template <bool CARRY>
+__global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_decoded_kernel(
+    const uint4* __restrict__ decoded, uint32_t first_row, uint32_t n_rt, uint32_t rows, uint32_t n_chunks,
+    const uint4* __restrict__ xp, uint32_t tok_tiles, uint32_t tok_groups, uint32_t per_split, uint32_t flush,
+    uint32_t n_tokens, float* __restrict__ y, float* __restrict__ parts) {
+    struct Shared {
+        uint4 a[3][GEMM_WIDE_WAVES][GEMM_TILE_WORDS];
+        uint4 b[3][GEMM_WIDE_TOK_TILES][GEMM_TILE_WORDS];
+    };
+    __shared__ __attribute__((aligned(16))) Shared sh;
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (as in gemm_wide_kernel: each die takes a contiguous run of tiles, token groups fastest)
+    uint32_t id = blockIdx.x;
+    {
+        const uint32_t total = gridDim.x, q = total / 8, rem = total % 8, die = id % 8;
+        id = die * q + min(die, rem) + id / 8;
+    }
+    const uint32_t row_groups = (n_rt + GEMM_WIDE_WAVES - 1) / GEMM_WIDE_WAVES;
+    const uint32_t tg = id % tok_groups, rg = (id / tok_groups) % row_groups, part = id / (tok_groups * row_groups);
+    const uint32_t ch0 = part * per_split, ch1 = min(n_chunks, ch0 + per_split), n_steps = ch1 - ch0;
+    // a row tile or token tile past the last is read from the last one and not stored
+    const uint4* my_a = decoded + (uint64_t)min(rg * GEMM_WIDE_WAVES + wave, n_rt - 1) * n_chunks * GEMM_TILE_WORDS + lane;
+    const uint4* my_x = xp + (uint64_t)min(tg * GEMM_WIDE_TOK_TILES + (wave >> 1), tok_tiles - 1) * n_chunks * GEMM_TILE_WORDS +
+                        (wave & 1) * 128 + lane;
+    struct Ahead {  // what a wave brings into LDS for one chunk
+        uint4 a0, a1, a2, a3, x0, x1;
+    };
+    auto fetch = [&](uint32_t nth) __attribute__((always_inline)) {
+        const uint64_t at = (uint64_t)min(ch0 + nth, ch1 - 1) * GEMM_TILE_WORDS;
+        const uint4 *a = my_a + at, *x = my_x + at;
+        Ahead o;
+        o.a0 = a[0];
+        o.a1 = a[64];
+        o.a2 = a[128];
+        o.a3 = a[192];
+        o.x0 = x[0];
+        o.x1 = x[64];
+        return o;
+    };
+    gemm_f32x16 acc[2][2], sum[2][2];  // [row tile][token tile]
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[r][t][i] = sum[r][t][i] = 0.0f;
+    const uint32_t wr = 2 * (wave & 3), wt = 2 * (wave >> 2);  // first row tile and token tile that the wave multiplies
+    struct Operands {
+        gemm_bf16x8 a[2], b[2];
+    };
+    auto read_operands = [&](uint32_t buf, int j) __attribute__((always_inline)) {
+        const gemm_bf16x8* a = reinterpret_cast<const gemm_bf16x8*>(sh.a[buf][wr]) + lane;
+        const gemm_bf16x8* b = reinterpret_cast<const gemm_bf16x8*>(sh.b[buf][wt]) + lane;
+        const Operands o = {{a[64 * j], a[GEMM_TILE_WORDS + 64 * j]}, {b[64 * j], b[GEMM_TILE_WORDS + 64 * j]}};
+        return o;
+    };
+    auto store_quarter = [&](const Ahead o, uint32_t buf, int j) __attribute__((always_inline)) {
+        sh.a[buf][wave][64 * j + lane] = j == 0 ? o.a0 : j == 1 ? o.a1 : j == 2 ? o.a2 : o.a3;
+        if (j >= 2) sh.b[buf][wave >> 1][(wave & 1) * 128 + 64 * (j - 2) + lane] = j == 2 ? o.x0 : o.x1;
+    };
+    uint32_t until_flush = flush;
+    // Before step s: buffer s % 3 holds chunk s and buffer (s + 1) % 3 chunk s + 1; `o` is chunk s + 2, on its way since the
+    // step before; chunk s + 3 is asked for during the step; `op` are the operands of the step's first quarter.
+    Operands op;
+    auto step = [&](uint32_t s, const uint32_t buf, const Ahead o) __attribute__((always_inline)) {
+        const uint32_t buf1 = buf == 2u ? 0u : buf + 1u, buf2 = buf == 0u ? 2u : buf - 1u;
+        const Ahead asked = fetch(s + 3);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const Operands next = read_operands(j < 3 ? buf : buf1, (j + 1) & 3);
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc[r][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.b[t], op.a[r], acc[r][t], 0, 0, 0);
+            store_quarter(o, buf2, j);
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x200, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            op = next;
+        }
+        if (--until_flush == 0u) {
+            until_flush = flush;
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        if (CARRY) {
+                            gemm_carry(sum[r][t], acc[r][t], i);
+                        } else {
+                            sum[r][t][i] += acc[r][t][i];
+                            acc[r][t][i] = 0.0f;
+                        }
+                    }
+        }
+        __syncthreads();
+        return asked;
+    };
+    Ahead o0;
+    {
+        const Ahead first = fetch(0), second = fetch(1);
+        o0 = fetch(2);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            store_quarter(first, 0, j);
+            store_quarter(second, 1, j);
+        }
+        __syncthreads();
+        op = read_operands(0, 0);
+    }
+    // Six steps to a round, so that neither the buffers' places nor the registers of what is on its way move (a copy of a
+    // register that is being loaded waits for the load).
+    uint32_t s = 0;
+    for (uint32_t rounds = n_steps / 6; rounds > 0; --rounds, s += 6) {
+        const Ahead o1 = step(s, 0, o0);
+        const Ahead o2 = step(s + 1, 1, o1);
+        const Ahead o3 = step(s + 2, 2, o2);
+        const Ahead o4 = step(s + 3, 0, o3);
+        const Ahead o5 = step(s + 4, 1, o4);
+        o0 = step(s + 5, 2, o5);
+    }
+    if (s < n_steps) {
+        const Ahead o1 = step(s, 0, o0);
+        if (s + 1 < n_steps) {
+            const Ahead o2 = step(s + 1, 1, o1);
+            if (s + 2 < n_steps) {
+                const Ahead o3 = step(s + 2, 2, o2);
+                if (s + 3 < n_steps) {
+                    const Ahead o4 = step(s + 3, 0, o3);
+                    if (s + 4 < n_steps) step(s + 4, 1, o4);
+                }
+            }
+        }
+    }
+    // the first part goes to the result itself, where gemm_sum_kernel adds the others to it
+    float* out = part == 0 ? y : parts + (uint64_t)(part - 1) * n_tokens * rows;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const uint32_t rt = rg * GEMM_WIDE_WAVES + wr + r, row = first_row + rt * GEMM_ROWS + (lane & 31);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint32_t tok0 = (tg * GEMM_WIDE_TOK_TILES + wt + t) * GEMM_TOKENS + 4 * (lane >> 5);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const uint32_t tok = tok0 + 8 * (i >> 2) + (i & 3);
+                if (rt < n_rt && row < rows && tok < n_tokens) out[(uint64_t)tok * rows + row] = sum[r][t][i] + acc[r][t][i];
+            }
+        }
+    }
+}
+
 // y = the partial results in order (count elements each): the first, which may stand in y itself, and n_more others.
 __global__ __launch_bounds__(256) void gemm_sum_kernel(const float* first, const float* __restrict__ more, uint32_t n_more,
                                                        uint64_t count, float* y) {

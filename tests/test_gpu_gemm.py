@@ -319,6 +319,48 @@ def test_gemm_wide_tile_many_steps(rows, cols, n_tokens, steps, share):
         assert worst <= (cols + 64) * U, (r0, worst / U)
 
 
+@pytest.mark.parametrize("rows,cols,n_tokens,share,split,wide_split", [
+    (4100, 4128, 2001, 0.006, 1, 2), (8001, 1056, 2500, 0.0, 1, 1), (28700, 512, 1900, 0.04, 1, 1),
+    (33000, 4160, 1000, 0.002, 1, 1), (4099, 8224, 900, 0.006, 3, 3), (500, 28672, 400, 0.01, 16, 16)])
+def test_gemm_decoded_first(rows, cols, n_tokens, share, split, wide_split):
+    """Products large enough for the matrix to be decoded first: ragged row tiles, row groups and token groups, half chunks,
+    step counts of every remainder in the loop, tiles with more than 64 entries and with none, two slabs, columns split over
+    workgroups.  Against binary64 on the GPU with the bound of every product here; and where both split the columns alike,
+    bit for bit what the 256 x 128 tile makes of the codes, which a workspace without room for the decoded matrix gets."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + cols)
+    block, n = 32, rows * cols
+    codes = torch.randint(0, 256, (n // 2,), generator=g, device=DEV, dtype=torch.uint8)
+    scales = (torch.rand(n // block, generator=g, device=DEV) * 0.1 + 0.05).to(torch.float16)
+    cb = cb_for(block, 1) + 0.004
+    oi = ov = tab = None
+    k = int(n * share)
+    if k:
+        oi = torch.unique(torch.randint(0, n // 2, (k,), generator=g, device=DEV))  # (none in the lower half of the rows)
+        k = oi.numel()
+        ov = torch.randn(k, generator=g, device=DEV).to(torch.float16)
+        tab = binding.bof4_gemm_outlier_table(codes, scales, rows, cols, block, cb, oi, ov)
+    packed = binding.bof4_gemm_pack(codes, scales, rows, cols, block)
+    x = torch.randn((n_tokens, cols), generator=g, device=DEV).to(torch.bfloat16)
+    need = binding.bof4_gemm_workspace_bytes(rows, cols, n_tokens)
+    chunks, n_pad = (cols + 63) // 64, (n_tokens + 31) // 32 * 32
+    parts = n_pad * chunks * 128 + (split - 1) * n_tokens * rows * 4  # x in product order, partial results
+    assert need > parts + min(n * 2, 120 << 20)  # room for the decoded matrix, or a slab of it
+    ws = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device=DEV)
+    out = torch.full((n_tokens + 2, rows), float("nan"), device=DEV)
+    y = binding.bof4_gemm(packed, rows, cols, cb, x, tab, k, out=out[1:-1], ws=ws[:need])
+    assert bool((ws[need:] == 0xFF).all()) and bool(out[0].isnan().all()) and bool(out[-1].isnan().all())
+    assert torch.equal(binding.bof4_gemm(packed, rows, cols, cb, x, tab, k), y)
+    y_wide = binding.bof4_gemm(packed, rows, cols, cb, x, tab, k, ws=ws[: need - min(n // 2, 60 << 20)])
+    assert torch.equal(y_wide, y) == (split == wide_split)
+    w = binding.bof4_dequantize(codes, scales, n, block, cb, oi, ov).reshape(rows, cols)
+    for r0 in range(0, rows, 8192):
+        wd = w[r0: r0 + 8192].double()
+        ref, mag = x.double() @ wd.T, x.double().abs() @ wd.abs().T
+        worst = float(((y[:, r0: r0 + 8192].double() - ref).abs() / mag).max())
+        assert worst <= (cols + 64) * U, (r0, worst / U)
+
+
 @pytest.mark.parametrize("rows,cols,n_tokens", [(300, 2304, 330), (520, 512, 600)])
 def test_gemm_wide_tile_is_exact_where_every_partial_sum_is_a_binary32_number(rows, cols, n_tokens):
     """As for the other kernel: levels k / 8, constants 2^e, x small integers, list values multiples of 1 / 8, so that no
