@@ -1092,7 +1092,7 @@ uint64_t gemv_resident_workgroups(int variant, uint32_t threads, size_t lds) {
         size_t lds;
         uint64_t slots;
     };
-    static thread_local Key cache[8] = {};
+    static thread_local Key cache[16] = {};
     static thread_local int next = 0;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
@@ -1104,13 +1104,17 @@ uint64_t gemv_resident_workgroups(int variant, uint32_t threads, size_t lds) {
         case 0: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gemv_kernel<1, false>, (int)threads, lds); break;
         case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gemv_kernel<1, true>, (int)threads, lds); break;
         case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gemv_kernel<2, false>, (int)threads, lds); break;
-        default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gemv_kernel<2, true>, (int)threads, lds); break;
+        case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gemv_kernel<2, true>, (int)threads, lds); break;
+        case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gemv_kernel<3, false>, (int)threads, lds); break;
+        case 5: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gemv_kernel<3, true>, (int)threads, lds); break;
+        case 6: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gemv_kernel<4, false>, (int)threads, lds); break;
+        default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gemv_kernel<4, true>, (int)threads, lds); break;
     }
     if (e != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return 0;
     if (per_cu < 1) per_cu = 1;
     Key& slot = cache[next];
-    next = (next + 1) % 8;
+    next = (next + 1) % 16;
     slot = Key{dev, variant, threads, lds, (uint64_t)per_cu * (uint64_t)cus};
     return slot.slots;
 }
@@ -1589,8 +1593,14 @@ int bof4_gemv(const uint8_t* codes_dev, const uint16_t* scales_dev, uint64_t row
     const uint4* codes = (const uint4*)codes_dev;
     const uint16_t* x = (const uint16_t*)x_dev;
     timing_begin(s);
-    for (uint32_t t0 = 0; t0 < n_tokens; t0 += GEMV_MAX_TOKENS) {
-        const uint32_t nt = n_tokens - t0 < GEMV_MAX_TOKENS ? n_tokens - t0 : GEMV_MAX_TOKENS;
+    for (uint32_t t0 = 0, nt; t0 < n_tokens; t0 += nt) {
+        // Three or four tokens in one launch look a weight up once instead of twice and save a launch, at three and two waves
+        // per SIMD instead of four: 1001 x 1536, 3 tokens 9.6 -> 6.6 us, 4096 x 4096 13.7 -> 8.6, 22016 x 4096 30.5 -> 23.5 (4:
+        // 34.4 -> 33.4); with a list 11.7 -> 7.1, 16.6 -> 10.0, 40.5 -> 31.6.  Not where it is slower: 4096 x 11008, 3 tokens
+        // 22.6 -> 23.2, with a list 27.0 -> 28.2; 28672 x 8192, 4 tokens 76.3 -> 77.6 (with a list 95.3 -> 91.6).
+        nt = n_tokens - t0 < GEMV_MAX_TOKENS ? n_tokens - t0 : GEMV_MAX_TOKENS;
+        if (nt == 3 && strips > 4 && rows * cols > (1ull << 25)) nt = 2;
+        if (nt == 4 && n_outliers == 0 && rows * cols >= (1ull << 27)) nt = 2;
         const uint16_t* xt = x + (uint64_t)t0 * cols;
         float* yt = y_dev + (uint64_t)t0 * rows;
         // with a list every wave keeps its slice of x in LDS as well
@@ -1598,7 +1608,7 @@ int bof4_gemv(const uint8_t* codes_dev, const uint16_t* scales_dev, uint64_t row
         const size_t lds = n_outliers > 0 ? (size_t)waves * GEMV_STRIP * 2 * nt : 0;
         // Rows per workgroup: every workgroup pays for its slice of x, the level table and two barriers, so the
         // rows are dealt out evenly over as many workgroups as the chip holds at once - one round, no tail.
-        const int variant = (nt == 1 ? 0 : 2) + (n_outliers > 0 ? 1 : 0);
+        const int variant = 2 * (int)(nt - 1) + (n_outliers > 0 ? 1 : 0);
         const uint64_t slots = gemv_resident_workgroups(variant, 64 * waves, lds);
         if (slots == 0) return fail(BOF4_ERR_HIP, "bof4_gemv: occupancy query failed");
         uint64_t rc64 = (rows + slots - 1) / slots;
@@ -1608,11 +1618,11 @@ int bof4_gemv(const uint8_t* codes_dev, const uint16_t* scales_dev, uint64_t row
     hipLaunchKernelGGL((gemv_kernel<T_, OUT_>), dim3(grid), dim3(64 * waves), lds, s, codes, scales_dev,          \
                        (uint32_t)rows, (uint32_t)cols, log2_block, rc, (uint32_t)strips, cb, offsets_dev,         \
                        entries_dev, (uint32_t)n_outliers, xt, yt);
-        if (n_outliers > 0) {
-            if (nt == 1) { BOF4_LAUNCH_GEMV(1, true) } else { BOF4_LAUNCH_GEMV(2, true) }
-        } else {
-            if (nt == 1) { BOF4_LAUNCH_GEMV(1, false) } else { BOF4_LAUNCH_GEMV(2, false) }
-        }
+#define BOF4_LAUNCH_GEMV_NT(OUT_)                                                                                 \
+    if (nt == 1) { BOF4_LAUNCH_GEMV(1, OUT_) } else if (nt == 2) { BOF4_LAUNCH_GEMV(2, OUT_) }                     \
+    else if (nt == 3) { BOF4_LAUNCH_GEMV(3, OUT_) } else { BOF4_LAUNCH_GEMV(4, OUT_) }
+        if (n_outliers > 0) { BOF4_LAUNCH_GEMV_NT(true) } else { BOF4_LAUNCH_GEMV_NT(false) }
+#undef BOF4_LAUNCH_GEMV_NT
 #undef BOF4_LAUNCH_GEMV
     }
     timing_end(s);

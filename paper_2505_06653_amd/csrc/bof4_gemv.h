@@ -25,7 +25,7 @@ namespace bof4 {
 
 constexpr uint32_t GEMV_STRIP = 2048;   // columns per wave
 constexpr uint32_t GEMV_MAX_RC = 64;    // rows per workgroup at most: the last step has one lane per row
-constexpr uint32_t GEMV_MAX_TOKENS = 2;    // tokens per launch: their slices of x live in registers
+constexpr uint32_t GEMV_MAX_TOKENS = 4;    // tokens per launch: their slices of x live in registers
 constexpr uint32_t GEMV_MAX_STRIPS = 16;  // up to 32768 columns
 constexpr uint32_t GEMV_MAX_WAVES = 8;    // waves per workgroup: two per SIMD, so that several workgroups pack a CU
 
@@ -95,13 +95,13 @@ __device__ __forceinline__ uint32_t byte_of(uint32_t v) {
 // One workgroup: rows [blockIdx.x * rc, ...) of the matrix; wave w takes strips w, w + waves, ... one after the other.
 // U rows are in flight per wave.
 template <int T, bool OUTLIERS>
-__global__ __launch_bounds__(64 * GEMV_MAX_WAVES, 4) void gemv_kernel(const uint4* __restrict__ codes, const uint16_t* __restrict__ scales,
+__global__ __launch_bounds__(64 * GEMV_MAX_WAVES, T <= 2 ? 4 : T == 3 ? 3 : 2) void gemv_kernel(const uint4* __restrict__ codes, const uint16_t* __restrict__ scales,
                                                     uint32_t rows, uint32_t cols, uint32_t log2_block, uint32_t rc,
                                                     uint32_t n_strips, CodebookArgs cb,
                                                     const uint32_t* __restrict__ strip_ptr,
                                                     const uint2* __restrict__ entries, uint32_t n_out,
                                                     const uint16_t* __restrict__ x, float* __restrict__ y) {
-    constexpr uint32_t U = T == 2 ? 1 : (OUTLIERS ? 2 : 4);  // measured best for each variant
+    constexpr uint32_t U = T >= 2 ? 1 : (OUTLIERS ? 2 : 4);  // measured best for each variant
     struct Shared {  // one object, so that the table sits at LDS offset 0 (reachable by an immediate offset)
         float tab[16];
         float part[GEMV_MAX_WAVES * GEMV_MAX_RC * T];
@@ -120,6 +120,30 @@ __global__ __launch_bounds__(64 * GEMV_MAX_WAVES, 4) void gemv_kernel(const uint
     // with a list, the wave also keeps its slice of x as bfloat16 in LDS, where an entry's column can be looked up
     extern __shared__ __attribute__((aligned(16))) uint16_t x_lds[];
     if (OUTLIERS) wave_lds_fence();  // the previous strip's slice has been read
+    struct Rows {  // U rows at a time: codes and block constants
+        uint4 q[U];
+        float m[U];
+    };
+    auto fetch = [&](uint32_t r) {
+        Rows g;
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t rr = min(r + u, r1 - 1);  // rows past the chunk repeat its last row and are dropped
+            const uint64_t e = (uint64_t)rr * cols + col0;
+            g.q[u] = active ? load_stream(&codes[e >> 5]) : make_uint4(0u, 0u, 0u, 0u);
+            g.m[u] = active ? f16_bits_to_f32(__builtin_nontemporal_load(&scales[e >> log2_block])) : 0.0f;
+        }
+        return g;
+    };
+    // where this strip's entries of the chunk's rows begin and end: lane j holds row r0 + j (asked for together with x:
+    // 12288 x 4096 with a list, one token 10.9 -> 10.5 us)
+    uint32_t p_lo = 0, p_hi = 0;
+    if (OUTLIERS && lane < r1 - r0) {
+        p_lo = strip_ptr[(uint64_t)(r0 + lane) * n_strips + strip];
+        p_hi = strip_ptr[(uint64_t)(r0 + lane) * n_strips + strip + 1];
+    }
+    p_lo = min(p_lo, n_out);
+    p_hi = min(p_hi, n_out);
     float xr[T][32];
 #pragma unroll
     for (int t = 0; t < T; ++t) {
@@ -137,15 +161,7 @@ __global__ __launch_bounds__(64 * GEMV_MAX_WAVES, 4) void gemv_kernel(const uint
             }
         }
     }
-    // where this strip's entries of the chunk's rows begin and end: lane j holds row r0 + j
-    uint32_t p_lo = 0, p_hi = 0;
-    if (OUTLIERS) {
-        if (lane < r1 - r0) {
-            p_lo = min(strip_ptr[(uint64_t)(r0 + lane) * n_strips + strip], n_out);
-            p_hi = min(strip_ptr[(uint64_t)(r0 + lane) * n_strips + strip + 1], n_out);
-        }
-        wave_lds_fence();
-    }
+    if (OUTLIERS) wave_lds_fence();
     // what one list entry adds: (value - decoded placeholder) * x
     auto correction = [&](uint2 e, float* c) {
         const uint32_t col = (e.x - strip * GEMV_STRIP) & (GEMV_STRIP - 1);  // inside the strip by construction
@@ -154,27 +170,23 @@ __global__ __launch_bounds__(64 * GEMV_MAX_WAVES, 4) void gemv_kernel(const uint
             c[t] = fmaf(__uint_as_float(e.y),
                         bf16_bits_to_f32(x_lds[((uint32_t)t * n_waves + wave) * GEMV_STRIP + col]), c[t]);
     };
-    struct Group {  // U rows at a time: codes, block constants, and the rows' first 64 list entries
-        uint4 q[U];
-        float m[U];
-        uint32_t pa[U], pb[U];
+    struct Entries {  // the rows' first 64 list entries
         uint2 oe[U];
     };
-    auto issue = [&](uint32_t r, Group& g) {
+    auto fetch_entries = [&](uint32_t r) {
+        Entries g;
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
-            const uint32_t rr = min(r + u, r1 - 1);  // rows past the chunk repeat its last row and are dropped
-            const uint64_t e = (uint64_t)rr * cols + col0;
-            g.q[u] = active ? load_stream(&codes[e >> 5]) : make_uint4(0u, 0u, 0u, 0u);
-            g.m[u] = active ? f16_bits_to_f32(__builtin_nontemporal_load(&scales[e >> log2_block])) : 0.0f;
             if (OUTLIERS) {
-                g.pa[u] = (uint32_t)__builtin_amdgcn_readlane((int)p_lo, (int)(rr - r0));
-                g.pb[u] = (uint32_t)__builtin_amdgcn_readlane((int)p_hi, (int)(rr - r0));
-                g.oe[u] = g.pa[u] + lane < g.pb[u] ? entries[g.pa[u] + lane] : make_uint2(0u, 0u);
+                const int j = (int)(min(r + u, r1 - 1) - r0);
+                const uint32_t pa = (uint32_t)__builtin_amdgcn_readlane((int)p_lo, j);
+                const uint32_t pb = (uint32_t)__builtin_amdgcn_readlane((int)p_hi, j);
+                g.oe[u] = pa + lane < pb ? entries[pa + lane] : make_uint2(0u, 0u);
             }
         }
+        return g;
     };
-    auto compute = [&](uint32_t r, const Group& g) {
+    auto compute = [&](uint32_t r, const Rows& g, const Entries& en) {
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
             if (r + u >= r1) break;  // wave-uniform: the chunk's last group may be short
@@ -203,7 +215,7 @@ __global__ __launch_bounds__(64 * GEMV_MAX_WAVES, 4) void gemv_kernel(const uint
 #pragma unroll
             for (int t = 0; t < T; ++t) c[t] = 0.0f;
             if (OUTLIERS) {
-                correction(g.oe[u], c);  // no entry: delta 0 (a non-finite x makes every row non-finite anyway)
+                correction(en.oe[u], c);  // no entry: delta 0 (a non-finite x makes every row non-finite anyway)
             }
 #pragma unroll
             for (int t = 0; t < T; ++t) {
@@ -218,9 +230,8 @@ __global__ __launch_bounds__(64 * GEMV_MAX_WAVES, 4) void gemv_kernel(const uint
     // No second buffer of rows in flight: it was tried (with and without a list) and the registers it takes cost more
     // occupancy than the overlap gains; other waves cover the loads.
     for (uint32_t r = r0; r < r1; r += U) {
-        Group g;
-        issue(r, g);
-        compute(r, g);
+        const Rows g = fetch(r);
+        compute(r, g, fetch_entries(r));
     }
     if (OUTLIERS) {
         // Rows with more than 64 list entries inside this strip: the loop above took the first 64 (one per lane); the

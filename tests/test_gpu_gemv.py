@@ -86,6 +86,20 @@ def test_gemv_shapes(rows, cols):
     check(cb, codes, scales, oi, ov, rows, cols, 32, rand_x(2, cols, 11))
 
 
+@pytest.mark.parametrize("opq", [0, 1])
+@pytest.mark.parametrize("n_tokens", [3, 4, 7])
+@pytest.mark.parametrize("rows,cols", [(37, 2304), (130, 6144), (9, 32768), (3700, 9248)])
+def test_gemv_three_and_four_tokens_in_one_launch(rows, cols, n_tokens, opq):
+    """One to sixteen strips (the last shape is large enough for two launches); every token's results are those of the
+    token alone, bit for bit, and the bound of every product here."""
+    cb, codes, scales, oi, ov = quantized(rows, cols, 32, 1, opq, seed=53 + rows)
+    lst = (oi, ov) if opq else (None, None)
+    x = rand_x(n_tokens, cols, 19)
+    y, _ = check(cb, codes, scales, lst[0], lst[1], rows, cols, 32, x)
+    for t in range(n_tokens):
+        assert np.array_equal(y[t], run_gpu(cb, codes, scales, lst[0], lst[1], rows, cols, 32, x[t: t + 1].contiguous())[0])
+
+
 def _random_cases(count, seed):
     rng = np.random.default_rng(seed)
     cases = []
