@@ -1252,6 +1252,16 @@ GemmWideSplit gemm_wide_choice(uint64_t rows, uint64_t cols, uint64_t tok_tiles,
     return 1.04 * wide.time + 1.5 < (list ? 1.1 : 1.0) * gemm_kernel_time(rows, cols, tok_tiles) ? wide : narrow;
 }
 
+// Where gemm_kernel reads x as it stands instead of in a copy reordered by a kernel of its own (3 us): tokens of one tile, and
+// matrices so small that the launch is what counts - a wave's load then touches a line per token and not 8 in all -, or so
+// few tokens that there are few lines.  Copy / in place: 4096 x 4096, 8 and 32 tokens 12.3 / 10.3 us (with a list 12.4 / 11.1), 500
+// x 28672 14.2 / 12.4; 8 tokens 12288 x 4096 15.1 / 13.2, 28672 x 8192 41.9 / 37.2, 8192 x 28672 45.7 / 43.2; but 32 tokens
+// 12288 x 4096 15.1 / 21.9, 8 tokens 4096 x 11008 14.6 / 15.2, with a list 12288 x 4096 17.7 / 17.3, 22016 x 4096 24.8 / 26.8.
+// (Turning whole lines into the products' order through LDS: 12288 x 4096, 8 / 32 tokens 14.7 / 16.3, 22016 x 4096 22.7 / 26.1.)
+bool gemm_x_in_place(uint64_t rows, uint64_t cols, uint64_t n_tokens, bool list) {
+    return n_tokens <= GEMM_TOKENS && (rows * cols <= (1ull << 24) || (!list && n_tokens <= 8 && rows >= 8192));
+}
+
 // Chunks in one chain of additions.  gemm_kernel: with a list half of what a wave takes, which holds its error to that of
 // adding the entries apart where they carry half of the sums' energy (measured 0.94 to 1.04 of it over twelve shapes;
 // 0.56 to 0.75 with the entries of Student-t weights).  Additions over more workgroups were that many more roundings, in
@@ -1475,14 +1485,15 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
     const uint32_t n_pad = (n_tokens + GEMM_TOKENS - 1) / GEMM_TOKENS * GEMM_TOKENS, tok_tiles = n_pad / GEMM_TOKENS;
     const uint4* xp = (const uint4*)((char*)ws_dev + L.xp);
     float* part = (float*)((char*)ws_dev + L.part);
-    {
+    const GemmWideSplit W = gemm_wide_choice(rows, cols, tok_tiles, n_outliers > 0);
+    const bool x_in_place = W.split == 0 && gemm_x_in_place(rows, cols, n_tokens, n_outliers > 0);
+    if (!x_in_place) {
         const uint64_t total = (uint64_t)tok_tiles * chunks * 256;
         hipLaunchKernelGGL(gemm_pack_x_kernel, dim3((uint32_t)((total + 255) / 256)), dim3(256), 0, s,
                            (const uint16_t*)x_dev, n_tokens, (uint32_t)cols, chunks, n_pad, (uint4*)xp);
     }
     timing_begin(s);
     const uint32_t tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
-    const GemmWideSplit W = gemm_wide_choice(rows, cols, tok_tiles, n_outliers > 0);
     float* wide_parts = (float*)((char*)ws_dev + L.wide_part);
     // (a smaller workspace gets the next kernel that it has room for: down to what gemm_kernel needs)
     const GemmDecodedPlan D = gemm_decoded_choice(rows, cols, tok_tiles, n_outliers > 0);
@@ -1542,13 +1553,14 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
         const uint32_t nt = n_tokens - t0 < nt_tiles * GEMM_TOKENS ? n_tokens - t0 : nt_tiles * GEMM_TOKENS;
         float* yt = y_dev + (uint64_t)t0 * rows;
         float* dst = split > 1 ? part : yt;
-#define BOF4_LAUNCH_GEMM(R_, NT_, OUT_)                                                                           \
-    hipLaunchKernelGGL((gemm_kernel<R_, NT_, OUT_>), dim3(row_groups, split), dim3(64 * C.waves), 0, s,           \
+#define BOF4_LAUNCH_GEMM(R_, NT_, OUT_, IN_)                                                                      \
+    hipLaunchKernelGGL((gemm_kernel<R_, NT_, OUT_, IN_>), dim3(row_groups, split), dim3(64 * C.waves), 0, s,           \
                        (const char*)packed_dev, (uint32_t)rows, (uint32_t)cols, cb, offsets_dev, entries_dev,     \
-                       (uint32_t)n_outliers, T.lg, T.row_tiles, xp, tile0, nt, C.list_flush, C.n_runs, dst);
+                       (uint32_t)n_outliers, T.lg, T.row_tiles, xp, (const uint16_t*)x_dev, tile0, nt, C.list_flush, C.n_runs, dst);
 #define BOF4_LAUNCH_GEMM_NT(R_, OUT_)                                                                             \
-    if (nt_tiles == 4) { BOF4_LAUNCH_GEMM(R_, 4, OUT_) } else if (nt_tiles == 3) { BOF4_LAUNCH_GEMM(R_, 3, OUT_) } \
-    else if (nt_tiles == 2) { BOF4_LAUNCH_GEMM(R_, 2, OUT_) } else { BOF4_LAUNCH_GEMM(R_, 1, OUT_) }
+    if (x_in_place) { BOF4_LAUNCH_GEMM(R_, 1, OUT_, true) } else if (nt_tiles == 4) { BOF4_LAUNCH_GEMM(R_, 4, OUT_, false) } \
+    else if (nt_tiles == 3) { BOF4_LAUNCH_GEMM(R_, 3, OUT_, false) }                                               \
+    else if (nt_tiles == 2) { BOF4_LAUNCH_GEMM(R_, 2, OUT_, false) } else { BOF4_LAUNCH_GEMM(R_, 1, OUT_, false) }
         if (n_outliers > 0) {
             if (per_wg_tiles == 2) { BOF4_LAUNCH_GEMM_NT(2, true) } else { BOF4_LAUNCH_GEMM_NT(1, true) }
         } else {

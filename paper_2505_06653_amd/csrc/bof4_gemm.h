@@ -219,11 +219,13 @@ __device__ __forceinline__ void gemm_carry(gemm_f32x16& sum, gemm_f32x16& acc, i
 // The packed matrix holds a multiple of GEMM_MAX_R row tiles.
 template <int R, int NT>
 constexpr bool GEMM_CARRY = R == 1 || NT == 2;
-template <int R, int NT, bool OUTLIERS>
-__global__ __launch_bounds__(64 * GEMM_MAX_WAVES) void gemm_kernel(
+template <int R, int NT, bool OUTLIERS, bool X_IN_PLACE>
+__global__ __launch_bounds__(64 * GEMM_MAX_WAVES, X_IN_PLACE ? 4 : 2) void gemm_kernel(
     const char* __restrict__ packed, uint32_t rows, uint32_t cols, CodebookArgs cb, const uint32_t* __restrict__ list_ptr,
     const uint32_t* __restrict__ entries, uint32_t n_out, GemmListGeometry lg, uint32_t row_tiles,
-    const uint4* __restrict__ xp, uint32_t tile0, uint32_t n_tokens, uint32_t flush, uint32_t n_runs, float* __restrict__ dst) {
+    const uint4* __restrict__ xp, const uint16_t* __restrict__ x, uint32_t tile0, uint32_t n_tokens, uint32_t flush,
+    uint32_t n_runs, float* __restrict__ dst) {
+    static_assert(!X_IN_PLACE || NT == 1, "one tile of tokens");
     constexpr uint32_t N_RED = R * NT > 1 && !(OUTLIERS && R * NT > 6) ? 2 : 1;  // (the largest one would spill)
     struct Shared {
         float tab[16];
@@ -253,7 +255,19 @@ __global__ __launch_bounds__(64 * GEMM_MAX_WAVES) void gemm_kernel(
         uint16_t m[R];
         uint32_t en[R], n_en[R];  // this lane's list entry of the tile, and how many entries the tile has
     };
+    // X_IN_PLACE: a single tile of tokens is read where it stands.  A lane's four words of a chunk are 64 consecutive bytes of its
+    // token's row, and what the wave reads of a row is one line.  (Lanes past the last token take the last one's and
+    // their results are not stored; columns past the width are zero.)
+    const char* x_tile = reinterpret_cast<const char*>(x);
+    const uint32_t my_x = (min(lane & 31u, n_tokens - 1) * cols + 32 * (lane >> 5)) * 2;  // 2 MB at most
     auto fetch_x = [&](Operands& o, uint32_t chunk) {
+        if constexpr (X_IN_PLACE) {
+            const bool inside = chunk * GEMM_CHUNK + 32 * (lane >> 5) < cols;
+            const uint4* p = reinterpret_cast<const uint4*>(x_tile + chunk * (GEMM_CHUNK * 2) + my_x);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o.xb[0][j] = inside ? p[j] : make_uint4(0u, 0u, 0u, 0u);
+            return;
+        }
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll

@@ -470,6 +470,18 @@ def test_gemm_a_token_that_is_not_finite_stays_on_its_own(opq):
     assert np.array_equal(y[~bad], y_clean[~bad])
 
 
+@pytest.mark.parametrize("rows,cols,n_tokens", [(70, 96, 1), (70, 2336, 5), (33, 32, 8), (300, 1056, 31), (8200, 2080, 6)])
+def test_gemm_x_read_in_place_takes_nothing_from_the_next_token(rows, cols, n_tokens):
+    """Few tokens and half a chunk at the end of every row of x: what follows there is the next token, not finite here, or
+    the end of the buffer.  (Small matrices, and one of 8192 rows and more with few tokens.)"""
+    cb, codes, scales, _, _ = quantized(rows, cols, 32, 1, 0, seed=97)
+    x = rand_x(n_tokens, cols, 17)
+    y_clean, _ = check(cb, codes, scales, None, None, rows, cols, 32, x)
+    x[1::2] = float("nan")
+    y = run_gpu(cb, codes, scales, None, None, rows, cols, 32, x)
+    assert np.array_equal(y[::2], y_clean[::2]) and np.isnan(y[1::2]).all()
+
+
 def test_gemm_unit_vectors_pick_single_decoded_weights():
     """x = a unit vector per token: the product returns one column of the decoded matrix, exactly."""
     rows, cols, block = 45, 2304, 64
