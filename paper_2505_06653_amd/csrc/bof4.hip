@@ -760,15 +760,15 @@ int bof4_quant_error(const void* w_dev, uint64_t n, uint32_t block, const double
     const uint64_t wantg = (tiles + WAVES_PER_WG - 1) / WAVES_PER_WG;
     const uint32_t sgrid = (uint32_t)(wantg < SEG_GRID ? wantg : SEG_GRID);
     timing_begin(s);
-#define BOF4_LAUNCH_ERR(II)                                                                                          \
-    if (bt.fast && opq) hipLaunchKernelGGL((seg_error_kernel<II, true, true>), dim3(sgrid), dim3(256), 0, s, w, n_seg, \
-                                           cb, bt, signed_norm, T2, partials);                                       \
-    else if (bt.fast) hipLaunchKernelGGL((seg_error_kernel<II, true, false>), dim3(sgrid), dim3(256), 0, s, w, n_seg,  \
-                                         cb, bt, signed_norm, T2, partials);                                         \
-    else if (opq) hipLaunchKernelGGL((seg_error_kernel<II, false, true>), dim3(sgrid), dim3(256), 0, s, w, n_seg, cb,  \
-                                     bt, signed_norm, T2, partials);                                                 \
-    else hipLaunchKernelGGL((seg_error_kernel<II, false, false>), dim3(sgrid), dim3(256), 0, s, w, n_seg, cb, bt,      \
-                            signed_norm, T2, partials);
+    const ErrorMode mode = !bt.fast ? ERROR_SLOW : error_differences_fit(cb) ? ERROR_FAST32 : ERROR_FAST64;
+#define BOF4_LAUNCH_ERR_AS(II, MODE_, OPQ_)                                                                          \
+    hipLaunchKernelGGL((seg_error_kernel<II, MODE_, OPQ_>), dim3(sgrid), dim3(256), 0, s, w, n_seg, cb, bt,          \
+                       signed_norm, T2, partials);
+#define BOF4_LAUNCH_ERR_MODE(II, OPQ_)                                                                               \
+    if (mode == ERROR_FAST32) { BOF4_LAUNCH_ERR_AS(II, ERROR_FAST32, OPQ_) }                                         \
+    else if (mode == ERROR_FAST64) { BOF4_LAUNCH_ERR_AS(II, ERROR_FAST64, OPQ_) }                                    \
+    else { BOF4_LAUNCH_ERR_AS(II, ERROR_SLOW, OPQ_) }
+#define BOF4_LAUNCH_ERR(II) if (opq) { BOF4_LAUNCH_ERR_MODE(II, true) } else { BOF4_LAUNCH_ERR_MODE(II, false) }
     switch (block) {
         case 32: BOF4_LAUNCH_ERR(32) break;
         case 64: BOF4_LAUNCH_ERR(64) break;
@@ -776,6 +776,8 @@ int bof4_quant_error(const void* w_dev, uint64_t n, uint32_t block, const double
         default: BOF4_LAUNCH_ERR(256) break;
     }
 #undef BOF4_LAUNCH_ERR
+#undef BOF4_LAUNCH_ERR_MODE
+#undef BOF4_LAUNCH_ERR_AS
     timing_end(s);
     double* rec_dev = partials + (uint64_t)sgrid * ERR_PART;
     double* direct = (double*)device_view_of_host(out_host);

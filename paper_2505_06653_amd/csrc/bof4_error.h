@@ -32,7 +32,27 @@ __device__ __forceinline__ void round_pair_to_bf16(float a, float b, float& ra, 
     rb = __uint_as_float(u & 0xffff0000u);
 }
 
-template <int I, bool FAST, bool OPQ>
+// How a pass takes the differences w - Q(w), which are exact in binary64.  In binary32 they round where the two numbers lie
+// more than 2^15 apart; where the codebook rules that out (error_differences_fit) ERROR_FAST32 takes them there: one
+// conversion and one maximum of two per pair of weights less.
+enum ErrorMode { ERROR_SLOW, ERROR_FAST64, ERROR_FAST32 };
+// Two bfloat16 numbers of 8 significant bits whose units lie at most 2^15 apart have an exact difference in binary32 (a zero
+// always).  A weight of a block with an ordinary constant m is x m with |x| <= 1 and its level l decodes to m l, each
+// rounded by less than a factor of 2; so it is enough that no level except zero is below 2^-13 or above 4, and that
+// the region of such a level stays 2^-13 of the largest level away from zero.
+inline bool error_differences_fit(const CodebookArgs& cb) {
+    float top = 0.0f;
+    for (int l = 0; l < 16; ++l) top = fmaxf(top, fabsf(cb.lv32[l]));
+    if (!(top <= 4.0f)) return false;
+    for (int l = 0; l < 16; ++l) {
+        if (cb.lv32[l] == 0.0f) continue;
+        const bool above = l > 0 && cb.thr[l - 1] >= top * 0x1p-13f, below = l < 15 && -cb.thr[l] >= top * 0x1p-13f;
+        if (fabsf(cb.lv32[l]) < 0x1p-13f || !(above || below)) return false;
+    }
+    return true;
+}
+
+template <int I, ErrorMode MODE, bool OPQ>
 __global__ __launch_bounds__(256, 2) void seg_error_kernel(const uint4* __restrict__ w, uint64_t n_seg, CodebookArgs cb,
                                                          BinTable bt, int signed_norm, double T2,
                                                          double* __restrict__ partials) {
@@ -61,6 +81,7 @@ __global__ __launch_bounds__(256, 2) void seg_error_kernel(const uint4* __restri
 
     double sse = 0.0, sae = 0.0;
     double mx = 0.0;
+    float mx32 = 0.0f;
     uint32_t kout = 0;
     uint4 G[C::NV];
     uint32_t R[C::NR];
@@ -88,7 +109,7 @@ __global__ __launch_bounds__(256, 2) void seg_error_kernel(const uint4* __restri
         // Placeholders that decode to something would count as errors of zeros: such waves take the loop that
         // looks at every element's outlier bit.
         const bool placeholders = OPQ && __builtin_amdgcn_ballot_w64(k_out != 0 && ph != 0.0f) != 0;
-        const bool fast = FAST && !placeholders && __builtin_amdgcn_ballot_w64(!maxabs_is_ordinary(maxabs)) == 0;
+        const bool fast = MODE != ERROR_SLOW && !placeholders && __builtin_amdgcn_ballot_w64(!maxabs_is_ordinary(maxabs)) == 0;
         if (active) {
             if (fast) {
                 const BlockDiv dv = make_block_div(m_eff);
@@ -111,14 +132,21 @@ __global__ __launch_bounds__(256, 2) void seg_error_kernel(const uint4* __restri
                     for (int e = 0; e < 8; e += 2) {
                         float q0, q1;
                         round_pair_to_bf16(q[e], q[e + 1], q0, q1);
-                        // the difference in binary64: in binary32 it rounds where the two numbers lie
-                        // more than 2^16 apart (a weight next to nothing against a level that is not zero)
-                        const double dd0 = (double)f[e] - (double)q0, dd1 = (double)f[e + 1] - (double)q1;
+                        double dd0, dd1;
+                        if (MODE == ERROR_FAST32) {
+                            const float d0 = f[e] - q0, d1 = f[e + 1] - q1;
+                            mx32 = __builtin_fmaxf(mx32, __builtin_fmaxf(fabsf(d0), fabsf(d1)));
+                            dd0 = (double)d0;
+                            dd1 = (double)d1;
+                        } else {
+                            dd0 = (double)f[e] - (double)q0;
+                            dd1 = (double)f[e + 1] - (double)q1;
+                            mx = fmax(mx, fmax(fabs(dd0), fabs(dd1)));
+                        }
                         sse = fma(dd0, dd0, sse);
                         sse = fma(dd1, dd1, sse);
                         sae += fabs(dd0);
                         sae += fabs(dd1);
-                        mx = fmax(mx, fmax(fabs(dd0), fabs(dd1)));
                     }
                 }
             } else {
@@ -155,7 +183,7 @@ __global__ __launch_bounds__(256, 2) void seg_error_kernel(const uint4* __restri
         }
     }
     // fixed-order butterfly inside the wave, then the four waves of the workgroup in wave order
-    double mxd = mx;
+    double mxd = fmax(mx, (double)mx32);
     unsigned long long kc = kout;
 #pragma unroll
     for (int mk = 32; mk >= 1; mk >>= 1) {
