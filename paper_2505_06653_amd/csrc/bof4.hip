@@ -176,7 +176,8 @@ QuantWsLayout quant_ws_layout(uint64_t n, uint64_t cap) {
     L.total = o;
     return L;
 }
-constexpr uint32_t SEG_GRID = 512;              // persistent workgroups of the MAE and error kernels (2 per CU)
+constexpr uint32_t SEG_GRID = 512;              // what the MAE step's workspace is counted in
+constexpr uint32_t ERR_GRID = 768;              // persistent workgroups of the error kernel (3 per CU)
 // persistent workgroups of a pass: as many as the 256 compute units hold at once
 constexpr uint32_t pass_grid(bool opq, bool quant, bool lloyd) {
     return 256u * (uint32_t)pass_waves_per_simd(opq, quant, lloyd);
@@ -242,7 +243,7 @@ hipError_t wait_for_flag(hipStream_t s, const uint64_t* flag_host) {
 }
 size_t lloyd_ws_bytes() { return ((size_t)PASS_GRID_MAX + 1) * LLOYD_PART * 8; }
 static_assert(pass_grid(false, true, false) <= PASS_GRID_MAX && pass_grid(false, false, true) <= PASS_GRID_MAX &&
-                  SEG_GRID <= PASS_GRID_MAX,
+                  ERR_GRID <= PASS_GRID_MAX,
               "workspace sized for fewer workgroups");
 // MAE step: histogram, search state, per-wave counts, per-workgroup floating-point partials, result record.
 // Entries of the candidate list of the MAE step, dealt out evenly to the waves of the pass kernels: n / 32 (four
@@ -744,7 +745,7 @@ int bof4_quant_error(const void* w_dev, uint64_t n, uint32_t block, const double
     if (!(opq_T >= 0.0) || !std::isfinite(opq_T)) return fail(BOF4_ERR_ARG, "bof4_quant_error: opq_T must be finite and >= 0");
     if (!aligned(w_dev, 16)) return fail(BOF4_ERR_ARG, "bof4_quant_error: misaligned weights");
     if (!ws_dev || !aligned(ws_dev, 256)) return fail(BOF4_ERR_ARG, "bof4_quant_error: workspace null or misaligned");
-    static_assert((SEG_GRID + 2) * ERR_PART <= (PASS_GRID_MAX + 1) * LLOYD_PART, "the Lloyd workspace holds the error records");
+    static_assert((ERR_GRID + 2) * ERR_PART <= (PASS_GRID_MAX + 1) * LLOYD_PART, "the Lloyd workspace holds the error records");
     if (ws_bytes < lloyd_ws_bytes()) return fail(BOF4_ERR_WORKSPACE, "bof4_quant_error: workspace too small");
     static_assert(sizeof(bof4_error_stats) == 5 * 8, "result record and bof4_error_stats must match");
     hipStream_t s = (hipStream_t)stream;
@@ -758,7 +759,7 @@ int bof4_quant_error(const void* w_dev, uint64_t n, uint32_t block, const double
     const uint4* w = (const uint4*)w_dev;
     const uint64_t tiles = (n_seg + 63) / 64;
     const uint64_t wantg = (tiles + WAVES_PER_WG - 1) / WAVES_PER_WG;
-    const uint32_t sgrid = (uint32_t)(wantg < SEG_GRID ? wantg : SEG_GRID);
+    const uint32_t sgrid = (uint32_t)(wantg < ERR_GRID ? wantg : ERR_GRID);
     timing_begin(s);
     const ErrorMode mode = !bt.fast ? ERROR_SLOW : error_differences_fit(cb) ? ERROR_FAST32 : ERROR_FAST64;
 #define BOF4_LAUNCH_ERR_AS(II, MODE_, OPQ_)                                                                          \

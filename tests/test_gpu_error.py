@@ -133,3 +133,23 @@ def test_error_against_block_size_on_gaussian_weights_as_in_the_papers_figure():
         if prev is not None:
             assert mse_s > prev[0] and mae_s > prev[1] and mse_u > prev[2] and mae_u > prev[3]
         prev = (mse_s, mae_s, mse_u, mae_u)
+
+
+@pytest.mark.parametrize("n_tiles", [1, 3073, 6150])
+@pytest.mark.parametrize("block,zero_level", [(32, True), (64, False), (256, True)])
+def test_quant_error_differences_of_numbers_far_apart(block, zero_level, n_tiles):
+    """Weights from the block's maximum down to 2^-40 of it, with a codebook whose differences are taken in binary32 and one
+    (no zero level) whose are not: the sums of the decoder's differences in binary64, to the order of additions, and the
+    largest of them exactly.  One tile, one more than there are waves, ragged."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n_tiles + block)
+    n = n_tiles * 64 * min(block, 64) - (block if n_tiles > 1 else 0)
+    w = torch.randn(n, generator=g, device=DEV) * torch.exp2(-torch.randint(0, 41, (n,), generator=g, device=DEV).float())
+    w = w.to(torch.bfloat16)
+    cb = cb_for(block, 1) if zero_level else cb_for(block, 1) + 0.013 * np.linspace(-1, 1, 16) ** 2 + 0.004
+    codes, scales, _, _, _ = binding.bof4_quantize(w, block, cb, 1)
+    d = (w.double() - binding.bof4_dequantize(codes, scales, n, block, cb).double()).abs()
+    got = binding.bof4_quant_error(w, block, cb, 1)
+    assert got["max_abs"] == float(d.max())
+    assert abs(got["sse"] - float((d * d).sum())) <= 1e-13 * got["sse"]
+    assert abs(got["sae"] - float(d.sum())) <= 1e-13 * got["sae"]
