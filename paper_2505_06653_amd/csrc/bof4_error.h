@@ -5,9 +5,9 @@
 //
 // Same front end as the quantiser (one lane, one segment): OPQ statistics, block constant, shortcut division, bin
 // table.  Instead of packing the code the lane decodes it again (16-entry LDS table of levels, one binary32 product,
-// hardware rounding to bfloat16), subtracts in binary32 (exact whenever the two numbers lie within 2^16 of each other,
-// which is every case where the difference matters) and adds the square and the magnitude up in binary64.  Nothing
-// is written but one record per workgroup: 2 bytes of HBM traffic per weight.
+// hardware rounding to bfloat16), subtracts exactly (in binary64, or in binary32 where the codebook makes that exact) and
+// adds the square and the magnitude up in binary64.  Nothing is written but one record per workgroup: 2 bytes of HBM
+// traffic per weight.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -9,7 +9,7 @@
 // per weight that follow are a dense contraction and go to the matrix cores: v_mfma_f32_32x32x16_bf16, A = 32 rows x
 // 16 columns of decoded weights, B = the same 16 columns of 32 tokens, binary32 accumulators; up to four tiles of
 // 32 tokens share one decoded A.  Codes, constants and x are read in that order from copies laid out for it (the
-// matrix once, x per call), so that every load of a wave is one run of consecutive bytes.  Lane l supplies
+// matrix once, x per call unless it is small), so that every load of a wave is one run of consecutive bytes.  Lane l supplies
 // row l % 32 of A and token l % 32 of B, eight consecutive columns each; which eight is the same for both (half
 // l / 32 of a 64-column chunk takes its columns 32 (l / 32) + 8 j .. + 7 in the j-th of four products), so a lane
 // decodes one 16-byte load of its row per chunk.
