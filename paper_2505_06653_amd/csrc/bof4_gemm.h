@@ -28,19 +28,9 @@
 #include "bof4_device.h"
 #include "bof4_segment.h"
 #include "bof4_gemv.h"
+#include "bof4_gemm_plan.h"
 
 namespace bof4 {
-
-constexpr uint32_t GEMM_ROWS = 32;    // rows per tile (M of the matrix-core product)
-constexpr uint32_t GEMM_MAX_R = 2;    // tiles of rows per workgroup: each word of x read serves up to 64 rows
-constexpr uint32_t GEMM_TOKENS = 32;  // tokens per tile (N of the matrix-core product)
-constexpr uint32_t GEMM_MAX_TILES = 4;  // token tiles per launch: the codes are decoded once per 128 tokens
-constexpr uint32_t GEMM_CHUNK = 64;   // columns per wave and step: four products of K = 16
-constexpr uint32_t GEMM_MAX_WAVES = 8;
-// Workgroups wanted before the columns are also split over workgroups: three quarters of the 256 compute units.
-// Measured: splitting further (to 256, 512 or 1024 workgroups) costs more in partial results and in the epilogue per
-// workgroup than the fuller chip gains; fewer than 192 leave too much of it idle.
-constexpr uint32_t GEMM_TARGET_WGS = 192;
 
 typedef __bf16 gemm_bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 gemm_bf16x2 __attribute__((ext_vector_type(2)));
@@ -506,9 +496,6 @@ __global__ __launch_bounds__(64 * GEMM_MAX_WAVES, X_IN_PLACE ? 4 : 2) void gemm_
 // TFLOP/s), 4096 x 4096 257 -> 100; with one 22016 x 4096 1087 -> 589, 57344 x 8192 3503 -> 2590, 4096 x 4096 305 -> 122.
 // The weights are the second operand here: accumulator i of lane l is token 8 (i / 4) + 4 (l / 32) + i % 4 and row
 // l % 32, so that a store of a wave writes two runs of 128 bytes.
-constexpr uint32_t GEMM_WIDE_WAVES = 8, GEMM_WIDE_TOK_TILES = 4;  // a row tile per wave; token tiles per workgroup
-constexpr uint32_t GEMM_WIDE_MAX_SPLIT = 16;
-constexpr uint32_t GEMM_TILE_WORDS = 4 * 64;                      // 16-byte words of one tile's bfloat16 operand
 template <bool OUTLIERS, bool CARRY>
 __global__ __launch_bounds__(64 * GEMM_WIDE_WAVES, 2) void gemm_wide_kernel(
     const char* __restrict__ packed, uint32_t rows, uint32_t cols, CodebookArgs cb, const uint32_t* __restrict__ list_ptr,
