@@ -120,7 +120,8 @@ __device__ __forceinline__ uint32_t list_lower_bound(const int64_t* __restrict__
     }
     return lo;
 }
-constexpr uint32_t GEMM_MAX_CHUNKS = GEMV_MAX_STRIPS * GEMV_STRIP / GEMM_CHUNK;  // 512: 32768 columns
+constexpr uint32_t GEMM_MAX_CHUNKS = GEMM_MAX_COLS / GEMM_CHUNK;  // 512
+static_assert(GEMM_MAX_COLS == GEMV_MAX_STRIPS * GEMV_STRIP, "both products take the same widths");
 // A grid of at most GEMM_LIST_WGS workgroups (a launch holds fewer than 2^32 lanes, a matrix up to 2^27 row tiles); 1024
 // lanes each where there are fewer row tiles than compute units, else 256.  An entry's distance from the first
 // position of its row tile is below 2^20, so rows and columns come from a 32-bit division: 500 x 28672 with 0.7 %

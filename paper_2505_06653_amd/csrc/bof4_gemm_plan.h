@@ -14,6 +14,7 @@ constexpr uint32_t GEMM_TOKENS = 32;  // tokens per tile (N of the matrix-core p
 constexpr uint32_t GEMM_MAX_TILES = 4;  // token tiles per launch: the codes are decoded once per 128 tokens
 constexpr uint32_t GEMM_CHUNK = 64;   // columns per wave and step: four products of K = 16
 constexpr uint32_t GEMM_MAX_WAVES = 8;
+constexpr uint32_t GEMM_MAX_COLS = 32768, GEMM_MAX_TOKENS = 65536;  // of a product; sizes are told for any
 // Workgroups wanted before the columns are also split over workgroups: three quarters of the 256 compute units.
 // Measured: splitting further (to 256, 512 or 1024 workgroups) costs more in partial results and in the epilogue per
 // workgroup than the fuller chip gains; fewer than 192 leave too much of it idle.
@@ -174,7 +175,7 @@ inline GemmDecodedPlan gemm_decoded_plan(uint64_t rows, uint64_t cols, uint64_t 
 inline GemmDecodedPlan gemm_decoded_choice(uint64_t rows, uint64_t cols, uint64_t tok_tiles, bool list) {
     const GemmDecodedPlan no = {0, 0, 0, 0.0, 0};
     const uint64_t wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS, tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
-    if (tok_groups < 2 || cols < 512 || (rows + wg_rows - 1) / wg_rows * tok_groups >= (1ull << 23)) return no;
+    if (tok_groups < 2 || cols < 512 || cols > GEMM_MAX_COLS || (rows + wg_rows - 1) / wg_rows * tok_groups >= (1ull << 23)) return no;
     const GemmWideSplit W = gemm_wide_choice(rows, cols, tok_tiles, list);
     // (what carrying costs: 21 % of the wide kernel's time where a chain is four chunks, 11 % at eight)
     const double flush = (double)gemm_chains(rows, cols, tok_tiles * GEMM_TOKENS, list).wide_flush;
@@ -188,7 +189,6 @@ inline GemmDecodedPlan gemm_decoded_choice(uint64_t rows, uint64_t cols, uint64_
 // gemm_kernel's lie behind `part`; the wide kernel's - all but the first part's, which goes to y - behind `wide_part`.
 // `total` is what a call cannot do without and what gemm_kernel takes; it holds room for a second copy of x that only the
 // wide kernel's partial results use (x transposed once stood there: buffers of that size are in use).
-constexpr uint32_t GEMM_MAX_TOKENS = 65536;
 struct GemmWsLayout {
     size_t xp, part, wide_part, total;
     size_t decoded(uint64_t split, uint64_t n_tokens, uint64_t rows) const {  // behind the partial results of the 256 x 128 tile

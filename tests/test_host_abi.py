@@ -3,6 +3,8 @@ argument validation behave as the header says.  No compute call is made (no GPU 
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -192,3 +194,12 @@ def test_gemm_workspace_never_shrinks_as_tokens_rise(rows, cols):
         assert size >= last, n_tokens
         assert size >= 4 * ((n_tokens + 31) // 32 * 32) * cols
         last = size
+
+
+def test_gemm_workspace_bytes_of_matrices_wider_than_a_product_takes():
+    """A size, not an abort, for any number of columns (in a process of its own: a division by zero ends it)."""
+    code = ("from paper_2505_06653_amd import binding as b\n"
+            "for cols in (32768 + 32, 1 << 19, (1 << 19) + 64, 1 << 20, 1 << 24):\n"
+            "    for n in (32, 129, 2000):\n"
+            "        assert b.bof4_gemm_workspace_bytes(70, cols, n) >= 4 * n * cols, (cols, n)\n")
+    assert subprocess.run([sys.executable, "-c", code], cwd=ROOT).returncode == 0
