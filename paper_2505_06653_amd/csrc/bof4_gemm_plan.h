@@ -3,6 +3,7 @@
 #pragma once
 #include <cstddef>
 #include <cstdint>
+#include <initializer_list>
 
 namespace bof4 {
 
@@ -206,22 +207,23 @@ inline GemmWsLayout gemm_ws_layout(uint64_t rows, uint64_t cols, uint64_t n_toke
     L.total = L.part + (split > 1 ? split * per_launch * rows * 4 : 0);
     return L;
 }
-// What bof4_gemm_workspace_bytes returns: enough for every kernel at this and at every smaller token count (the split falls
-// as the token groups grow in number, so the largest need is not that of the most tokens).
+// What bof4_gemm_workspace_bytes returns: enough for every kernel, with and without a list, at this and at every smaller token
+// count (the split falls as the token groups grow in number, so the largest need is not that of the most tokens).
 inline size_t gemm_ws_bytes(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     size_t need = gemm_ws_layout(rows, cols, n_tokens).total;
     for (uint64_t tiles = 1; (tiles - 1) * GEMM_TOKENS < n_tokens; ++tiles) {
         const uint64_t t = tiles * GEMM_TOKENS < n_tokens ? tiles * GEMM_TOKENS : n_tokens;  // the most tokens in them
-        // (with a list the wide tile is chosen wherever it is without one; so is decoding first)
-        const GemmWideSplit W = gemm_wide_choice(rows, cols, tiles, true);
-        if (W.split > 0) {
-            const size_t bytes = gemm_ws_layout(rows, cols, t).wide_part + (uint64_t)(W.split - 1) * t * rows * 4;
-            if (bytes > need) need = bytes;
-        }
-        const GemmDecodedPlan D = gemm_decoded_choice(rows, cols, tiles, true);
-        if (D.slab_tiles > 0) {
-            const size_t bytes = gemm_ws_layout(rows, cols, t).decoded(D.split, t, rows) + D.slab_bytes;
-            if (bytes > need) need = bytes;
+        for (const bool list : {true, false}) {  // (which kernel is chosen depends on it, neither way the other's superset)
+            const GemmWideSplit W = gemm_wide_choice(rows, cols, tiles, list);
+            if (W.split > 0) {
+                const size_t bytes = gemm_ws_layout(rows, cols, t).wide_part + (uint64_t)(W.split - 1) * t * rows * 4;
+                if (bytes > need) need = bytes;
+            }
+            const GemmDecodedPlan D = gemm_decoded_choice(rows, cols, tiles, list);
+            if (D.slab_tiles > 0) {
+                const size_t bytes = gemm_ws_layout(rows, cols, t).decoded(D.split, t, rows) + D.slab_bytes;
+                if (bytes > need) need = bytes;
+            }
         }
     }
     return need;

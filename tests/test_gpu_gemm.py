@@ -570,6 +570,22 @@ def test_gemm_workspace_of_more_tokens_and_of_the_least_size(rows, cols, n_max, 
     assert not torch.equal(y, y_least)  # the least size takes the other kernel
 
 
+@pytest.mark.parametrize("rows,cols,n_tokens,n_max", [(13551, 2240, 566, 2500), (31710, 1216, 581, 1400), (9496, 576, 1214, 2000)])
+def test_gemm_without_a_list_gives_the_same_bits_in_a_workspace_of_its_own_and_of_more_tokens(rows, cols, n_tokens, n_max):
+    """Products that are decoded first, or nearly, without a list and not (or elsewhere) with one."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows)
+    codes = torch.randint(0, 256, (rows * cols // 2,), generator=g, device=DEV, dtype=torch.uint8)
+    scales = (torch.rand(rows * cols // 32, generator=g, device=DEV) * 0.1 + 0.05).to(torch.float16)
+    packed = binding.bof4_gemm_pack(codes, scales, rows, cols, 32)
+    x = torch.randn((n_tokens, cols), generator=g, device=DEV).to(torch.bfloat16)
+    ys = []
+    for n in (n_tokens, n_max):
+        ws = torch.empty(binding.bof4_gemm_workspace_bytes(rows, cols, n), dtype=torch.uint8, device=DEV)
+        ys.append(binding.bof4_gemm(packed, rows, cols, cb_for(32, 1), x, ws=ws))
+    assert torch.equal(*ys)
+
+
 def test_gemm_pack_layout():
     """Per tile of 32 rows and 64 columns: 64 words of 16 bytes (row lane % 32, columns 32 (lane / 32) .. + 31), then
     64 constants; zeros past the last row and the last column."""

@@ -1,0 +1,69 @@
+"""The host's rules of bof4_gemm (which kernel takes a product, where its sums are cut, the workspace that follows), on the CPU:
+bof4_gemm_plan.h compiled with the host's compiler."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2505_06653_amd import binding
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2505_06653_amd", "csrc")
+NARROW, WIDE, DECODED = 0, 1, 2
+ANY_SIZE = (1 << 64) - 1
+
+
+class Plan(ctypes.Structure):
+    _fields_ = [(k, ctypes.c_uint32) for k in ("way", "wide_split", "decoded_split", "decoded_slab_tiles", "kernel_split",
+                                               "carry", "flush", "x_in_place")] + [("need", ctypes.c_uint64)]
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("plan") / "gemm_plan.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", so,
+                    os.path.join(HERE, "csrc", "gemm_plan.cpp")], check=True)
+    lib = ctypes.CDLL(so)
+    lib.plan.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int, ctypes.c_uint64, ctypes.POINTER(Plan)]
+    lib.plan.restype = None
+    lib.workspace_bytes.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32]
+    lib.workspace_bytes.restype = ctypes.c_uint64
+
+    def plan(rows, cols, n_tokens, listed, ws_bytes=ANY_SIZE):
+        p = Plan()
+        lib.plan(rows, cols, n_tokens, int(listed), ws_bytes, ctypes.byref(p))
+        return p
+
+    plan.workspace_bytes = lib.workspace_bytes
+    return plan
+
+
+def shapes(count, seed):
+    """Seeded shapes over the range of products that can be decoded first, every second one of 512 to 2300 columns."""
+    rng = np.random.default_rng(seed)
+    for i in range(count):
+        cols = int(np.exp(rng.uniform(np.log(512), np.log(2300 if i % 2 else 32768)))) // 32 * 32
+        yield int(np.exp(rng.uniform(np.log(300), np.log(60000)))), cols, int(np.exp(rng.uniform(np.log(100), np.log(3000))))
+
+
+NAMED = [(45826, 1152, 581), (1974, 3968, 1559), (29401, 544, 513), (9496, 576, 1214), (31710, 1216, 581), (13551, 2240, 566)]
+
+
+def test_gemm_workspace_bytes_is_enough_for_the_kernel_that_is_chosen_with_and_without_a_list(rules):
+    """Also the size for more tokens: it takes no call another way than the call's own size (the order of additions would be
+    another).  The library tells the same sizes."""
+    n_decoded = 0
+    for rows, cols, n in NAMED + list(shapes(6000, 1)):
+        own = rules.workspace_bytes(rows, cols, n)
+        for listed in (False, True):
+            best = rules(rows, cols, n, listed)
+            assert rules(rows, cols, n, listed, own).way == best.way, (rows, cols, n, listed)
+            assert rules(rows, cols, n, listed, best.need - 1).way < best.way or best.way == NARROW
+            n_decoded += best.way == DECODED
+    assert n_decoded > 1000
+    for rows, cols, n in NAMED + list(shapes(100, 2)):
+        assert binding.bof4_gemm_workspace_bytes(rows, cols, n) == rules.workspace_bytes(rows, cols, n)
+        sizes = [rules.workspace_bytes(rows, cols, m) for m in range(1, n, 13)] + [rules.workspace_bytes(rows, cols, n)]
+        assert sizes == sorted(sizes)
