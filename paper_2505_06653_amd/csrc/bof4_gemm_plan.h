@@ -79,8 +79,9 @@ inline GemmWideSplit gemm_wide_split(uint64_t rows, uint64_t cols, uint64_t tok_
     GemmWideSplit best = {1, (uint32_t)chunks, 0.0};
     for (uint64_t want = 1; want <= GEMM_WIDE_MAX_SPLIT && (want == 1 || want * 8 <= chunks); ++want) {
         const uint64_t per = (chunks + want - 1) / want, split = (chunks + per - 1) / per;
-        const double time = (double)((groups * split + 255) / 256) * (9.2 + 1.15 * (double)per) +
-                            (split > 1 ? (double)((2 * split + 1) * slots * rows) * 4.0 / 7e6 : 0.0);
+        const double sums = split > 1 ? (double)((2 * split + 1) * slots * rows) * 4.0 / 7e6 : 0.0;
+        if (want > 1 && sums >= best.time) break;  // (more in every wider split)
+        const double time = (double)((groups * split + 255) / 256) * (9.2 + 1.15 * (double)per) + sums;
         if (want == 1 || time < best.time) best = {(uint32_t)split, (uint32_t)per, time};
     }
     best.time += 3.5 + 0.8e-6 * (double)(tok_tiles * GEMM_TOKENS * cols);
@@ -161,9 +162,10 @@ inline GemmDecodedPlan gemm_decoded_plan(uint64_t rows, uint64_t cols, uint64_t 
         if ((n_slabs - 1) * slab >= groups) continue;
         for (uint64_t want = 1; want <= GEMM_WIDE_MAX_SPLIT && (want == 1 || want * 8 <= chunks); ++want) {
             const uint64_t per = (chunks + want - 1) / want, split = (chunks + per - 1) / per;
+            const double sums = split > 1 ? 2.0 + (double)((2 * split + 1) * slots * rows) * 4.0 / 7e6 : 0.0;
+            if (best.slab_tiles != 0 && sums >= best.time) break;  // (more in every wider split)
             const uint64_t rounds = (n_slabs - 1) * ((slab * tok_groups * split + 255) / 256) + (last * tok_groups * split + 255) / 256;
-            const double time = (split > 1 ? 2.0 + (double)((2 * split + 1) * slots * rows) * 4.0 / 7e6 : 0.0) + 4.0 * (double)n_slabs +
-                                (double)rounds * (7.5 + 0.82 * (double)per) +
+            const double time = sums + 4.0 * (double)n_slabs + (double)rounds * (7.5 + 0.82 * (double)per) +
                                 (slab * group_bytes > (200ull << 20) ? 0.9e-6 : 0.46e-6) * (double)(rows * cols);
             if (best.slab_tiles == 0 || time < best.time)
                 best = {(uint32_t)(slab * GEMM_WIDE_WAVES), (uint32_t)split, (uint32_t)per, time, (size_t)(slab * group_bytes)};
@@ -172,16 +174,18 @@ inline GemmDecodedPlan gemm_decoded_plan(uint64_t rows, uint64_t cols, uint64_t 
     best.time += 6.0 + 0.8e-6 * (double)(tok_tiles * GEMM_TOKENS * cols);
     return best;
 }
-// The plan where the product is decoded first, else slab_tiles = 0.
-inline GemmDecodedPlan gemm_decoded_choice(uint64_t rows, uint64_t cols, uint64_t tok_tiles, bool list) {
+// The plan where the product is decoded first, else slab_tiles = 0.  W: gemm_wide_choice's answer.
+inline GemmDecodedPlan gemm_decoded_choice(uint64_t rows, uint64_t cols, uint64_t tok_tiles, bool list, const GemmWideSplit& W) {
     const GemmDecodedPlan no = {0, 0, 0, 0.0, 0};
     const uint64_t wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS, tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
     if (tok_groups < 2 || cols < 512 || cols > GEMM_MAX_COLS || (rows + wg_rows - 1) / wg_rows * tok_groups >= (1ull << 23)) return no;
-    const GemmWideSplit W = gemm_wide_choice(rows, cols, tok_tiles, list);
     // (what carrying costs: 21 % of the wide kernel's time where a chain is four chunks, 11 % at eight)
     const double flush = (double)gemm_chains(rows, cols, tok_tiles * GEMM_TOKENS, list).wide_flush;
     const double other = W.split > 0 ? W.time * (list ? 1.0 + 0.85 / (flush < 3.0 ? 3.0 : flush) : 1.0)
                                      : (list ? 1.1 : 1.0) * gemm_kernel_time(rows, cols, tok_tiles);
+    // (every plan's least: the decoding at its best rate and the products without what a round costs to start)
+    const uint64_t chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK, groups = (rows + wg_rows - 1) / wg_rows;
+    if (0.98 * (10.0 + 0.46e-6 * (double)(rows * cols) + 0.82 / 256.0 * (double)(groups * tok_groups * chunks)) >= other) return no;
     const GemmDecodedPlan D = gemm_decoded_plan(rows, cols, tok_tiles);
     return 0.98 * D.time * (list ? 1.0 + 0.3 / flush : 1.0) + 1.0 < other ? D : no;
 }
@@ -208,21 +212,32 @@ inline GemmWsLayout gemm_ws_layout(uint64_t rows, uint64_t cols, uint64_t n_toke
     return L;
 }
 // What bof4_gemm_workspace_bytes returns: enough for every kernel, with and without a list, at this and at every smaller token
-// count (the split falls as the token groups grow in number, so the largest need is not that of the most tokens).
+// count that a product takes (the split falls as the token groups grow in number, so the largest need is not that of the most
+// tokens).  Splits and slabs are the same for all token tiles of a group, so the most tokens of a group for which a kernel is
+// chosen need the most: 8192 x 28672 at 2000 / 65536 tokens 29 us / 0.37 ms, 4096 x 4096 15 us / 0.18 ms (45 / 1500 and 30 / 1000
+// where every token tile is asked about).
 inline size_t gemm_ws_bytes(uint64_t rows, uint64_t cols, uint64_t n_tokens) {
     size_t need = gemm_ws_layout(rows, cols, n_tokens).total;
-    for (uint64_t tiles = 1; (tiles - 1) * GEMM_TOKENS < n_tokens; ++tiles) {
-        const uint64_t t = tiles * GEMM_TOKENS < n_tokens ? tiles * GEMM_TOKENS : n_tokens;  // the most tokens in them
-        for (const bool list : {true, false}) {  // (which kernel is chosen depends on it, neither way the other's superset)
-            const GemmWideSplit W = gemm_wide_choice(rows, cols, tiles, list);
-            if (W.split > 0) {
-                const size_t bytes = gemm_ws_layout(rows, cols, t).wide_part + (uint64_t)(W.split - 1) * t * rows * 4;
-                if (bytes > need) need = bytes;
-            }
-            const GemmDecodedPlan D = gemm_decoded_choice(rows, cols, tiles, list);
-            if (D.slab_tiles > 0) {
+    const uint64_t most = n_tokens < GEMM_MAX_TOKENS ? n_tokens : GEMM_MAX_TOKENS;
+    const uint64_t all_tiles = (most + GEMM_TOKENS - 1) / GEMM_TOKENS;
+    for (uint64_t below = 0; below < all_tiles; below += GEMM_WIDE_TOK_TILES) {  // the token tiles before a group
+        bool has_wide = false, has_decoded = false;
+        for (uint64_t tiles = below + GEMM_WIDE_TOK_TILES < all_tiles ? below + GEMM_WIDE_TOK_TILES : all_tiles;
+             tiles > below && !(has_wide && has_decoded); --tiles) {
+            const uint64_t t = tiles * GEMM_TOKENS < most ? tiles * GEMM_TOKENS : most;  // the most tokens in them
+            for (const bool list : {true, false}) {  // (which kernel is chosen depends on it, neither way the other's superset)
+                const GemmWideSplit W = gemm_wide_choice(rows, cols, tiles, list);
+                if (W.split > 0 && !has_wide) {
+                    const size_t bytes = gemm_ws_layout(rows, cols, t).wide_part + (uint64_t)(W.split - 1) * t * rows * 4;
+                    if (bytes > need) need = bytes;
+                    has_wide = true;
+                }
+                if (has_decoded) continue;
+                const GemmDecodedPlan D = gemm_decoded_choice(rows, cols, tiles, list, W);
+                if (D.slab_tiles == 0) continue;
                 const size_t bytes = gemm_ws_layout(rows, cols, t).decoded(D.split, t, rows) + D.slab_bytes;
                 if (bytes > need) need = bytes;
+                has_decoded = true;
             }
         }
     }
@@ -245,7 +260,7 @@ inline GemmPlan gemm_plan(uint64_t rows, uint64_t cols, uint64_t n_tokens, bool 
     GemmPlan P;
     P.ws = gemm_ws_layout(rows, cols, n_tokens);
     P.wide = gemm_wide_choice(rows, cols, tok_tiles, list);
-    P.decoded = gemm_decoded_choice(rows, cols, tok_tiles, list);
+    P.decoded = gemm_decoded_choice(rows, cols, tok_tiles, list, P.wide);
     P.chains = gemm_chains(rows, cols, n_tokens, list);
     P.x_in_place = P.wide.split == 0 && gemm_x_in_place(rows, cols, n_tokens, list);
     P.way = GEMM_NARROW;

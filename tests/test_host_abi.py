@@ -5,6 +5,7 @@ import os
 import re
 import subprocess
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -203,3 +204,10 @@ def test_gemm_workspace_bytes_of_matrices_wider_than_a_product_takes():
             "    for n in (32, 129, 2000):\n"
             "        assert b.bof4_gemm_workspace_bytes(70, cols, n) >= 4 * n * cols, (cols, n)\n")
     assert subprocess.run([sys.executable, "-c", code], cwd=ROOT).returncode == 0
+
+
+def test_gemm_workspace_bytes_of_more_tokens_than_a_product_takes():
+    """The largest argument is answered in no time (every count of 32 tokens up to it was asked about once)."""
+    t = time.perf_counter()
+    assert binding.bof4_gemm_workspace_bytes(1000, 1536, 2 ** 32 - 1) >= 2 ** 32 * 1536 * 4
+    assert time.perf_counter() - t < 1.0
