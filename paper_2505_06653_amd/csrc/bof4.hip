@@ -1305,9 +1305,9 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
 #define BOF4_LAUNCH_DECODED(CARRY_)                                                                                    \
     hipLaunchKernelGGL((gemm_decoded_kernel<CARRY_>), dim3(tok_groups * groups * D.split), dim3(64 * GEMM_WIDE_WAVES), \
                        0, s, decoded, rt0 * GEMM_ROWS, n_rt, (uint32_t)rows, chunks, xp, tok_tiles, tok_groups,        \
-                       D.per_split, C.wide_flush, n_tokens, y_dev, wide_parts);
+                       D.per_split, D.flush, n_tokens, y_dev, wide_parts);
             if (n_outliers > 0) { BOF4_LAUNCH_DECODE(true) } else { BOF4_LAUNCH_DECODE(false) }
-            if (C.wide_carry) { BOF4_LAUNCH_DECODED(true) } else { BOF4_LAUNCH_DECODED(false) }
+            if (D.carry) { BOF4_LAUNCH_DECODED(true) } else { BOF4_LAUNCH_DECODED(false) }
 #undef BOF4_LAUNCH_DECODE
 #undef BOF4_LAUNCH_DECODED
         }

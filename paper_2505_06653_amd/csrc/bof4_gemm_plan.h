@@ -149,6 +149,8 @@ struct GemmDecodedPlan {
     uint32_t split, per_split;  // workgroups along the columns, chunks each
     double time;
     size_t slab_bytes;
+    uint32_t flush;  // chunks in one chain of additions
+    bool carry;
 };
 inline GemmDecodedPlan gemm_decoded_plan(uint64_t rows, uint64_t cols, uint64_t tok_tiles) {
     const uint64_t tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
@@ -156,7 +158,7 @@ inline GemmDecodedPlan gemm_decoded_plan(uint64_t rows, uint64_t cols, uint64_t 
     const uint64_t chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK, slots = tok_groups * GEMM_WIDE_TOK_TILES * GEMM_TOKENS;
     const uint64_t group_bytes = chunks * GEMM_WIDE_WAVES * GEMM_TILE_WORDS * 16, most = GEMM_DECODED_BYTES / group_bytes;
     const uint64_t least_slabs = (groups + most - 1) / most;
-    GemmDecodedPlan best = {0, 0, 0, 0.0, 0};
+    GemmDecodedPlan best = {0, 0, 0, 0.0, 0, 0, false};
     for (uint64_t n_slabs = least_slabs; n_slabs <= least_slabs + 2 && n_slabs <= groups; ++n_slabs) {
         const uint64_t slab = (groups + n_slabs - 1) / n_slabs, last = groups - (n_slabs - 1) * slab;
         if ((n_slabs - 1) * slab >= groups) continue;
@@ -168,7 +170,7 @@ inline GemmDecodedPlan gemm_decoded_plan(uint64_t rows, uint64_t cols, uint64_t 
             const double time = sums + 4.0 * (double)n_slabs + (double)rounds * (7.5 + 0.82 * (double)per) +
                                 (slab * group_bytes > (200ull << 20) ? 0.9e-6 : 0.46e-6) * (double)(rows * cols);
             if (best.slab_tiles == 0 || time < best.time)
-                best = {(uint32_t)(slab * GEMM_WIDE_WAVES), (uint32_t)split, (uint32_t)per, time, (size_t)(slab * group_bytes)};
+                best = {(uint32_t)(slab * GEMM_WIDE_WAVES), (uint32_t)split, (uint32_t)per, time, (size_t)(slab * group_bytes), 0, false};
         }
     }
     best.time += 6.0 + 0.8e-6 * (double)(tok_tiles * GEMM_TOKENS * cols);
@@ -176,18 +178,37 @@ inline GemmDecodedPlan gemm_decoded_plan(uint64_t rows, uint64_t cols, uint64_t 
 }
 // The plan where the product is decoded first, else slab_tiles = 0.  W: gemm_wide_choice's answer.
 inline GemmDecodedPlan gemm_decoded_choice(uint64_t rows, uint64_t cols, uint64_t tok_tiles, bool list, const GemmWideSplit& W) {
-    const GemmDecodedPlan no = {0, 0, 0, 0.0, 0};
+    const GemmDecodedPlan no = {0, 0, 0, 0.0, 0, 0, false};
     const uint64_t wg_rows = GEMM_WIDE_WAVES * GEMM_ROWS, tok_groups = (tok_tiles + GEMM_WIDE_TOK_TILES - 1) / GEMM_WIDE_TOK_TILES;
     if (tok_groups < 2 || cols < 512 || cols > GEMM_MAX_COLS || (rows + wg_rows - 1) / wg_rows * tok_groups >= (1ull << 23)) return no;
     // (what carrying costs: 21 % of the wide kernel's time where a chain is four chunks, 11 % at eight)
-    const double flush = (double)gemm_chains(rows, cols, tok_tiles * GEMM_TOKENS, list).wide_flush;
+    const GemmChains C = gemm_chains(rows, cols, tok_tiles * GEMM_TOKENS, list);
+    const double flush = (double)C.wide_flush;
     const double other = W.split > 0 ? W.time * (list ? 1.0 + 0.85 / (flush < 3.0 ? 3.0 : flush) : 1.0)
                                      : (list ? 1.1 : 1.0) * gemm_kernel_time(rows, cols, tok_tiles);
     // (every plan's least: the decoding at its best rate and the products without what a round costs to start)
     const uint64_t chunks = (cols + GEMM_CHUNK - 1) / GEMM_CHUNK, groups = (rows + wg_rows - 1) / wg_rows;
     if (0.98 * (10.0 + 0.46e-6 * (double)(rows * cols) + 0.82 / 256.0 * (double)(groups * tok_groups * chunks)) >= other) return no;
-    const GemmDecodedPlan D = gemm_decoded_plan(rows, cols, tok_tiles);
-    return 0.98 * D.time * (list ? 1.0 + 0.3 / flush : 1.0) + 1.0 < other ? D : no;
+    GemmDecodedPlan D = gemm_decoded_plan(rows, cols, tok_tiles);
+    // The error stays that of the kernel which would take the product otherwise.  Where that is the wide tile with the columns
+    // split alike, by the same additions.  Else the sums are carried, over chains no longer than that kernel's in the mean (with a
+    // list gemm_kernel's are no shorter than wide_flush; it adds its waves' sums in binary64, so eight uncarried runs are 35 / 8
+    // roundings more), a chunk shorter for every three workgroups more that share the columns.  Error over the other kernel's:
+    // 12288 x 4096 with 700 tokens 1.10 if not carried, 13264 x 1632 with 562 1.29, 5970 x 23808 with 1065 and a list in two parts
+    // 1.025 without the shorter chain; now 0.9 to 1.0, at 1 to 4 % more time.
+    D.flush = C.wide_flush;
+    D.carry = C.wide_carry;
+    if (D.split != W.split) {
+        const uint32_t split = W.split > 0 ? W.split : gemm_split(rows, cols, tok_tiles * GEMM_TOKENS);
+        uint32_t chain = C.wide_flush;
+        if (W.split > 0) chain = W.per_split / ((W.per_split + chain - 1) / chain);
+        if (!list && W.split == 0) chain = (uint32_t)((chunks + split - 1) / split - 1) / C.waves;
+        const uint32_t shorter = D.split > split ? (D.split - split + 2) / 3 : 0;
+        D.flush = chain > shorter ? chain - shorter : 1;
+        D.carry = true;
+    }
+    const double cost = list || (D.carry && (!C.wide_carry || W.split == 0)) ? 1.0 + 0.3 / (double)D.flush : 1.0;
+    return 0.98 * D.time * cost + 1.0 < other ? D : no;
 }
 
 // Workspace of bof4_gemm: x in the order of the products, then the partial results of the workgroups that share a row.

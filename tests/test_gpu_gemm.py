@@ -15,6 +15,7 @@ import oracle
 from paper_2505_06653_amd import binding, inputs
 from test_gpu_parity import cb_for, make_weights
 from test_gpu_gemv import dev_i64, dev_u16, quantized, rand_x
+from test_host_gemm_plan import rules  # noqa: F401 (a fixture: the host's choice of the kernel)
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -361,6 +362,41 @@ def test_gemm_decoded_first(rows, cols, n_tokens, share, split, wide_split):
         assert worst <= (cols + 64) * U, (r0, worst / U)
 
 
+@pytest.mark.parametrize("rows,cols,n_tokens,listed,split,wide_split", [
+    (12288, 4096, 700, False, 1, 0), (7824, 4736, 1050, False, 1, 0), (6978, 4128, 1197, False, 1, 2),
+    (5970, 23808, 1065, True, 2, 1), (12230, 7392, 702, True, 2, 3)])
+def test_gemm_decoded_first_rounds_no_more_than_the_kernel_it_replaces(rules, rows, cols, n_tokens, listed, split, wide_split):
+    """The root mean square error of products that are decoded first and split otherwise, against binary64, next to that of the kernel
+    which the call takes in a workspace one byte too small for it; half a per cent is several times what the sample of more
+    than 10^6 results leaves open."""
+    plan = rules(rows, cols, n_tokens, listed)
+    assert (plan.way, plan.decoded_split, plan.wide_split) == (2, split, wide_split)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
+    block, n = 32, rows * cols
+    codes = torch.randint(0, 256, (n // 2,), generator=g, device=DEV, dtype=torch.uint8)
+    scales = (torch.rand(n // block, generator=g, device=DEV) * 0.1 + 0.05).to(torch.float16)
+    cb = cb_for(64, 1)
+    oi = ov = tab = None
+    k = 0
+    if listed:  # half of the energy in the list
+        sigma = float(binding.bof4_dequantize(codes, scales, n, block, cb).float().pow(2).mean().sqrt()) * 150 ** 0.5
+        oi = torch.unique(torch.randint(0, n, (n // 150,), generator=g, device=DEV))
+        k = oi.numel()
+        ov = (torch.randn(k, generator=g, device=DEV) * sigma).to(torch.float16)
+        tab = binding.bof4_gemm_outlier_table(codes, scales, rows, cols, block, cb, oi, ov)
+    packed = binding.bof4_gemm_pack(codes, scales, rows, cols, block)
+    x = torch.randn((n_tokens, cols), generator=g, device=DEV).to(torch.bfloat16)
+    ref = x.double() @ binding.bof4_dequantize(codes, scales, n, block, cb, oi, ov).reshape(rows, cols)[:2048].double().T
+    ws = torch.empty(plan.need, dtype=torch.uint8, device=DEV)
+    err = []
+    for size in (plan.need, plan.need - 1):
+        y = binding.bof4_gemm(packed, rows, cols, cb, x, tab, k, ws=ws[:size])
+        err.append(float((y[:, :2048].double() - ref).norm() / ref.norm()))
+    print(f"rms error {err[0]:.3e}, of the other kernel {err[1]:.3e}")
+    assert err[0] <= 1.005 * err[1]
+
+
 @pytest.mark.parametrize("rows,cols,n_tokens", [(300, 2304, 330), (520, 512, 600)])
 def test_gemm_wide_tile_is_exact_where_every_partial_sum_is_a_binary32_number(rows, cols, n_tokens):
     """As for the other kernel: levels k / 8, constants 2^e, x small integers, list values multiples of 1 / 8, so that no
@@ -570,7 +606,7 @@ def test_gemm_workspace_of_more_tokens_and_of_the_least_size(rows, cols, n_max, 
     assert not torch.equal(y, y_least)  # the least size takes the other kernel
 
 
-@pytest.mark.parametrize("rows,cols,n_tokens,n_max", [(13551, 2240, 566, 2500), (31710, 1216, 581, 1400), (9496, 576, 1214, 2000)])
+@pytest.mark.parametrize("rows,cols,n_tokens,n_max", [(13551, 2240, 566, 2500), (4471, 1568, 1159, 2500), (1594, 3808, 2273, 2500)])
 def test_gemm_without_a_list_gives_the_same_bits_in_a_workspace_of_its_own_and_of_more_tokens(rows, cols, n_tokens, n_max):
     """Products that are decoded first, or nearly, without a list and not (or elsewhere) with one."""
     g = torch.Generator(device=DEV)

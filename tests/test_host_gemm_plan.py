@@ -17,10 +17,10 @@ ANY_SIZE = (1 << 64) - 1
 
 class Plan(ctypes.Structure):
     _fields_ = [(k, ctypes.c_uint32) for k in ("way", "wide_split", "decoded_split", "decoded_slab_tiles", "kernel_split",
-                                               "carry", "flush", "x_in_place")] + [("need", ctypes.c_uint64)]
+                                               "carry", "flush", "decoded_carry", "decoded_flush", "x_in_place")] + [("need", ctypes.c_uint64)]
 
 
-@pytest.fixture(scope="module")
+@pytest.fixture(scope="session")
 def rules(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("plan") / "gemm_plan.so")
     subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", so,
@@ -67,3 +67,24 @@ def test_gemm_workspace_bytes_is_enough_for_the_kernel_that_is_chosen_with_and_w
         assert binding.bof4_gemm_workspace_bytes(rows, cols, n) == rules.workspace_bytes(rows, cols, n)
         sizes = [rules.workspace_bytes(rows, cols, m) for m in range(1, n, 13)] + [rules.workspace_bytes(rows, cols, n)]
         assert sizes == sorted(sizes)
+
+
+def test_gemm_decoded_first_adds_uncarried_sums_only_as_the_wide_tile_would(rules):
+    """Where the columns are split as the wide tile splits them the chains are that tile's (the results are the same bits); in all
+    other products the sums are carried, over chains that are no longer than those of the kernel that would take the product."""
+    alike = other = 0
+    for rows, cols, n in [(12288, 4096, 700), (16343, 1376, 588), (5970, 23808, 1065)] + list(shapes(6000, 3)):
+        for listed in (False, True):
+            p = rules(rows, cols, n, listed)
+            if p.way != DECODED:
+                continue
+            if p.decoded_split == p.wide_split:
+                alike += 1
+                assert (p.decoded_carry, p.decoded_flush) == (p.carry, p.flush)
+                continue
+            other += 1
+            per_wave = -(-(-(-(-(-cols // 64)) // p.kernel_split)) // 8)  # chunks that a wave of gemm_kernel takes, at most
+            assert p.decoded_carry == 1 and 1 <= p.decoded_flush <= p.flush
+            assert p.wide_split > 0 or listed or p.decoded_flush <= per_wave
+            assert p.wide_split == 0 or p.decoded_split <= p.wide_split or p.decoded_flush < max(p.flush, 2)
+    assert alike > 1000 and other > 100, (alike, other)
