@@ -208,7 +208,11 @@ inline GemmDecodedPlan gemm_decoded_choice(uint64_t rows, uint64_t cols, uint64_
         D.carry = true;
     }
     const double cost = list || (D.carry && (!C.wide_carry || W.split == 0)) ? 1.0 + 0.3 / (double)D.flush : 1.0;
-    return 0.98 * D.time * cost + 1.0 < other ? D : no;
+    // Decoding first has to save 1 us and may be 2 % slower by the models, without a list and carried sums, where they are too
+    // kind to it, has to save 3 %: of 82 such products measured from 0.98 on, other kernel / decoded first is 0.94 to 1.09
+    // below 1.03 (28 of them, 1.01 in the mean; 28672 x 8192 with 1200 tokens 743 / 784 us) and 0.99 to 1.32 from there on.
+    const bool kind = !list && !C.wide_carry && D.split >= W.split && W.split + D.split > 1;
+    return (kind ? 1.03 : 0.98) * D.time * cost + 1.0 < other ? D : no;
 }
 
 // Workspace of bof4_gemm: x in the order of the products, then the partial results of the workgroups that share a row.

@@ -88,3 +88,13 @@ def test_gemm_decoded_first_adds_uncarried_sums_only_as_the_wide_tile_would(rule
             assert p.wide_split > 0 or listed or p.decoded_flush <= per_wave
             assert p.wide_split == 0 or p.decoded_split <= p.wide_split or p.decoded_flush < max(p.flush, 2)
     assert alike > 1000 and other > 100, (alike, other)
+
+
+@pytest.mark.parametrize("rows,cols,n_tokens,listed,way", [
+    (28672, 8192, 1200, False, WIDE), (40770, 2112, 757, False, WIDE), (27007, 1792, 628, False, WIDE),
+    (57344, 8192, 1200, False, DECODED), (16234, 9888, 2383, False, DECODED), (28672, 8192, 1200, True, DECODED),
+    (12288, 4096, 420, True, DECODED), (4096, 4096, 2000, False, DECODED)])
+def test_gemm_takes_the_kernel_that_was_measured_faster(rules, rows, cols, n_tokens, listed, way):
+    """us, the other kernel / decoded first: 743 / 784, 196 / 208, 124 / 131; 1466 / 1349, 1003 / 933, 860 / 816, 102 / 88,
+    97 / 88."""
+    assert rules(rows, cols, n_tokens, listed).way == way
