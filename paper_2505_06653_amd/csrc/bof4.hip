@@ -1121,6 +1121,28 @@ uint64_t gemv_resident_workgroups(int variant, uint32_t threads, size_t lds) {
     return slot.slots;
 }
 
+// The largest matrix (in weights) that three or four tokens pass through in one launch of bof4_gemv instead of two: a weight is looked
+// up once instead of twice and a launch saved, at three and two waves per SIMD instead of four.  What fits a compute unit
+// then depends on a workgroup's waves, one per strip of 2048 columns up to eight, and decides on large matrices.  Two
+// launches / one over 18 widths at 4 M to 600 M weights (us; three or four tokens, `l` with a list):
+//   three  1001 x 1536 10.5 / 6.6, 22016 x 4096 30.7 / 23.7, l 40.7 / 31.9; four strips 28672 x 8192 65.5 / 53.2, l 81.6 / 82.7, l
+//          40000 x 8192 113 / 119; six strips 1500 x 11008 1.12 - 1.15, 3600 x 11008 and more 0.98 - 0.85; more than eight
+//          (two per wave) 80 M weights 1.04 - 1.27, 260 M 0.89 - 1.11
+//   four   4096 x 4096 14.6 / 10.0; 28672 x 4096 41.9 / 41.1, l 55.9 / 61.2, l 16384 x 4096 38.1 / 37.6; three strips 6500 x 6144
+//          1.07, l 1.11, 20000 x 6144 46.7 / 54.8, l 57.8 / 64.8; five strips 1.1 - 1.5; 28672 x 8192 76.7 / 77.6, l 95.3 / 91.9;
+//          l six strips 120 M 1.03, 260 M 0.96
+uint64_t gemv_most_weights(uint64_t strips, uint32_t n_tokens, bool list) {
+    if (n_tokens == 3) {
+        if (strips == 6) return 1ull << 25;
+        if (strips > 8) return 1ull << 26;
+        return strips == 4 && list ? 3ull << 26 : strips < 6 ? ~0ull : 1ull << 28;
+    }
+    if (strips == 5 || (strips == 1 && list)) return ~0ull;
+    if (strips == 3 || (strips == 2 && list)) return list ? 1ull << 26 : 1ull << 25;
+    if (list) return strips == 6 || (strips > 8 && strips < 13) ? 1ull << 27 : 1ull << 28;
+    return strips > 8 && strips < 13 ? 1ull << 26 : 1ull << 27;
+}
+
 // Outlier table of bof4_gemv: offsets [rows * strips + 1] (padded to 8 bytes), then one {column, delta} pair per entry.
 struct GemvTableLayout {
     size_t entries, total;
@@ -1401,25 +1423,23 @@ int bof4_gemv(const uint8_t* codes_dev, const uint16_t* scales_dev, uint64_t row
     const uint16_t* x = (const uint16_t*)x_dev;
     timing_begin(s);
     for (uint32_t t0 = 0, nt; t0 < n_tokens; t0 += nt) {
-        // Three or four tokens in one launch look a weight up once instead of twice and save a launch, at three and two waves
-        // per SIMD instead of four: 1001 x 1536, 3 tokens 9.6 -> 6.6 us, 4096 x 4096 13.7 -> 8.6, 22016 x 4096 30.5 -> 23.5 (4:
-        // 34.4 -> 33.4); with a list 11.7 -> 7.1, 16.6 -> 10.0, 40.5 -> 31.6.  Not where it is slower: 4096 x 11008, 3 tokens
-        // 22.6 -> 23.2, with a list 27.0 -> 28.2; 28672 x 8192, 4 tokens 76.3 -> 77.6 (with a list 95.3 -> 91.6).
         nt = n_tokens - t0 < GEMV_MAX_TOKENS ? n_tokens - t0 : GEMV_MAX_TOKENS;
-        if (nt == 3 && strips > 4 && rows * cols > (1ull << 25)) nt = 2;
-        if (nt == 4 && n_outliers == 0 && rows * cols >= (1ull << 27)) nt = 2;
+        if (nt > 2 && rows * cols > gemv_most_weights(strips, nt, n_outliers > 0)) nt = 2;
         const uint16_t* xt = x + (uint64_t)t0 * cols;
         float* yt = y_dev + (uint64_t)t0 * rows;
         // with a list every wave keeps its slice of x in LDS as well
         const uint32_t waves = (uint32_t)(strips < GEMV_MAX_WAVES ? strips : GEMV_MAX_WAVES);
         const size_t lds = n_outliers > 0 ? (size_t)waves * GEMV_STRIP * 2 * nt : 0;
         // Rows per workgroup: every workgroup pays for its slice of x, the level table and two barriers, so the
-        // rows are dealt out evenly over as many workgroups as the chip holds at once - one round, no tail.
+        // rows are dealt out evenly over as many workgroups as the chip holds at once - one round, no tail - or, with more
+        // than GEMV_MAX_RC rows for each of them, over full rounds (40000 x 8192, three tokens with a list, which hold two
+        // workgroups per compute unit: 113 more workgroups than fit 185 us, two rounds 119).
         const int variant = 2 * (int)(nt - 1) + (n_outliers > 0 ? 1 : 0);
         const uint64_t slots = gemv_resident_workgroups(variant, 64 * waves, lds);
         if (slots == 0) return fail(BOF4_ERR_HIP, "bof4_gemv: occupancy query failed");
-        uint64_t rc64 = (rows + slots - 1) / slots;
-        const uint32_t rc = (uint32_t)(rc64 < 4 ? 4 : rc64 > GEMV_MAX_RC ? GEMV_MAX_RC : rc64);
+        const uint64_t rounds = (rows + slots * GEMV_MAX_RC - 1) / (slots * GEMV_MAX_RC);
+        const uint64_t rc64 = (rows + slots * rounds - 1) / (slots * rounds);
+        const uint32_t rc = (uint32_t)(rc64 < 4 ? 4 : rc64);
         const uint32_t grid = (uint32_t)((rows + rc - 1) / rc);
 #define BOF4_LAUNCH_GEMV(T_, OUT_)                                                                                \
     hipLaunchKernelGGL((gemv_kernel<T_, OUT_>), dim3(grid), dim3(64 * waves), lds, s, codes, scales_dev,          \

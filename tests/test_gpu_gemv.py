@@ -100,6 +100,17 @@ def test_gemv_three_and_four_tokens_in_one_launch(rows, cols, n_tokens, opq):
         assert np.array_equal(y[t], run_gpu(cb, codes, scales, lst[0], lst[1], rows, cols, 32, x[t: t + 1].contiguous())[0])
 
 
+@pytest.mark.parametrize("opq", [0, 1])
+@pytest.mark.parametrize("rows,cols,n_tokens", [(3100, 11008, 3), (5500, 6144, 4), (11000, 6144, 4), (300001, 32, 1), (300001, 32, 4),
+                                                (140003, 96, 3)])
+def test_gemv_two_launches_and_several_rounds_of_workgroups(rows, cols, n_tokens, opq):
+    """Matrices whose three or four tokens take two launches (with a list from the third one on: its limit is twice the other),
+    and more rows than the workgroups that the chip holds at once take with 64 rows each, dealt out over two and three full rounds."""
+    cb, codes, scales, oi, ov = quantized(rows, cols, 32, 1, opq, seed=61)
+    lst = (oi, ov) if opq else (None, None)
+    check(cb, codes, scales, lst[0], lst[1], rows, cols, 32, rand_x(n_tokens, cols, 23))
+
+
 def _random_cases(count, seed):
     rng = np.random.default_rng(seed)
     cases = []
