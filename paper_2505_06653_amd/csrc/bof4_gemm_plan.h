@@ -101,12 +101,20 @@ inline GemmWideSplit gemm_wide_choice(uint64_t rows, uint64_t cols, uint64_t tok
 
 // Where gemm_kernel reads x as it stands instead of in a copy reordered by a kernel of its own (3 us): tokens of one tile, and
 // matrices so small that the launch is what counts - a wave's load then touches a line per token and not 8 in all -, or so
-// few tokens that there are few lines.  Copy / in place: 4096 x 4096, 8 and 32 tokens 12.3 / 10.3 us (with a list 12.4 / 11.1), 500
-// x 28672 14.2 / 12.4; 8 tokens 12288 x 4096 15.1 / 13.2, 28672 x 8192 41.9 / 37.2, 8192 x 28672 45.7 / 43.2; but 32 tokens
-// 12288 x 4096 15.1 / 21.9, 8 tokens 4096 x 11008 14.6 / 15.2, with a list 12288 x 4096 17.7 / 17.3, 22016 x 4096 24.8 / 26.8.
+// few tokens that there are few lines.  Copy / in place, us:
+//   up to 2^24 weights, 75 shapes: 1.07 to 1.4 times as fast at 8 and 16 tokens (4096 x 4096, 8 and 32 tokens 12.8 / 10.0, 12.9 /
+//   10.7), at 32 too except where the second workgroup of a compute unit is there for some only: 257 to 330 workgroups and
+//   14 M weights and more 0.88 to 0.95 (4160 x 4032, 3000 x 5568, 10000 x 1664), 376 1.02 and with a list 0.96, 10 M 1.1
+//   above that, no list: 8 tokens 12288 x 4096 14.6 / 12.8, 28672 x 8192 42.2 / 37.4, 8192 x 28672 45.3 / 42.0, 57344 x 8192 1.00; with
+//   one workgroup per compute unit, eight waves, the lines are waited for (8192 x 8192 15.3 / 16.9, 8192 x 12288 0.89, 8192 x
+//   4096 1.01 - 1.14); 16 tokens 8256 x 4096 0.98, 32 tokens 12288 x 4096 0.69; with a list, 8 tokens 22016 x 4096 0.92
 // (Turning whole lines into the products' order through LDS: 12288 x 4096, 8 / 32 tokens 14.7 / 16.3, 22016 x 4096 22.7 / 26.1.)
 inline bool gemm_x_in_place(uint64_t rows, uint64_t cols, uint64_t n_tokens, bool list) {
-    return n_tokens <= GEMM_TOKENS && (rows * cols <= (1ull << 24) || (!list && n_tokens <= 8 && rows >= 8192));
+    if (n_tokens > GEMM_TOKENS) return false;
+    const uint64_t wgs = gemm_row_tiles(rows) / gemm_row_tiles_per_wg(rows, cols, n_tokens) * gemm_split(rows, cols, n_tokens);
+    if (rows * cols <= (1ull << 24))
+        return n_tokens <= 16 || wgs <= 256 || wgs >= 384 || rows * cols <= (3ull << 22);
+    return !list && n_tokens <= 8 && rows >= 8192 && (wgs > 256 || cols <= 4096 || rows * cols >= (1ull << 27));
 }
 
 // Chunks in one chain of additions.  gemm_kernel: with a list half of what a wave takes, which holds its error to that of

@@ -98,3 +98,12 @@ def test_gemm_takes_the_kernel_that_was_measured_faster(rules, rows, cols, n_tok
     """us, the other kernel / decoded first: 743 / 784, 196 / 208, 124 / 131; 1466 / 1349, 1003 / 933, 860 / 816, 102 / 88,
     97 / 88."""
     assert rules(rows, cols, n_tokens, listed).way == way
+
+
+@pytest.mark.parametrize("rows,cols,n_tokens,listed,in_place", [
+    (4096, 4096, 32, True, 1), (4160, 4032, 32, False, 0), (4160, 4032, 16, True, 1), (10000, 1664, 32, True, 0), (10000, 1024, 32, True, 1),
+    (3000, 5568, 32, False, 0), (12000, 1376, 32, False, 0), (12000, 1376, 16, False, 1), (6144, 2688, 32, False, 1),
+    (8192, 8192, 8, False, 0), (8192, 11008, 1, False, 0), (8192, 4096, 8, False, 1), (9000, 8192, 8, False, 1), (9000, 8192, 9, False, 0),
+    (9000, 8192, 8, True, 0), (8192, 16384, 8, False, 1), (28672, 8192, 1, False, 1), (4096, 11008, 8, False, 0)])
+def test_gemm_reads_x_in_place_where_that_was_measured_faster(rules, rows, cols, n_tokens, listed, in_place):
+    assert rules(rows, cols, n_tokens, listed).x_in_place == in_place
