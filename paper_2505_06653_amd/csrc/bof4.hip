@@ -1375,10 +1375,14 @@ int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double
                        (const char*)packed_dev, (uint32_t)rows, (uint32_t)cols, cb, offsets_dev, entries_dev,     \
                        (uint32_t)n_outliers, T.lg, T.row_tiles, xp, (const uint16_t*)x_dev, tile0, nt, C.list_flush, C.n_runs, dst);
 #define BOF4_LAUNCH_GEMM_NT(R_, OUT_)                                                                             \
-    if (P.x_in_place) { BOF4_LAUNCH_GEMM(R_, 1, OUT_, true) } else if (nt_tiles == 4) { BOF4_LAUNCH_GEMM(R_, 4, OUT_, false) } \
+    if (nt_tiles == 4) { BOF4_LAUNCH_GEMM(R_, 4, OUT_, false) }                                                     \
     else if (nt_tiles == 3) { BOF4_LAUNCH_GEMM(R_, 3, OUT_, false) }                                               \
     else if (nt_tiles == 2) { BOF4_LAUNCH_GEMM(R_, 2, OUT_, false) } else { BOF4_LAUNCH_GEMM(R_, 1, OUT_, false) }
-        if (n_outliers > 0) {
+        if (P.x_in_place && n_outliers > 0) {  // (with a list only on matrices that take one tile of rows per wave)
+            BOF4_LAUNCH_GEMM(1, 1, true, true)
+        } else if (P.x_in_place) {
+            if (per_wg_tiles == 2) { BOF4_LAUNCH_GEMM(2, 1, false, true) } else { BOF4_LAUNCH_GEMM(1, 1, false, true) }
+        } else if (n_outliers > 0) {
             if (per_wg_tiles == 2) { BOF4_LAUNCH_GEMM_NT(2, true) } else { BOF4_LAUNCH_GEMM_NT(1, true) }
         } else {
             if (per_wg_tiles == 2) { BOF4_LAUNCH_GEMM_NT(2, false) } else { BOF4_LAUNCH_GEMM_NT(1, false) }

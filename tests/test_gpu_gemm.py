@@ -518,6 +518,28 @@ def test_gemm_x_read_in_place_takes_nothing_from_the_next_token(rows, cols, n_to
     assert np.array_equal(y[::2], y_clean[::2]) and np.isnan(y[1::2]).all()
 
 
+def test_gemm_x_read_in_place_with_two_tiles_of_rows_per_wave():
+    """No list, few tokens, a matrix of 2^27 weights and more with half a chunk at the end of its rows: the bound of every product
+    here, and nothing from the neighbouring tokens."""
+    rows, cols, n_tokens = 8224, 16352, 5
+    g = torch.Generator(device=DEV)
+    g.manual_seed(99)
+    codes = torch.randint(0, 256, (rows * cols // 2,), generator=g, device=DEV, dtype=torch.uint8)
+    scales = (torch.rand(rows * cols // 32, generator=g, device=DEV) * 0.1 + 0.05).to(torch.float16)
+    cb = cb_for(32, 1) + 0.004
+    packed = binding.bof4_gemm_pack(codes, scales, rows, cols, 32)
+    x = torch.randn((n_tokens, cols), generator=g, device=DEV).to(torch.bfloat16)
+    y = binding.bof4_gemm(packed, rows, cols, cb, x)
+    w = binding.bof4_dequantize(codes, scales, rows * cols, 32, cb).reshape(rows, cols)
+    for r0 in range(0, rows, 2048):
+        wd = w[r0: r0 + 2048].double()
+        ref, mag = x.double() @ wd.T, x.double().abs() @ wd.abs().T
+        assert bool(((y[:, r0: r0 + 2048].double() - ref).abs() <= (cols + 64) * U * mag).all())
+    x[1::2] = float("nan")
+    z = binding.bof4_gemm(packed, rows, cols, cb, x)
+    assert torch.equal(z[::2], y[::2]) and bool(z[1::2].isnan().all())
+
+
 def test_gemm_unit_vectors_pick_single_decoded_weights():
     """x = a unit vector per token: the product returns one column of the decoded matrix, exactly."""
     rows, cols, block = 45, 2304, 64

@@ -107,3 +107,12 @@ def test_gemm_takes_the_kernel_that_was_measured_faster(rules, rows, cols, n_tok
     (9000, 8192, 8, True, 0), (8192, 16384, 8, False, 1), (28672, 8192, 1, False, 1), (4096, 11008, 8, False, 0)])
 def test_gemm_reads_x_in_place_where_that_was_measured_faster(rules, rows, cols, n_tokens, listed, in_place):
     assert rules(rows, cols, n_tokens, listed).x_in_place == in_place
+
+
+def test_gemm_reads_x_in_place_with_a_list_only_where_a_wave_takes_one_tile_of_rows(rules):
+    """(There is no kernel for the other.)  A wave takes two from 2^27 weights up at these token counts."""
+    rng = np.random.default_rng(4)
+    for _ in range(20000):
+        rows, cols = int(np.exp(rng.uniform(0, 13))), int(rng.integers(1, 1025)) * 32
+        p = rules(rows, cols, int(rng.integers(1, 33)), True)
+        assert not p.x_in_place or rows * cols < 1 << 27
