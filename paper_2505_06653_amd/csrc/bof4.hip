@@ -257,16 +257,17 @@ static_assert(pass_grid(false, true, false) <= PASS_GRID_MAX && pass_grid(false,
 constexpr uint64_t MAE_SAMPLED_TILES = 2000;
 constexpr uint64_t MAE_SAMPLING_MIN_TILES = 16384;
 uint32_t mae_sample_mask(uint64_t tiles) {
-    uint32_t one_in = 2;
+    uint32_t one_in = 8;
     while (one_in < 64 && tiles / (2 * one_in) >= MAE_SAMPLED_TILES) one_in *= 2;
     return one_in - 1;
 }
+static_assert(MAE_SAMPLING_MIN_TILES / 8 >= MAE_SAMPLED_TILES, "one in 8 is enough from there on");
 uint64_t mae_cand_entries(uint64_t n) {
     const uint64_t e = n < (1ull << 29) ? n / 16 : n / 32;
     return e < (1ull << 27) ? e : (1ull << 27);
 }
 // Two waves per SIMD of mae_pass_kernel, three of mae_window_kernel.
-constexpr uint32_t MAE_PASS_GRID = 2048 / MAE_PASS_WAVES, MAE_WINDOW_GRID = 3072 / WAVES_PER_WG;
+constexpr uint32_t MAE_PASS_GRID = 2048 / MAE_PASS_WAVES, MAE_WINDOW_GRID = MAE_WINDOW_WAVES / WAVES_PER_WG;
 constexpr uint32_t MAE_SLOTS = MAE_PASS_GRID * MAE_PASS_WAVES * MAE_SLOTS_PER_PASS_WAVE;  // at most
 static_assert(MAE_WINDOW_GRID <= MAE_MAX_WGS && MAE_PASS_GRID <= MAE_MAX_WGS &&
                   MAE_WINDOW_GRID * WAVES_PER_WG * MAE_SLOTS_PER_WINDOW_WAVE == MAE_SLOTS,
@@ -274,7 +275,7 @@ static_assert(MAE_WINDOW_GRID <= MAE_MAX_WGS && MAE_PASS_GRID <= MAE_MAX_WGS &&
 // The room for counts, floating-point partials and the list's fill is what a count per wave once took (workspaces of that
 // size are in use).
 struct MaeWsLayout {
-    size_t hist, state, cnt_part, sae_part, record, cand_count, cand_full, cand, total;
+    size_t hist, state, cnt_part, sae_part, record, cand_count, list, cand, total;
 };
 MaeWsLayout mae_ws_layout(uint64_t n) {
     MaeWsLayout L;
@@ -291,7 +292,7 @@ MaeWsLayout mae_ws_layout(uint64_t n) {
                       (size_t)MAE_MAX_WGS * WAVES_PER_WG * 4 <= room, "the records fit where they stood");
     o += room;
     L.record = o;   o += align_up(MAE_REC * 8, 256);
-    L.cand_full = o;  o += 256;
+    L.list = o;       o += 256;
     L.cand = o;       o += align_up(mae_cand_entries(n) * 8, 256);
     L.total = o;
     return L;
@@ -1634,58 +1635,54 @@ int bof4_lloyd_step_mae(const void* w_dev, uint64_t n, uint32_t block, const dou
     // pass, when a wave's stretch would be tiny, or when zeroed outliers run through the search of the region around
     // zero (they are taken out again by a negative weight, which an entry cannot carry).
     uint32_t* cand_count = (uint32_t*)(base + ML.cand_count);
-    uint32_t* cand_full = (uint32_t*)(base + ML.cand_full);
+    uint32_t* list = (uint32_t*)(base + ML.list);  // MaeListWord
     unsigned long long* cand = (unsigned long long*)(base + ML.cand);
     const uint32_t n_slots = sgrid * MAE_PASS_WAVES * MAE_SLOTS_PER_PASS_WAVE;
     const bool zero_region_searched = !((skip_mask >> bt.code_of_zero) & 1u);
     const bool use_list = passes >= 3 && mae_cand_entries(n) / (sgrid * MAE_PASS_WAVES) >= 8 && !(opq && zero_region_searched);
-    // One pass over all the weights instead of two (large tensors): a sampling pass over one tile in 16 tells
+    // One pass over all the weights instead of two (large tensors): a sampling pass over one tile in 8 to 64 tells
     // mae_window_kernel which first digits to write to the list (bof4_mae.h).
     const bool sampling = use_list && tiles >= MAE_SAMPLING_MIN_TILES && std::getenv("BOF4_MAE_NO_SAMPLING") == nullptr;
-    const uint32_t cand_waves = sampling ? MAE_WINDOW_GRID * WAVES_PER_WG : sgrid * MAE_PASS_WAVES;
-    const uint32_t cand_cap = (uint32_t)(mae_cand_entries(n) / cand_waves);
+    // a stretch of the list for every wave of the kernel that writes it
+    const uint32_t cand_waves = sgrid * MAE_PASS_WAVES, cand_cap = (uint32_t)(mae_cand_entries(n) / cand_waves);
+    const uint32_t window_cap = sampling ? (uint32_t)(mae_cand_entries(n) / MAE_WINDOW_WAVES) : 0u;
     hipLaunchKernelGGL(mae_init_kernel, dim3(16), dim3(256), 0, s, lc, state, hist);
-#define BOF4_LAUNCH_MAE(II, KIND_, CAND_, FULL_, SAMPLE_)                                                            \
-    if (bt.fast && opq) hipLaunchKernelGGL((mae_pass_kernel<II, true, true, KIND_>), dim3(sgrid), dim3(64 * MAE_PASS_WAVES),          \
-                                           0, s, w, n_seg, cb, bt, signed_norm, T2, state, hist, cnt_part, sae_part,  \
-                                           CAND_, cand_count, cand_cap, FULL_, cand_waves, unweighted, SAMPLE_);                  \
-    else if (bt.fast) hipLaunchKernelGGL((mae_pass_kernel<II, true, false, KIND_>), dim3(sgrid), dim3(64 * MAE_PASS_WAVES),           \
-                                         0, s, w, n_seg, cb, bt, signed_norm, T2, state, hist, cnt_part, sae_part,    \
-                                         CAND_, cand_count, cand_cap, FULL_, cand_waves, unweighted, SAMPLE_);                    \
-    else if (opq) hipLaunchKernelGGL((mae_pass_kernel<II, false, true, KIND_>), dim3(sgrid), dim3(64 * MAE_PASS_WAVES), 0,            \
-                                     s, w, n_seg, cb, bt, signed_norm, T2, state, hist, cnt_part, sae_part, CAND_,    \
-                                     cand_count, cand_cap, FULL_, cand_waves, unweighted, SAMPLE_);                               \
-    else hipLaunchKernelGGL((mae_pass_kernel<II, false, false, KIND_>), dim3(sgrid), dim3(64 * MAE_PASS_WAVES), 0, s, w,              \
-                            n_seg, cb, bt, signed_norm, T2, state, hist, cnt_part, sae_part, CAND_, cand_count,       \
-                            cand_cap, FULL_, cand_waves, unweighted, SAMPLE_);
-#define BOF4_LAUNCH_MAE_BLOCK(KIND_, CAND_, FULL_, SAMPLE_)                 \
+#define BOF4_LAUNCH_MAE_AS(II, FAST_, OPQ_, KIND_, READ_, SAMPLE_, SECOND_)                                                \
+    hipLaunchKernelGGL((mae_pass_kernel<II, FAST_, OPQ_, KIND_>), dim3(sgrid), dim3(64 * MAE_PASS_WAVES), 0, s, w, n_seg,   \
+                       cb, bt, signed_norm, T2, state, hist, cnt_part, sae_part, cand, cand_count, cand_cap, READ_,         \
+                       window_cap, unweighted, SAMPLE_, SECOND_);
+#define BOF4_LAUNCH_MAE(II, KIND_, READ_, SAMPLE_, SECOND_)                                                                \
+    if (bt.fast && opq) { BOF4_LAUNCH_MAE_AS(II, true, true, KIND_, READ_, SAMPLE_, SECOND_) }                              \
+    else if (bt.fast) { BOF4_LAUNCH_MAE_AS(II, true, false, KIND_, READ_, SAMPLE_, SECOND_) }                               \
+    else if (opq) { BOF4_LAUNCH_MAE_AS(II, false, true, KIND_, READ_, SAMPLE_, SECOND_) }                                   \
+    else { BOF4_LAUNCH_MAE_AS(II, false, false, KIND_, READ_, SAMPLE_, SECOND_) }
+#define BOF4_LAUNCH_MAE_BLOCK(KIND_, READ_, SAMPLE_, SECOND_)                 \
     switch (block) {                                                         \
-        case 32: BOF4_LAUNCH_MAE(32, KIND_, CAND_, FULL_, SAMPLE_) break;   \
-        case 64: BOF4_LAUNCH_MAE(64, KIND_, CAND_, FULL_, SAMPLE_) break;   \
-        case 128: BOF4_LAUNCH_MAE(128, KIND_, CAND_, FULL_, SAMPLE_) break; \
-        default: BOF4_LAUNCH_MAE(256, KIND_, CAND_, FULL_, SAMPLE_) break;  \
+        case 32: BOF4_LAUNCH_MAE(32, KIND_, READ_, SAMPLE_, SECOND_) break;   \
+        case 64: BOF4_LAUNCH_MAE(64, KIND_, READ_, SAMPLE_, SECOND_) break;   \
+        case 128: BOF4_LAUNCH_MAE(128, KIND_, READ_, SAMPLE_, SECOND_) break; \
+        default: BOF4_LAUNCH_MAE(256, KIND_, READ_, SAMPLE_, SECOND_) break;  \
     }
 #define BOF4_LAUNCH_MAE_WINDOW_AS(II, FAST_, OPQ_)                                                                    \
     hipLaunchKernelGGL((mae_window_kernel<II, FAST_, OPQ_>), dim3(MAE_WINDOW_GRID), dim3(256), 0, s, w, n_seg, cb, bt,      \
-                       signed_norm, T2, state, hist, cnt_part, sae_part, cand, cand_count, cand_cap, cand_full, unweighted);
+                       signed_norm, T2, state, hist, cnt_part, sae_part, cand, cand_count, window_cap, list, unweighted);
 #define BOF4_LAUNCH_MAE_WINDOW(II)                                                      \
     if (bt.fast && opq) { BOF4_LAUNCH_MAE_WINDOW_AS(II, true, true) }                   \
     else if (bt.fast) { BOF4_LAUNCH_MAE_WINDOW_AS(II, true, false) }                    \
     else if (opq) { BOF4_LAUNCH_MAE_WINDOW_AS(II, false, true) }                        \
     else { BOF4_LAUNCH_MAE_WINDOW_AS(II, false, false) }
-    unsigned long long* const no_cand = nullptr;
-    const uint32_t* const no_gate = nullptr;
-    auto select = [&](const uint32_t* gate, bool first, bool last, bool wrote_list, bool check_window) {
+    const uint32_t* const no_list = nullptr;
+    auto select = [&](bool first, bool last, MaeWrote wrote) {
         hipLaunchKernelGGL(mae_select_kernel, dim3(1), dim3(1024), 0, s, state, hist, cnt_part, sae_part,
-                           sampling ? MAE_WINDOW_GRID : sgrid, sampling ? sgrid : 0u, n_slots, gate, first ? 1 : 0, last ? 1 : 0,
-                           (uint32_t)skip_mask, wrote_list ? cand_count : (const uint32_t*)nullptr, cand_waves, cand_cap,
-                           cand_full, check_window ? 1 : 0, direct ? direct : rec_dev, unweighted);
+                           sampling ? MAE_WINDOW_GRID : sgrid, sampling ? sgrid : 0u, n_slots, first ? 1 : 0, last ? 1 : 0,
+                           (uint32_t)skip_mask, (int)wrote, cand_count, wrote == MAE_AFTER_WINDOWS ? MAE_WINDOW_WAVES : cand_waves,
+                           wrote == MAE_AFTER_WINDOWS ? window_cap : cand_cap, list, direct ? direct : rec_dev, unweighted);
     };
     if (sampling) {
         const uint32_t sample_mask = mae_sample_mask(tiles);
-        BOF4_LAUNCH_MAE_BLOCK(MAE_SAMPLE, no_cand, no_gate, sample_mask)
+        BOF4_LAUNCH_MAE_BLOCK(MAE_SAMPLE, no_list, sample_mask, 0)
         hipLaunchKernelGGL(mae_predict_kernel, dim3(1), dim3(1024), 0, s, state, hist, (double)n / (sample_mask + 1),
-                           (uint32_t)skip_mask, (double)cand_cap * cand_waves / (sample_mask + 1), cand_full);
+                           (uint32_t)skip_mask, (double)mae_cand_entries(n) / (sample_mask + 1), list);
         timing_begin(s);
         switch (block) {
             case 32: BOF4_LAUNCH_MAE_WINDOW(32) break;
@@ -1694,29 +1691,30 @@ int bof4_lloyd_step_mae(const void* w_dev, uint64_t n, uint32_t block, const dou
             default: BOF4_LAUNCH_MAE_WINDOW(256) break;
         }
         timing_end(s);
-        select(no_gate, true, false, true, true);
-        // only if the list cannot be used: the first pass over all the weights after all
-        BOF4_LAUNCH_MAE_BLOCK(MAE_FIRST, no_cand, cand_full, 0u)
-        select(cand_full, true, false, false, false);
+        select(true, false, MAE_AFTER_WINDOWS);
+        // only if the windows did not do: the first pass over all the weights after all
+        BOF4_LAUNCH_MAE_BLOCK(MAE_FIRST, list, 0u, 0)
+        select(true, false, MAE_AFTER_RERUN);
     }
     for (uint32_t p = sampling ? 1 : 0; p < passes; ++p) {
         const bool first = p == 0;
-        const bool writes_list = use_list && !sampling && p == 1, reads_list = use_list && p > (sampling ? 0u : 1u);
-        unsigned long long* cand_w = writes_list || reads_list ? cand : nullptr;
-        const uint32_t* full = reads_list ? cand_full : nullptr;
+        // the second pass writes the list, or where mae_window_kernel has done that reads it if it can; the others read it
+        const bool second = use_list && p == 1;
+        const uint32_t* read = use_list && p > (sampling ? 0u : 1u) ? list : no_list;
         if (first) {
             timing_begin(s);
-            BOF4_LAUNCH_MAE_BLOCK(MAE_FIRST, cand_w, full, 0u)
+            BOF4_LAUNCH_MAE_BLOCK(MAE_FIRST, no_list, 0u, 0)
             timing_end(s);
         } else {
-            BOF4_LAUNCH_MAE_BLOCK(MAE_LATER, cand_w, full, 0u)
+            BOF4_LAUNCH_MAE_BLOCK(MAE_LATER, read, 0u, second ? 1 : 0)
         }
-        select(no_gate, first, p + 1 == passes, writes_list, false);
+        select(first, p + 1 == passes, second ? (sampling ? MAE_AFTER_SECOND : MAE_AFTER_LIST) : MAE_NO_LIST);
     }
 #undef BOF4_LAUNCH_MAE_WINDOW
 #undef BOF4_LAUNCH_MAE_WINDOW_AS
 #undef BOF4_LAUNCH_MAE_BLOCK
 #undef BOF4_LAUNCH_MAE
+#undef BOF4_LAUNCH_MAE_AS
     HIP_TRY(hipGetLastError());
     if (direct) {
         HIP_TRY(wait_for_flag(s, &out_host->n_used));
@@ -1725,18 +1723,24 @@ int bof4_lloyd_step_mae(const void* w_dev, uint64_t n, uint32_t block, const dou
         HIP_TRY(wait_for_stream(s));
     }
     if (std::getenv("BOF4_MAE_TRACE") != nullptr) {  // debugging aid: which way the search went
-        uint32_t unusable = 0;
-        if (use_list) HIP_TRY(hipMemcpy(&unusable, cand_full, 4, hipMemcpyDeviceToHost));
-        std::fprintf(stderr, "bof4_lloyd_step_mae: passes %u, list %d, sampling %d, list unusable %u\n", passes,
-                     (int)use_list, (int)sampling, unusable);
+        uint32_t word[MAE_LIST_WORDS] = {};
+        if (use_list) HIP_TRY(hipMemcpy(word, list, sampling ? sizeof(word) : 4, hipMemcpyDeviceToHost));
+        const char* const outcome[4] = {"", ": windows missed", ": a stretch ran full", ": declined"};
+        const uint32_t o = word[MAE_WINDOW_OUTCOME] & 3u;
+        std::fprintf(stderr, "bof4_lloyd_step_mae: passes %u, list %d, sampling %d, list unusable %u%s%s\n", passes,
+                     (int)use_list, (int)sampling, sampling ? (o != MAE_LIST_SERVED ? 1u : 0u) : word[MAE_LIST_UNUSABLE], outcome[o],
+                     o == MAE_LIST_SERVED           ? ""
+                     : word[MAE_NO_LIST_AT_ALL]     ? ", few values"
+                     : word[MAE_LIST_UNUSABLE] != 0 ? ", and in the second pass" : ", written by the second pass");
         if (use_list && std::getenv("BOF4_MAE_TRACE")[0] == '2') {  // the fullest stretch of the list, the windows
-            std::vector<uint32_t> counts(cand_waves);
-            HIP_TRY(hipMemcpy(counts.data(), cand_count, (size_t)cand_waves * 4, hipMemcpyDeviceToHost));
+            const bool by_windows = sampling && (o == MAE_LIST_SERVED || word[MAE_NO_LIST_AT_ALL]);
+            std::vector<uint32_t> counts(by_windows ? MAE_WINDOW_WAVES : cand_waves);
+            HIP_TRY(hipMemcpy(counts.data(), cand_count, counts.size() * 4, hipMemcpyDeviceToHost));
             uint32_t most = 0;
             for (uint32_t c : counts) most = c > most ? c : most;
             MaeLevelState st[16];
             HIP_TRY(hipMemcpy(st, state, sizeof(st), hipMemcpyDeviceToHost));
-            std::fprintf(stderr, "  fullest stretch %u of %u entries;", most, cand_cap);
+            std::fprintf(stderr, "  fullest stretch %u of %u entries;", most, by_windows ? window_cap : cand_cap);
             for (int l = 0; l < 16; ++l)
                 std::fprintf(stderr, " [%d: window %u+%u, key %u of %u bits]", l, st[l].win_lo, st[l].win_len,
                              st[l].prefix, lc.bits[l]);

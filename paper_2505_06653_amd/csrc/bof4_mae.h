@@ -14,12 +14,12 @@
 // list - key, region and block constant in 8 bytes - and the passes after it read that list instead of the weights.
 // Every wave appends to a region of its own; if one of them runs full (a tensor of equal numbers), the later passes
 // scan the weights as before.
-// Large tensors get by with ONE pass over all the weights: a first-digit histogram over one tile in 16 (picked by a
+// Large tensors get by with ONE pass over all the weights: a first-digit histogram over one tile in 8 to 64 (picked by a
 // hash of the tile number) says where every region's median will be to within a few digits; the full pass
 // (mae_window_kernel) then adds up what lies below that window and in all, and writes the elements inside to the list.
 // If the exact first digit of every region falls inside its window (it does unless the sampled tiles differ from the
-// rest), all later passes read the list; if not, or if the list runs full, the first pass and all others scan the
-// weights.
+// rest), all later passes read the list.  If not, the first pass follows after all, without the sums and counts that
+// mae_window_kernel has taken already; and then, or if the list ran full, the second pass writes the list anew.
 //
 // What is computed is "the smallest x_k with 2 * sum_{x_j <= x_k} a_j >= sum_j a_j" - the lower weighted median,
 // which minimises sum a_j |x_j - c|.  (The closing formula of appendix B.4 names the element before it; its own
@@ -53,6 +53,17 @@ constexpr uint32_t MAE_MAX_WGS = 768;  // most workgroups of a pass: the stride 
 // mae_pass_kernel takes 3 slots, one of mae_window_kernel (whose grid holds half as many waves again) 2.
 constexpr uint32_t MAE_SLOTS_PER_PASS_WAVE = 3;
 constexpr uint32_t MAE_SLOTS_PER_WINDOW_WAVE = 2;
+constexpr uint32_t MAE_WINDOW_WAVES = 3072;  // three per SIMD
+// What became of the list, in the workspace.  Words after the first are there only where the step samples.
+enum MaeListWord {
+    MAE_LIST_UNUSABLE,   // 1: scan the weights
+    MAE_DIGITS_MISSING,  // 1: mae_window_kernel did not find the regions' first digits
+    MAE_DECLINED,        // 1: the sample says that the windows would take in too much: mae_window_kernel does not run
+    MAE_NO_LIST_AT_ALL,  // 1: nor would the second pass's find room (few values)
+    MAE_WINDOW_OUTCOME,  // MaeOutcome of mae_window_kernel's list, for who looks into it
+    MAE_LIST_WORDS
+};
+enum MaeOutcome { MAE_LIST_SERVED, MAE_WINDOW_MISSED, MAE_STRETCH_FULL, MAE_LIST_DECLINED };
 // Bins of all regions' windows together in mae_window_kernel.
 constexpr uint32_t MAE_WINDOW_BINS = 1024;
 // A wave-uniform number to scalar registers (divisions leave it in vector registers).
@@ -147,8 +158,9 @@ __global__ __launch_bounds__(256) void mae_init_kernel(MaeLevelConst lc, MaeLeve
 
 // One pass over the weights, by KIND: the first one also counts the regions' elements and accumulates the error sum
 // sum |block constant| |x - level| at the current codebook; the sampling pass is a first one over the sampled tiles
-// without either (a third of its vector work).  A later pass reads the list (n_stretches stretches of at most cand_cap
-// entries, cand_count of them) where there is one and *full says that it can be used, and the weights where not.
+// without either (a third of its vector work).  A later pass reads the list where there is one and the words at `list` say
+// that it can be used, and the weights where not: a stretch of at most cand_cap entries for every wave of a pass, or of
+// window_cap for every wave of mae_window_kernel (0: that did not write it), cand_count of them filled.
 enum MaePass { MAE_SAMPLE, MAE_FIRST, MAE_LATER };
 template <int I, bool FAST, bool OPQ, MaePass KIND>
 __global__ __launch_bounds__(64 * MAE_PASS_WAVES, 2) void mae_pass_kernel(const uint4* __restrict__ w, uint64_t n_seg, CodebookArgs cb,
@@ -159,14 +171,15 @@ __global__ __launch_bounds__(64 * MAE_PASS_WAVES, 2) void mae_pass_kernel(const 
                                                            double* __restrict__ sae_part,
                                                            unsigned long long* __restrict__ cand,
                                                            uint32_t* __restrict__ cand_count, uint32_t cand_cap,
-                                                           const uint32_t* __restrict__ full, uint32_t n_stretches,
-                                                           int unweighted, uint32_t sample_mask) {
+                                                           const uint32_t* __restrict__ list, uint32_t window_cap,
+                                                           int unweighted, uint32_t sample_mask, int second) {
     using C = SegCfg<I>;
     constexpr bool FIRST = KIND != MAE_LATER, SUMS = KIND == MAE_FIRST;
-    // full != nullptr, a first pass: this launch only matters if the word is set.  cand != nullptr where no list is read:
-    // append the elements that still count to this wave's stretch of the list.
-    const bool from_list = full != nullptr && *full == 0u;
-    if (FIRST && from_list) return;
+    // list != nullptr, a first pass: it follows mae_window_kernel, whose sums stand if it ran.  The second pass, where it
+    // reads no list: append the elements that still count to this wave's stretch of it.
+    if (FIRST && list != nullptr && list[MAE_DIGITS_MISSING] == 0u) return;
+    const bool sums_too = SUMS && (list == nullptr || list[MAE_DECLINED] != 0u);
+    const bool from_list = KIND == MAE_LATER && list != nullptr && list[MAE_LIST_UNUSABLE] == 0u;
     struct Shared {  // one object, so that the table sits at LDS offset 0 (reachable by an immediate offset)
         uint2 tab[BIN_TABLE_ENTRIES];
         uint4 info[16];    // per region: klo, (lo | hi << 8 | digit mask << 16), then prefix and active flag; in
@@ -201,13 +214,16 @@ __global__ __launch_bounds__(64 * MAE_PASS_WAVES, 2) void mae_pass_kernel(const 
         for (int p = 0; p < 8; ++p) cntcol[p * 64 + lane] = 0u;
     }
     __syncthreads();
-    if (KIND == MAE_LATER && from_list) {
+    if (from_list) {
         const uint64_t n_waves = (uint64_t)gridDim.x * MAE_PASS_WAVES;
+        const bool by_windows = window_cap != 0u && list[MAE_WINDOW_OUTCOME] == MAE_LIST_SERVED;
+        const uint64_t n_stretches = by_windows ? MAE_WINDOW_WAVES : n_waves;
+        const uint32_t cap = by_windows ? window_cap : cand_cap;
         // every stretch in two halves, its even and odd runs of 512 entries: 3072 stretches deal out evenly to 2048 waves
         constexpr uint32_t AHEAD = 8, RUN = 64 * AHEAD;  // loads in flight per lane
-        for (uint64_t half = (uint64_t)blockIdx.x * MAE_PASS_WAVES + wave; half < 2ull * n_stretches; half += n_waves) {
-            const uint32_t count = cand_count[half >> 1];  // at most cand_cap, or the list would count as full
-            const unsigned long long* mine = cand + (half >> 1) * cand_cap;
+        for (uint64_t half = (uint64_t)blockIdx.x * MAE_PASS_WAVES + wave; half < 2 * n_stretches; half += n_waves) {
+            const uint32_t count = cand_count[half >> 1];  // at most cap, or the list would count as full
+            const unsigned long long* mine = cand + (half >> 1) * cap;
             for (uint32_t i0 = ((uint32_t)half & 1u) * RUN + lane; i0 < count; i0 += 2 * RUN) {
                 unsigned long long e[AHEAD];
 #pragma unroll
@@ -233,7 +249,7 @@ __global__ __launch_bounds__(64 * MAE_PASS_WAVES, 2) void mae_pass_kernel(const 
         }
         return;
     }
-    const bool writes_list = KIND == MAE_LATER && cand != nullptr && full == nullptr;
+    const bool writes_list = KIND == MAE_LATER && second != 0 && (list == nullptr || list[MAE_NO_LIST_AT_ALL] == 0u);
     const uint2* tab = sh.tab;
     const uint32_t lane_off = bin_lane_offset(threadIdx.x & 63u);
     char* stage = sh.stage + wave * C::STAGE_BYTES;
@@ -272,7 +288,7 @@ __global__ __launch_bounds__(64 * MAE_PASS_WAVES, 2) void mae_pass_kernel(const 
     uint4 G[C::NV];
     uint32_t R[C::NR];
     if (at.more()) tile_issue_loads<I>(w, at.t * 64 * C::NV, n_vec, lane, G);
-    if (SUMS) sums.close_until(at.slot, n_waves, lane, sae_part);
+    if (SUMS && sums_too) sums.close_until(at.slot, n_waves, lane, sae_part);
     for (MaeTiles next; at.more(); at = next) {  // wave-uniform
         next = at.next();
         const uint64_t t = at.t;
@@ -350,14 +366,16 @@ __global__ __launch_bounds__(64 * MAE_PASS_WAVES, 2) void mae_pass_kernel(const 
                 }
                 if (FIRST) {  // every weight lands in some bin: no branches
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        atomicAdd(&sh.hist[bin[e]], W);
-                        if (!SUMS) continue;
-                        atomicAdd(&cntcol[(code[e] >> 1) * 64 + lane], 1u << ((code[e] & 1u) * 16u));
-                        dsum += fabs((double)x[e] - __hiloint2double((int)inf[e].w, (int)inf[e].z));
-                        // pin the addition here: left alone, the compiler sinks all of them below the loop and keeps
-                        // every x and level alive until then (it spilled 300 registers)
-                        asm volatile("" : "+v"(dsum));
+                    for (int e = 0; e < 8; ++e) atomicAdd(&sh.hist[bin[e]], W);
+                    if (SUMS && sums_too) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            atomicAdd(&cntcol[(code[e] >> 1) * 64 + lane], 1u << ((code[e] & 1u) * 16u));
+                            dsum += fabs((double)x[e] - __hiloint2double((int)inf[e].w, (int)inf[e].z));
+                            // pin the addition here: left alone, the compiler sinks all of them below the loop and keeps
+                            // every x and level alive until then (it spilled 300 registers)
+                            asm volatile("" : "+v"(dsum));
+                        }
                     }
                 } else if (__builtin_amdgcn_ballot_w64(any) != 0) {  // later passes: one weight in 256 still counts
 #pragma unroll
@@ -383,24 +401,24 @@ __global__ __launch_bounds__(64 * MAE_PASS_WAVES, 2) void mae_pass_kernel(const 
                 const bool counts = FIRST ? true : (inf.w != 0u && (sub >> hi) == inf.z);
                 if (counts)
                     atomicAdd(&sh.hist[cz * 256 + ((sub >> lo) & dmask)], 0ull - (unsigned long long)k_out * W);
-                if (SUMS) {
+                if (SUMS && sums_too) {
                     atomicAdd(&cntcol[(cz >> 1) * 64 + lane], 0u - (k_out << ((cz & 1u) * 16u)));
                     dsum -= (double)k_out * fabs(__hiloint2double((int)inf.w, (int)inf.z));
                     kout += k_out;
                 }
             }
-            if (SUMS) {
+            if (SUMS && sums_too) {
                 sums.sae = fma(a_sum, dsum, sums.sae);
                 sums.w_est = fma(a_sum, (double)(C::SEG - k_out), sums.w_est);
             }
         }
-        if (SUMS) sums.close_until(next.slot, n_waves, lane, sae_part);
-        if (SUMS && ++tiles_since_flush == 65535u / C::SEG) {
+        if (SUMS && sums_too) sums.close_until(next.slot, n_waves, lane, sae_part);
+        if (SUMS && sums_too && ++tiles_since_flush == 65535u / C::SEG) {
             flush_counts();
             tiles_since_flush = 0;
         }
     }
-    if (SUMS) {
+    if (SUMS && sums_too) {
         flush_counts();
         // counts leave as one record per workgroup, [17][MAE_MAX_WGS]
         uint32_t kc = kout;
@@ -448,9 +466,9 @@ __global__ __launch_bounds__(256, 3) void mae_window_kernel(const uint4* __restr
                                                             double* __restrict__ sae_part,
                                                             unsigned long long* __restrict__ cand,
                                                             uint32_t* __restrict__ cand_count, uint32_t cand_cap,
-                                                            const uint32_t* __restrict__ full, int unweighted) {
+                                                            const uint32_t* __restrict__ list, int unweighted) {
     using C = SegCfg<I>;
-    if (*full != 0u) return;
+    if (list[MAE_DECLINED] != 0u) return;
     struct Shared {  // one object, so that the table sits at LDS offset 0 (reachable by an immediate offset)
         uint2 tab[BIN_TABLE_ENTRIES];
         u32x4 info[16];  // per region: the level as binary64, the window's first value and the first one past it
@@ -793,11 +811,11 @@ __global__ __launch_bounds__(256, 3) void mae_window_kernel(const uint4* __restr
 // weights), converted to digits by the share of the region's weight that the median's digit holds, at least half a
 // digit to either side.  Clears the bins.  The search state proper is left alone.  If the windows would fill more
 // than four fifths of the list's room (few values, many of them equal) or have more digits than mae_window_kernel has
-// bins, *cand_full says at once that the list cannot be used.
+// bins, the list is declined: all passes scan the weights.
 __global__ __launch_bounds__(1024) void mae_predict_kernel(MaeLevelState* __restrict__ state,
                                                            unsigned long long* __restrict__ hist,
                                                            double sampled, uint32_t skip_mask, double list_room,
-                                                           uint32_t* __restrict__ cand_full) {
+                                                           uint32_t* __restrict__ list) {
     __shared__ double expected[16];
     __shared__ uint32_t bins[16];
     __shared__ double share[16];
@@ -876,32 +894,46 @@ __global__ __launch_bounds__(1024) void mae_predict_kernel(MaeLevelState* __rest
             sum_captured += expected[i];
             sum_bins += bins[i];
         }
-        *cand_full = sum_captured > 0.8 * list_room || sum_bins > MAE_WINDOW_BINS ? 1u : 0u;
+        const uint32_t declined = sum_captured > 0.8 * list_room || sum_bins > MAE_WINDOW_BINS ? 1u : 0u;
+        list[MAE_LIST_UNUSABLE] = list[MAE_DIGITS_MISSING] = list[MAE_DECLINED] = list[MAE_NO_LIST_AT_ALL] = declined;
+        list[MAE_WINDOW_OUTCOME] = declined ? MAE_LIST_DECLINED : MAE_LIST_SERVED;
     }
 }
 
 // After a pass: one wave per region reads its 256 bins, fixes the next digit and clears the bins.  FIRST also takes
-// the region's total from the bins.  LAST writes the result record (layout of bof4_mae_stats): [0..15] median,
+// the region's total from the bins.  `wrote` says what the pass before it did to the list.  LAST writes the result record (layout of bof4_mae_stats): [0..15] median,
 // [16..31] den, [32..47] cnt (integers), [48] sae, [49] n_used, [50] n_outliers (integers); word 49 is stored last, at
 // system scope, so that a host watching it may read the record as soon as it changes.
+enum MaeWrote {
+    MAE_NO_LIST,
+    MAE_AFTER_LIST,     // the second pass of a step that does not sample
+    MAE_AFTER_WINDOWS,  // mae_window_kernel
+    MAE_AFTER_RERUN,    // the first pass, where mae_window_kernel did not find the first digits
+    MAE_AFTER_SECOND    // the second pass after these: it has written the list where that could not be used
+};
 __global__ __launch_bounds__(1024) void mae_select_kernel(MaeLevelState* __restrict__ state,
                                                           unsigned long long* __restrict__ hist,
                                                           const unsigned long long* __restrict__ cnt_part,
                                                           const double* __restrict__ sae_part, uint32_t n_part,
                                                           uint32_t n_part_scan, uint32_t n_slots,
-                                                          const uint32_t* __restrict__ gate, int first, int last, uint32_t skip_mask,
+                                                          int first, int last, uint32_t skip_mask, int wrote,
                                                           const uint32_t* __restrict__ cand_count,
                                                           uint32_t cand_waves, uint32_t cand_cap,
-                                                          uint32_t* __restrict__ cand_full, int check_window,
+                                                          uint32_t* __restrict__ list,
                                                           double* __restrict__ out, int unweighted) {
     const uint32_t lane = threadIdx.x & 63, l = threadIdx.x >> 6;  // wave l = region l
-    if (gate != nullptr && *gate == 0u) return;  // as for the passes: this launch follows one that did nothing
+    // as for the passes: this launch follows one that did nothing
+    if (wrote == MAE_AFTER_WINDOWS && list[MAE_DECLINED] != 0u) return;
+    if (wrote == MAE_AFTER_RERUN && list[MAE_DIGITS_MISSING] == 0u) return;
     // after the pass that wrote the list: did every wave's stretch hold its entries?  (and, below, if the list was
-    // captured by windows: was the pass run at all, and does every region's digit lie inside its window?  If not, the state
-    // stays as it is: a first pass over all the weights starts the search again.)
-    uint32_t list_bad = check_window ? *cand_full : 0u;
-    if (cand_count != nullptr && list_bad == 0u)
-        for (uint32_t i = threadIdx.x; i < cand_waves; i += 1024) list_bad |= cand_count[i] > cand_cap ? 1u : 0u;
+    // captured by windows: does every region's digit lie inside its window?  If not, the state stays as it is: a first pass
+    // over all the weights starts the search again.)
+    const bool check_window = wrote == MAE_AFTER_WINDOWS;
+    const bool written = wrote == MAE_AFTER_LIST || check_window ||
+                         (wrote == MAE_AFTER_SECOND && list[MAE_LIST_UNUSABLE] != 0u && list[MAE_NO_LIST_AT_ALL] == 0u);
+    uint32_t stretch_full = 0, missed = 0;
+    if (written)
+        for (uint32_t i = threadIdx.x; i < cand_waves; i += 1024) stretch_full |= cand_count[i] > cand_cap ? 1u : 0u;
     MaeLevelState s = state[l];
     unsigned long long b[4], sum = 0ull;
 #pragma unroll
@@ -946,19 +978,25 @@ __global__ __launch_bounds__(1024) void mae_select_kernel(MaeLevelState* __restr
         s.prefix = (s.prefix << (s.hi - lo)) | digit;
         s.base = nb;
         s.hi = lo;
-        if (check_window && !((digit - s.win_lo) < s.win_len)) list_bad = 1u;
+        if (check_window && !((digit - s.win_lo) < s.win_len)) missed = 1u;
     }
-    int any_bad = 0;
-    if (cand_count != nullptr) {  // uniform
-        any_bad = __syncthreads_or((int)list_bad);
-        if (threadIdx.x == 0) *cand_full = any_bad ? 1u : 0u;
+    if (written) {  // uniform
+        const uint32_t any_full = (uint32_t)__syncthreads_or((int)stretch_full);
+        if (check_window) missed = (uint32_t)__syncthreads_or((int)missed);
+        if (threadIdx.x == 0) {
+            list[MAE_LIST_UNUSABLE] = any_full != 0u || missed != 0u ? 1u : 0u;
+            if (check_window) {
+                list[MAE_DIGITS_MISSING] = missed != 0u ? 1u : 0u;
+                list[MAE_WINDOW_OUTCOME] = missed != 0u ? MAE_WINDOW_MISSED : any_full != 0u ? MAE_STRETCH_FULL : MAE_LIST_SERVED;
+            }
+        }
     }
-    if (lane == 0 && !(check_window && any_bad)) state[l] = s;
+    if (lane == 0 && !(check_window && missed != 0u)) state[l] = s;
     if (!last) return;
     __shared__ double med[16], den[16];
     __shared__ unsigned long long cnt[17];
-    // the records of mae_window_kernel, or of mae_pass_kernel where that did not do
-    const uint32_t n_rec = (n_part_scan != 0u && *cand_full != 0u) ? n_part_scan : n_part;
+    // the records of mae_window_kernel, or of mae_pass_kernel where that did not run
+    const uint32_t n_rec = (n_part_scan != 0u && list[MAE_DECLINED] != 0u) ? n_part_scan : n_part;
     unsigned long long k_l = 0ull, k_out = 0ull;
     for (uint32_t i0 = lane; i0 < n_rec; i0 += 64 * 4) {  // four independent loads in flight (integers: any order)
         unsigned long long a[4], b[4];

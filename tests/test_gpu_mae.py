@@ -165,19 +165,22 @@ def test_mae_step_skips_pinned_regions(signed, opq):
 
 
 def _sampled_tiles(n_tiles):
-    """Which wave tiles (4096 weights at block 64) the sampling pass of the MAE step looks at: one in 16, by the
-    multiplicative hash that bof4_mae.h documents."""
+    """Which wave tiles (4096 weights at block 64) the sampling pass of the MAE step looks at: one in 8 to 64, the most for
+    which 2000 or more are left, by the multiplicative hash that bof4_mae.h documents."""
+    one_in = 8
+    while one_in < 64 and n_tiles // (2 * one_in) >= 2000:
+        one_in *= 2
     t = np.arange(n_tiles, dtype=np.uint64)
-    return (((t * np.uint64(0x9E3779B1)) & np.uint64(0xFFFFFFFF)) >> np.uint64(16)) & np.uint64(15) == 0
+    return (((t * np.uint64(0x9E3779B1)) & np.uint64(0xFFFFFFFF)) >> np.uint64(16)) & np.uint64(one_in - 1) == 0
 
 
 @pytest.mark.parametrize("misled", [False, True])
 def test_mae_one_pass_search_and_its_fallback(misled, capfd, monkeypatch):
-    """From 2^26 weights up the step reads the weights once: a sampling pass over one tile in 16 places a window of
+    """From 2^26 weights up the step reads the weights once: a sampling pass over one tile in 8 or more places a window of
     first digits per region, the full pass writes the elements inside to the list.  On ordinary data the exact first
     digit falls inside the window and the list serves all later passes; if the sampled tiles are unlike the rest
-    (here: cubed, which moves every region's median) the windows miss and the later passes scan the weights.  Both
-    ways return the oracle's medians bit for bit; the library's trace line says which way was taken."""
+    (here: cubed, which moves every region's median) the windows miss, the first pass follows and the second one writes the
+    list.  Both ways return the oracle's medians bit for bit; the library's trace line says which way was taken."""
     n_tiles = 16384 + 37
     g = torch.Generator().manual_seed(4242)
     w = torch.randn(n_tiles * 4096, generator=g)
@@ -194,6 +197,7 @@ def test_mae_one_pass_search_and_its_fallback(misled, capfd, monkeypatch):
     got = binding.bof4_lloyd_step_mae(w.to(DEV), 64, cb, 1, skip_mask=pin)
     trace = capfd.readouterr().err
     assert "sampling 1" in trace and f"list unusable {1 if misled else 0}" in trace, trace
+    assert ("windows missed, written by the second pass" in trace) == misled, trace
     wanted = np.array([not ((pin >> l) & 1) for l in range(16)])
     assert np.array_equal(got["median"][wanted], o["median"][wanted]) and np.all(np.isnan(got["median"][~wanted]))
     assert np.array_equal(got["den"], o["den"]) and np.array_equal(got["cnt"], o["cnt"])
@@ -229,13 +233,37 @@ def test_mae_one_pass_search_with_opq(block, signed, weighted, capfd, monkeypatc
     assert abs(got["sae"] - o["sae"]) <= RTOL * o["sae"]
 
 
-@pytest.mark.parametrize("case", ["zeros", "clumps", "close levels", "few values"])
+@pytest.mark.parametrize("block,opq", [(32, 1), (64, 0), (64, 1), (128, 0), (128, 1), (256, 0), (256, 1)])
+def test_mae_one_pass_search_without_the_bin_table(block, opq, capfd, monkeypatch):
+    """The one-pass search with two levels closer than a bin of the search table (every weight is compared with all thresholds),
+    all regions wanted that the list can serve: medians, masses and counts as the oracle's."""
+    n = (16384 + 5) * 64 * min(block, 64) + 3 * block
+    w = make_weights(1, n, seed=811 + block)
+    cb = mae_cb(block, 1).copy()
+    cb[10] = cb[9] + 0.004
+    T = oracle.opq_threshold(0.95, block) if opq else 0.0
+    skip = codebooks.PIN_BOF4S if opq else 0
+    st, o = oracle.lloyd_step_mae(inputs.bits(w), block, cb, 1, opq_T=T)
+    assert st == oracle.OK
+    monkeypatch.setenv("BOF4_MAE_TRACE", "1")
+    capfd.readouterr()
+    got = binding.bof4_lloyd_step_mae(w.to(DEV), block, cb, 1, opq_T=T, skip_mask=skip)
+    assert "sampling 1" in capfd.readouterr().err
+    wanted = np.array([not ((skip >> l) & 1) for l in range(16)])
+    assert np.array_equal(got["median"][wanted], o["median"][wanted], equal_nan=True)
+    assert np.array_equal(got["den"], o["den"]) and np.array_equal(got["cnt"], o["cnt"])
+    assert got["n_outliers"] == o["n_outliers"] and abs(got["sae"] - o["sae"]) <= RTOL * o["sae"]
+
+
+@pytest.mark.parametrize("case", ["zeros", "clumps", "close levels", "few values", "full stretch"])
 @pytest.mark.parametrize("block", [32])
 def test_mae_one_pass_search_edges(block, case, capfd, monkeypatch):
     """The one-pass search just above the size from which it samples, ragged tail: the region around zero wanted, its
     median among zeros of both signs (a window's edge may lie between them); tiles in which several hundred elements lie inside a
-    window (they are listed in several goes); a codebook with two levels closer than a bin of the search table; and a tensor
-    of few values, for which no list is tried.  Medians, masses and counts as the oracle's, and the error sum bit for bit
+    window (they are listed in several goes: the trace says how full the fullest wave's stretch of 682 entries is, at most half
+    on ordinary weights); a codebook with two levels closer than a bin of the search table; a tensor
+    of few values, for which no list is tried; and one tile of equal weights inside a window, which fill more than a wave's stretch
+    of the list (the digits stand, and the other passes do without that list).  Medians, masses and counts as the oracle's, and the error sum bit for bit
     that of the passes over all the weights."""
     tile = 64 * block
     n = (16384 + 3) * tile + 3 * block
@@ -246,9 +274,13 @@ def test_mae_one_pass_search_edges(block, case, capfd, monkeypatch):
         z = torch.randint(0, 64, (n,), generator=g)
         w[z == 0], w[z == 1] = 0.0, -0.0
         skip = 0xffff ^ (1 << 7)
-    elif case == "clumps":
-        tiles = w[: 64 * tile].reshape(64, 64, block)  # the first tile of 64 waves: seven blocks of nearly equal weights
-        tiles[:, 5:40:5, 0], tiles[:, 5:40:5, 1:] = 1.0, 0.34 + 0.001 * torch.rand((64, 7, block - 1), generator=g)
+    elif case == "clumps":  # the first tile of 64 waves: seven blocks of weights next to the median of region 11
+        tiles = w[: 64 * tile].reshape(64, 64, block)
+        tiles[:, 5:40:5, 0], tiles[:, 5:40:5, 1:] = 1.0, 0.337890625
+    elif case == "full stretch":
+        assert not _sampled_tiles(2)[1]
+        blocks = w[tile: 2 * tile].reshape(64, block)
+        blocks[:, 0], blocks[:, 1:], usable = 1.0, 0.337890625, 0
     elif case == "close levels":
         cb = cb.copy()
         cb[10] = cb[9] + 0.004
@@ -257,12 +289,16 @@ def test_mae_one_pass_search_edges(block, case, capfd, monkeypatch):
     w = w.to(torch.bfloat16)
     st, o = oracle.lloyd_step_mae(inputs.bits(w), block, cb, 1)
     assert st == oracle.OK
-    monkeypatch.setenv("BOF4_MAE_TRACE", "1")
+    monkeypatch.setenv("BOF4_MAE_TRACE", "2")
     capfd.readouterr()
     wd = w.to(DEV)
     got = binding.bof4_lloyd_step_mae(wd, block, cb, 1, skip_mask=skip)
     trace = capfd.readouterr().err
     assert "sampling 1" in trace and f"list unusable {1 - usable}" in trace, trace
+    assert ("declined" in trace) == (case == "few values") and ("a stretch ran full" in trace) == (case == "full stretch"), trace
+    fullest = int(trace.split("fullest stretch ")[1].split(" of ")[0])
+    # (ordinary waves hold 250 to 330 entries here, 64 of them seven times 31 more)
+    assert case != "clumps" or 250 + 217 <= fullest <= 682, trace
     assert case != "zeros" or o["median"][7] == 0.0
     wanted = np.array([not ((skip >> l) & 1) for l in range(16)])
     assert np.array_equal(got["median"][wanted], o["median"][wanted], equal_nan=True)
