@@ -256,9 +256,12 @@ static_assert(pass_grid(false, true, false) <= PASS_GRID_MAX && pass_grid(false,
 // the windows let so much through that the list is three quarters full; at 4096 tiles it is 99 against 90.
 constexpr uint64_t MAE_SAMPLED_TILES = 2000;
 constexpr uint64_t MAE_SAMPLING_MIN_TILES = 16384;
-uint32_t mae_sample_mask(uint64_t tiles) {
+// With a median wanted in an outermost region one in 16 at the least: every block has an element there that is 1 or -1, up to
+// one weight in 32, which lie in one digit and take half of the list's room, so that the other windows have to be narrow (537 M
+// Gaussian weights at block 64, no region skipped: one in 64 fills the list, 1262 us, one in 16 does not, 660).
+uint32_t mae_sample_mask(uint64_t tiles, bool outermost) {
     uint32_t one_in = 8;
-    while (one_in < 64 && tiles / (2 * one_in) >= MAE_SAMPLED_TILES) one_in *= 2;
+    while (one_in < (outermost ? 16u : 64u) && tiles / (2 * one_in) >= MAE_SAMPLED_TILES) one_in *= 2;
     return one_in - 1;
 }
 static_assert(MAE_SAMPLING_MIN_TILES / 8 >= MAE_SAMPLED_TILES, "one in 8 is enough from there on");
@@ -1679,7 +1682,7 @@ int bof4_lloyd_step_mae(const void* w_dev, uint64_t n, uint32_t block, const dou
                            wrote == MAE_AFTER_WINDOWS ? window_cap : cand_cap, list, direct ? direct : rec_dev, unweighted);
     };
     if (sampling) {
-        const uint32_t sample_mask = mae_sample_mask(tiles);
+        const uint32_t sample_mask = mae_sample_mask(tiles, (skip_mask & 0x8001u) != 0x8001u);
         BOF4_LAUNCH_MAE_BLOCK(MAE_SAMPLE, no_list, sample_mask, 0)
         hipLaunchKernelGGL(mae_predict_kernel, dim3(1), dim3(1024), 0, s, state, hist, (double)n / (sample_mask + 1),
                            (uint32_t)skip_mask, (double)mae_cand_entries(n) / (sample_mask + 1), list);

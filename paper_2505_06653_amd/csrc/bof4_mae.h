@@ -805,18 +805,22 @@ __global__ __launch_bounds__(256, 3) void mae_window_kernel(const uint4* __restr
     }
 }
 
-// After the sampling pass (over `sampled` elements): one wave per region reads the sampled first-digit histogram, finds
-// where the sample's weighted median lies, and sets the window of first digits that the full first pass will capture: the sampled place
-// plus or minus six standard deviations of a sampled quantile (0.5 / sqrt(samples), widened by half for the unequal
-// weights), converted to digits by the share of the region's weight that the median's digit holds, at least half a
-// digit to either side.  Clears the bins.  The search state proper is left alone.  If the windows would fill more
-// than four fifths of the list's room (few values, many of them equal) or have more digits than mae_window_kernel has
-// bins, the list is declined: all passes scan the weights.
+// After the sampling pass (over `sampled` elements): one wave per region reads the sampled first-digit histogram and sets the
+// window of first digits that mae_window_kernel will capture: from the digit below which half of the sample's weight lies less
+// six standard deviations of a sampled quantile (0.5 / sqrt(samples), widened by half for the unequal weights) to the one
+// with as much more, and half a digit to either side of the sample's median.  (Not so many digits as the median's
+// weight makes of six deviations: around zero a digit is an octave and holds next to nothing, and between the atoms of a
+// tensor of some hundred values there are digits without any.  That took in most of the region or missed the next atom:
+// 537 M Gaussian weights with the region around zero wanted 1992 us, now 660.)  Clears the bins.  The search state proper
+// is left alone.  If the windows would take in more than 6 % of the weights (few values, many of them equal) or have more
+// digits than mae_window_kernel has bins, it does not run: capturing would cost more than the first pass's histogram.  (Not
+// already where they would fill the list: the digits it finds and its sums stand if a stretch runs full.)  And if the
+// medians' digits alone would fill the list, no pass writes one.
 __global__ __launch_bounds__(1024) void mae_predict_kernel(MaeLevelState* __restrict__ state,
                                                            unsigned long long* __restrict__ hist,
                                                            double sampled, uint32_t skip_mask, double list_room,
                                                            uint32_t* __restrict__ list) {
-    __shared__ double expected[16];
+    __shared__ double expected[16], least[16];
     __shared__ uint32_t bins[16];
     __shared__ double share[16];
     const uint32_t lane = threadIdx.x & 63, l = threadIdx.x >> 6;  // wave l = region l
@@ -841,7 +845,7 @@ __global__ __launch_bounds__(1024) void mae_predict_kernel(MaeLevelState* __rest
     for (int i = 0; i < 16; ++i) all += share[i];
     const double samples = all > 0.0 ? sampled * ((double)total / all) : 0.0;
     uint32_t win_lo = 0, win_len = 0;
-    double captured = 0.0;  // elements of the sample inside the window
+    double captured = 0.0, median_digits = 0.0;  // elements of the sample inside the window, and in the median's digit
     if (total != 0ull && ((skip_mask >> l) & 1u) == 0u) {  // wave-uniform
         const unsigned long long ballot = __builtin_amdgcn_ballot_w64(2ull * incl >= total);
         const uint32_t L = ballot ? (uint32_t)__builtin_ctzll(ballot) : 63u;
@@ -864,14 +868,27 @@ __global__ __launch_bounds__(1024) void mae_predict_kernel(MaeLevelState* __rest
         const double mass_d = (double)(unsigned long long)__shfl((long long)mass, (int)L, 64);
         const double tot = (double)total;
         const double place = (double)digit + (mass_d > 0.0 ? (0.5 * tot - below_d) / mass_d : 0.5);
-        const double sigma_q = 0.75 / sqrt(samples);
-        double half = mass_d > 0.0 ? 6.0 * sigma_q * tot / mass_d : 256.0;
-        if (half < 0.5) half = 0.5;
-        if (half > 256.0) half = 256.0;
-        const double lo_d = floor(place - half), hi_d = floor(place + half);
-        const int lo_i = lo_d < 0.0 ? 0 : (int)lo_d, hi_i = hi_d > 255.0 ? 255 : (int)hi_d;
+        const double six_sigma = 6.0 * 0.75 / sqrt(samples);
+        auto digit_of = [&](double weight) {  // the first digit up to and including which there is at least that much
+            const unsigned long long reached = __builtin_amdgcn_ballot_w64((double)incl >= weight);
+            if (reached == 0ull) return 255;
+            unsigned long long below_k = incl - sum;
+            int k_at = 3;
+#pragma unroll
+            for (int k = 3; k >= 0; --k) {
+                unsigned long long up_to = below_k;
+#pragma unroll
+                for (int i = 0; i <= k; ++i) up_to += b[i];
+                if ((double)up_to >= weight) k_at = k;
+            }
+            return __shfl((int)(4 * lane) + k_at, (int)__builtin_ctzll(reached), 64);
+        };
+        const int from = min(digit_of((0.5 - six_sigma) * tot), (int)floor(place - 0.5));
+        const int to = max(digit_of((0.5 + six_sigma) * tot), (int)floor(place + 0.5));
+        const int lo_i = max(from, 0), hi_i = min(to, 255);
         win_lo = (uint32_t)lo_i;
-        win_len = hi_i >= lo_i ? (uint32_t)(hi_i - lo_i + 1) : 0u;
+        win_len = (uint32_t)(hi_i - lo_i + 1);
+        median_digits = mass_d / tot * samples;
         double inside = 0.0;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
@@ -884,18 +901,21 @@ __global__ __launch_bounds__(1024) void mae_predict_kernel(MaeLevelState* __rest
         state[l].win_lo = win_lo;
         state[l].win_len = win_len;
         expected[l] = captured;
+        least[l] = median_digits;
         bins[l] = win_len + 2;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        double sum_captured = 0.0;
+        double sum_captured = 0.0, sum_least = 0.0;
         uint32_t sum_bins = 0;
         for (int i = 0; i < 16; ++i) {
             sum_captured += expected[i];
+            sum_least += least[i];
             sum_bins += bins[i];
         }
-        const uint32_t declined = sum_captured > 0.8 * list_room || sum_bins > MAE_WINDOW_BINS ? 1u : 0u;
-        list[MAE_LIST_UNUSABLE] = list[MAE_DIGITS_MISSING] = list[MAE_DECLINED] = list[MAE_NO_LIST_AT_ALL] = declined;
+        const uint32_t declined = sum_captured > 0.06 * sampled || sum_bins > MAE_WINDOW_BINS ? 1u : 0u;
+        list[MAE_LIST_UNUSABLE] = list[MAE_DIGITS_MISSING] = list[MAE_DECLINED] = declined;
+        list[MAE_NO_LIST_AT_ALL] = sum_least > 0.95 * list_room ? 1u : 0u;
         list[MAE_WINDOW_OUTCOME] = declined ? MAE_LIST_DECLINED : MAE_LIST_SERVED;
     }
 }

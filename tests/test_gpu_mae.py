@@ -255,6 +255,28 @@ def test_mae_one_pass_search_without_the_bin_table(block, opq, capfd, monkeypatc
     assert got["n_outliers"] == o["n_outliers"] and abs(got["sae"] - o["sae"]) <= RTOL * o["sae"]
 
 
+def test_mae_one_pass_search_on_a_large_tensor_with_all_regions_wanted(capfd, monkeypatch):
+    """2^29 weights and more, where the list has room for one weight in 32, no region skipped: ordinary weights are served by the
+    windows' list, although the region around zero has octaves for digits and the outermost one holds 1 for every block.
+    Medians, masses, counts and the error sum as those of the passes over all the weights."""
+    n = (1 << 29) + 64 * 64 * 5 + 64
+    g = torch.Generator(device=DEV)
+    g.manual_seed(77)
+    w = torch.empty(n, dtype=torch.bfloat16, device=DEV)
+    for a in range(0, n, 1 << 27):
+        w[a: a + (1 << 27)] = torch.randn(min(1 << 27, n - a), generator=g, device=DEV).to(torch.bfloat16)
+    monkeypatch.setenv("BOF4_MAE_TRACE", "1")
+    capfd.readouterr()
+    got = binding.bof4_lloyd_step_mae(w, 64, mae_cb(64, 1), 1)
+    trace = capfd.readouterr().err
+    assert "sampling 1, list unusable 0" in trace, trace
+    monkeypatch.setenv("BOF4_MAE_NO_SAMPLING", "1")
+    two = binding.bof4_lloyd_step_mae(w, 64, mae_cb(64, 1), 1)
+    for k in ("median", "den", "cnt"):
+        assert np.array_equal(two[k], got[k], equal_nan=True), k
+    assert two["sae"] == got["sae"] and got["cnt"].sum() == n
+
+
 @pytest.mark.parametrize("case", ["zeros", "clumps", "close levels", "few values", "full stretch"])
 @pytest.mark.parametrize("block", [32])
 def test_mae_one_pass_search_edges(block, case, capfd, monkeypatch):
