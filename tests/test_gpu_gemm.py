@@ -397,6 +397,54 @@ def test_gemm_decoded_first_rounds_no_more_than_the_kernel_it_replaces(rules, ro
     assert err[0] <= 1.005 * err[1]
 
 
+@pytest.mark.parametrize("listed", [False, True])
+@pytest.mark.parametrize("rows,cols,n_tokens,split,carry", [
+    (4100, 1056, 2500, 1, 1), (8001, 1056, 2500, 1, 0), (4096, 4096, 1200, 1, 1), (4096, 11008, 900, 2, 1), (8193, 8192, 900, 2, 1)])
+def test_gemm_decoded_first_exact_sums_unit_vectors_and_sums_that_are_not_finite(rules, rows, cols, n_tokens, split, carry, listed):
+    """The decoded kernels with and without carried sums (`carry`: without a list), one part and two.  Levels k / 8, constants 2^e, x
+    small integers, list values multiples of 1 / 8: every product and every sum is a multiple of 2^-9 below 2^15, so that no
+    addition rounds and binary64 on the GPU has the same numbers.  Then a unit vector per token, which picks one column of the
+    decoded matrix; and infinite and undefined terms early, at the edge of a chunk and late, which leave the other tokens as
+    they are."""
+    plan = rules(rows, cols, n_tokens, listed)
+    assert (plan.way, plan.decoded_split, plan.decoded_carry) == (2, split, 1 if listed else carry)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + cols)
+    block, n = 32, rows * cols
+    cb = (np.arange(16) - 8) / 8.0
+    codes = torch.randint(0, 256, (n // 2,), generator=g, device=DEV, dtype=torch.uint8)
+    xmax = 4 if cols <= 2048 else 1  # |product| <= 4 * xmax or xmax, times cols below 2^15
+    scales = torch.exp2(torch.randint(-6, 3 if cols <= 2048 else 1, (n // block,), generator=g, device=DEV).float()).to(torch.float16)
+    oi = ov = tab = None
+    k = 0
+    if listed:
+        oi = torch.unique(torch.randint(0, n, (n // 300,), generator=g, device=DEV))
+        k = oi.numel()
+        top = 32 if cols <= 2048 else 8
+        ov = (torch.randint(-top, top + 1, (k,), generator=g, device=DEV).float() / 8).to(torch.float16)
+        tab = binding.bof4_gemm_outlier_table(codes, scales, rows, cols, block, cb, oi, ov)
+    packed = binding.bof4_gemm_pack(codes, scales, rows, cols, block)
+    w = binding.bof4_dequantize(codes, scales, n, block, cb, oi, ov).reshape(rows, cols).double()
+    x = torch.randint(-xmax, xmax + 1, (n_tokens, cols), generator=g, device=DEV).to(torch.bfloat16)
+    ref = x.double() @ w.T
+    assert float((x.double().abs() @ w.abs().T).max()) < 2 ** 15
+    y = binding.bof4_gemm(packed, rows, cols, cb, x, tab, k)
+    assert torch.equal(y.double(), ref)
+    bad = {3: (0, "inf"), 130: (63, "-inf"), 131: (cols // 2, "nan"), n_tokens - 1: (cols - 1, "inf")}
+    for t, (c, v) in bad.items():
+        x[t, c] = float(v)
+    z = binding.bof4_gemm(packed, rows, cols, cb, x, tab, k)
+    rest = torch.ones(n_tokens, dtype=torch.bool, device=DEV)
+    rest[list(bad)] = False
+    want = x[~rest].double() @ w.T
+    assert torch.equal(z[rest], y[rest]) and not bool(want.isfinite().any())
+    assert torch.equal(z[~rest].double().nan_to_num(nan=7.0), want.nan_to_num(nan=7.0))
+    picks = torch.arange(n_tokens, device=DEV) * 61 % cols
+    x.zero_()
+    x[torch.arange(n_tokens, device=DEV), picks] = 1.0
+    assert torch.equal(binding.bof4_gemm(packed, rows, cols, cb, x, tab, k).double(), w[:, picks].T)
+
+
 @pytest.mark.parametrize("rows,cols,n_tokens", [(300, 2304, 330), (520, 512, 600)])
 def test_gemm_wide_tile_is_exact_where_every_partial_sum_is_a_binary32_number(rows, cols, n_tokens):
     """As for the other kernel: levels k / 8, constants 2^e, x small integers, list values multiples of 1 / 8, so that no
