@@ -245,10 +245,6 @@ static_assert(pass_grid(false, true, false) <= PASS_GRID_MAX && pass_grid(false,
                   ERR_GRID <= PASS_GRID_MAX,
               "workspace sized for fewer workgroups");
 // MAE step: histogram, search state, per-wave counts, per-workgroup floating-point partials, result record.
-// Entries of the candidate list of the MAE step, dealt out evenly to the waves of the pass kernels: n / 32 (four
-// times what the windows of the one-pass search let through on a large tensor, five times what a second pass
-// leaves), at most 2^27; below 2^29 weights n / 16, because the windows are wider there (fewer samples to place them:
-// 4 to 5 % of the weights at 2^26) and a wave's share of the list is small enough for its fill to vary.
 // The MAE step places its windows by the largest power of two in the tiles that leaves 2000 of them or more, at most one in
 // 64: about one for each wave of the sampling pass.  Fewer make the windows wider, more take longer (655 M weights, one in
 // 32 / 16 / 8 / 4 / 2: 572 / 594 / 643 / 740 / 900 us; 65 M: 138 at one in 16, 134 / 134 / 149).  From 16384 tiles (2^26
@@ -265,6 +261,11 @@ uint32_t mae_sample_mask(uint64_t tiles, bool outermost) {
     return one_in - 1;
 }
 static_assert(MAE_SAMPLING_MIN_TILES / 8 >= MAE_SAMPLED_TILES, "one in 8 is enough from there on");
+// Entries of the candidate list of the MAE step, dealt out evenly to the waves of the kernel that writes it: n / 32 (five
+// times what a second pass leaves; with the pinned levels skipped the windows of the one-pass search fill the fullest
+// wave's share to 69 % at most over six distributions, 2^29 weights and more), at most 2^27; below 2^29 weights n / 16,
+// because the windows are wider there (fewer samples to place them: 46 % at most) and a wave's share of the list is small
+// enough for its fill to vary.
 uint64_t mae_cand_entries(uint64_t n) {
     const uint64_t e = n < (1ull << 29) ? n / 16 : n / 32;
     return e < (1ull << 27) ? e : (1ull << 27);
@@ -1743,7 +1744,8 @@ int bof4_lloyd_step_mae(const void* w_dev, uint64_t n, uint32_t block, const dou
             for (uint32_t c : counts) most = c > most ? c : most;
             MaeLevelState st[16];
             HIP_TRY(hipMemcpy(st, state, sizeof(st), hipMemcpyDeviceToHost));
-            std::fprintf(stderr, "  fullest stretch %u of %u entries;", most, by_windows ? window_cap : cand_cap);
+            if (sampling && o == MAE_LIST_DECLINED && word[MAE_NO_LIST_AT_ALL]) std::fprintf(stderr, "  no list;");
+            else std::fprintf(stderr, "  fullest stretch %u of %u entries;", most, by_windows ? window_cap : cand_cap);
             for (int l = 0; l < 16; ++l)
                 std::fprintf(stderr, " [%d: window %u+%u, key %u of %u bits]", l, st[l].win_lo, st[l].win_len,
                              st[l].prefix, lc.bits[l]);
