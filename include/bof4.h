@@ -166,9 +166,10 @@ typedef struct {
  * maximum as stored in binary16, for absolute and signed normalisation alike) is found by a radix search that reads
  * the weights twice and then a list of the few elements still in question (in the workspace: n / 4 bytes, n / 2
  * below 2^29 weights; if the list runs full - a tensor of equal numbers - or outliers must be tracked through the
- * region around zero, the weights are read three or four times instead).  From 2^26 weights up (at block 64) the weights are read once, after a look at
- * one tile of 4096 weights in 16 that tells the search where to expect the medians; if those tiles are unlike the rest
- * of the tensor the search notices and reads the weights again as above - the result is the same either way.  Two
+ * region around zero, the weights are read three or four times instead).  From 2^26 weights up (at block 64) the weights
+ * are read once, after a look at one tile of 4096 weights in 8 to 64 that tells the search where to expect the medians; if
+ * those tiles are unlike the rest of the tensor the search notices and reads the weights again as above, and if the list
+ * runs full the second pass over the weights writes it anew - the result is the same either way.  Two
  * environment variables help when looking into this: BOF4_MAE_TRACE (set: every call prints to stderr which way it
  * went; set to 2: also how full the fullest wave's stretch of the list got and every region's window) and
  * BOF4_MAE_NO_SAMPLING (set: always the two-pass search).  The appendix's closing formula names the element before the
@@ -305,7 +306,7 @@ int bof4_quant_error(const void* w_dev, uint64_t n, uint32_t block, const double
  *   table_dev   what bof4_gemv_outlier_table made of the outlier list (n_outliers entries); may be NULL when
  *               n_outliers == 0
  *   x_dev       n_tokens x cols bfloat16 (device, 16-byte aligned), y_dev  n_tokens x rows binary32 (device)
- * Limits: cols <= 32768.  The matrix is read once per pair of tokens.  Only enqueues.
+ * Limits: cols <= 32768.  The matrix is read once per up to four tokens (two for some large ones).  Only enqueues.
  */
 int bof4_gemv(const uint8_t* codes_dev, const uint16_t* scales_dev, uint64_t rows, uint64_t cols, uint32_t block,
               const double* cb_host, const void* table_dev, uint64_t n_outliers, const void* x_dev,
@@ -326,13 +327,14 @@ size_t bof4_gemv_outlier_table_bytes(uint64_t rows, uint64_t cols, uint64_t n_ou
 /*
  * The decoder inside a matrix product for many tokens, as the paper's inference path runs it: the matrix is decoded to
  * bfloat16 (section 2.1 eq. 3 rounded as bof4_dequantize rounds it, outliers of section 3.3 as stored) and multiplied
- * with bfloat16 activations, binary32 accumulation - without the decoded matrix ever reaching memory:
+ * with bfloat16 activations, binary32 accumulation - inside one kernel, or for several hundred tokens and more by a
+ * kernel of its own into the workspace, whole or in slabs, once per call:
  *     y[t][r] = sum_c W^[r][c] * x[t][c],     W^ = what bof4_dequantize returns for the same quantised tensor.
  * Every product of two bfloat16 numbers is exact in binary32; the sums are binary32 (matrix cores, up to 128 tokens
  * per pass over the codes) in a fixed order: y is bit-reproducible and lies within (cols + 64) * 2^-24 * sum_c |W^ x|
  * of the exact sum, and is exact whenever every partial sum is a binary32 number.  The order of the additions depends
- * on rows, cols, n_tokens (how the columns are dealt out over workgroups) and on whether the workspace has its full size,
- * so the same token may differ in its last bits between calls with different n_tokens; equal calls give equal bits.
+ * on rows, cols, n_tokens (how the columns are dealt out over workgroups), on whether there is a list and on whether the
+ * workspace has its full size, so the same token may differ in its last bits between calls with different n_tokens; equal calls give equal bits.
  *
  * The matrix is read from a copy in the order of the matrix cores' operands, made once per matrix by bof4_gemm_pack
  * from what bof4_quantize wrote for n = rows * cols (row-major [rows x cols], cols a multiple of block):
@@ -353,8 +355,8 @@ size_t bof4_gemv_outlier_table_bytes(uint64_t rows, uint64_t cols, uint64_t n_ou
  *               4 bytes per token slot and column (token slots in 32s, columns in 64s), and for matrices with too few
  *               rows to fill the chip, up to 64 partial results of up to 128 tokens; BOF4_ERR_WORKSPACE below that.
  *               Between the two a call may take a slower kernel, whose order of additions is another
- * Limits: cols <= 32768 and a multiple of 32, n_tokens <= 65536.  The codes are read once per 128 tokens.  All three
- * calls only enqueue.
+ * Limits: cols <= 32768 and a multiple of 32, n_tokens <= 65536.  The codes are read once per 128 tokens, or
+ * once where the matrix is decoded first.  All three calls only enqueue.
  */
 int bof4_gemm(const void* packed_dev, uint64_t rows, uint64_t cols, const double* cb_host, const void* table_dev,
               uint64_t n_outliers, const void* x_dev, uint32_t n_tokens, float* y_dev, void* ws_dev, size_t ws_bytes,
