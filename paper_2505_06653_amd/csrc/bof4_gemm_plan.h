@@ -145,8 +145,9 @@ inline GemmChains gemm_chains(uint64_t rows, uint64_t cols, uint64_t n_tokens, b
 
 // Where the matrix is decoded first (gemm_decode_kernel, gemm_decoded_kernel), in slabs of whole row groups of at most
 // GEMM_DECODED_BYTES: what is decoded should still be in the 256 MB cache behind the L2s when it is multiplied (0.46 ps per
-// weight to decode 180 MB, 0.9 for 300 MB and more).  By a model of its time (us; 15 shapes at 192 to 2500 tokens): it
-// takes products from about 640 tokens on with a list, 1000 without one.  The other kernel / decoded first, measured:
+// weight to decode 180 MB, 0.9 for 300 MB and more).  By a model of its time (us; 15 shapes at 192 to 2500 tokens): on nine
+// matrices of 16 M to 470 M weights it takes all products from 384 to 1056 tokens on with a list, 544 to 1568 without one,
+// on large ones with some stretches before that (57344 x 8192 with a list: 544 to 768, then from 1056).  The other kernel / decoded first, measured:
 //   with a list      4096 x 4096, 512 / 1000 / 2000 tokens 52 / 81 / 127 -> 49 / 71 / 102, 12288 x 4096 106 / 213 / 353 -> 90 /
 //                    161 / 252, 22016 x 4096 215 / 331 / 649 -> 180 / 261 / 482, 8192 x 28672 320 / 648 / 1305 -> 371 / 573 / 1042
 //   without a list   4096 x 4096, 512 / 1000 / 2000 tokens 45 / 67 / 103 -> 48 / 66 / 93, 12288 x 4096 86 / 174 / 286 -> 85 /
